@@ -45,7 +45,8 @@ constexpr uint32_t HIST_BLOCKS = 512;
 
 template <int RB, bool GEN>
 __global__ __launch_bounds__(MQ_BLOCK) void radix_hist_kernel(SortSrc src, const uint32_t* __restrict__ keys,
-                                                              uint32_t n, int passes, uint32_t* __restrict__ part) {
+                                                              uint32_t n, int shift0, int passes,
+                                                              uint32_t* __restrict__ part) {
     using R = Radix<RB>;
     __shared__ uint32_t sh[R::MAXP * R::BUCKETS];
     for (int i = threadIdx.x; i < R::MAXP * R::BUCKETS; i += MQ_BLOCK) sh[i] = 0;
@@ -72,7 +73,7 @@ __global__ __launch_bounds__(MQ_BLOCK) void radix_hist_kernel(SortSrc src, const
         }
         const int cnt = first >= n ? 0 : (int)min((uint32_t)HIST_IPT, n - first);
         for (int p = 0; p < passes; p++) {
-            const int sh_p = p * RB;
+            const int sh_p = shift0 + p * RB;
             uint32_t cur = (k[0] >> sh_p) & R::MASK, run = 0;
 #pragma unroll
             for (int i = 0; i < HIST_IPT; i++) {
@@ -206,17 +207,18 @@ __global__ __launch_bounds__(NW * MQ_WAVE, GEN ? 4 : 1) void radix_pass_kernel(S
 
 #define MQ_RB_LIST(X) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11)
 
-hipError_t launch_radix_hist(const SortSrc& src, const uint32_t* keys, uint32_t n, int rb, int passes,
+hipError_t launch_radix_hist(const SortSrc& src, const uint32_t* keys, uint32_t n, int rb, int shift0, int passes,
                              uint32_t* part, uint32_t* hist, hipStream_t stream) {
     if (n == 0) return hipSuccess;
+    if (shift0 < 0 || passes < 1 || shift0 + (passes - 1) * rb > 31) return hipErrorInvalidValue;
     const uint32_t blocks = std::min((n + MQ_BLOCK * HIST_IPT - 1) / (MQ_BLOCK * HIST_IPT), HIST_BLOCKS);
     bool gen = keys == nullptr;
 #define MQ_H(B)                                                                                         \
     case B:                                                                                             \
         if (gen)                                                                                        \
-            radix_hist_kernel<B, true><<<blocks, MQ_BLOCK, 0, stream>>>(src, keys, n, passes, part);    \
+            radix_hist_kernel<B, true><<<blocks, MQ_BLOCK, 0, stream>>>(src, keys, n, shift0, passes, part);    \
         else                                                                                            \
-            radix_hist_kernel<B, false><<<blocks, MQ_BLOCK, 0, stream>>>(src, keys, n, passes, part);   \
+            radix_hist_kernel<B, false><<<blocks, MQ_BLOCK, 0, stream>>>(src, keys, n, shift0, passes, part);   \
         break;
     switch (rb) {
         MQ_RB_LIST(MQ_H)
@@ -229,11 +231,11 @@ hipError_t launch_radix_hist(const SortSrc& src, const uint32_t* keys, uint32_t 
 }
 
 hipError_t launch_radix_pass(int rb, int kpt, const SortSrc& src, const uint32_t* kin, const uint32_t* vin,
-                             uint32_t* kout, uint32_t* vout, uint32_t n, int pass, const uint32_t* hist_pass,
+                             uint32_t* kout, uint32_t* vout, uint32_t n, int shift, const uint32_t* hist_pass,
                              uint64_t* status, uint32_t* tile_ctr, uint32_t epoch, hipStream_t stream) {
     if (n == 0) return hipSuccess;
+    if (shift < 0 || shift > 31) return hipErrorInvalidValue;
     bool gen = kin == nullptr;
-    int shift = pass * rb;
 #define MQ_P(B, K)                                                                                          \
     {                                                                                                       \
         const uint32_t tiles = radix_tiles(n, K, B, gen);                                                   \

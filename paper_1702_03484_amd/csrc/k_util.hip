@@ -1,5 +1,5 @@
-// Small gfx950 utility kernels: fills, gathers, min/max, run boundaries,
-// duplicate flags and ID checks used when a store is loaded and indexed.
+// Small gfx950 utility kernels: fills, gathers, min/max, run boundaries and
+// duplicate flags.
 #include "device_common.h"
 #include "kernels.h"
 
@@ -246,39 +246,6 @@ hipError_t launch_dup_flags(const int32_t* p, const int32_t* s, const int32_t* o
                             uint64_t n, int32_t* keep, hipStream_t stream) {
     if (n == 0) return hipSuccess;
     dup_flags_kernel<<<grid_for(n, 256 * 8, 8192), 256, 0, stream>>>(p, s, o, perm, n, keep);
-    return hipGetLastError();
-}
-
-__global__ void check_ids_kernel(const int32_t* __restrict__ a, uint64_t n, uint32_t* __restrict__ bad) {
-    uint32_t c = 0;
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
-        int32_t v = a[i];
-        c += (v < 0 || v == INT32_MAX) ? 1u : 0u;
-    }
-    c = wave_sum(c);
-    if (mq::lane() == 0 && c) atomicAdd(bad, c);
-}
-hipError_t launch_check_ids(const int32_t* a, uint64_t n, uint32_t* bad, hipStream_t stream) {
-    if (n == 0) return hipSuccess;
-    check_ids_kernel<<<grid_for(n, 256 * 16, 2048), 256, 0, stream>>>(a, n, bad);
-    return hipGetLastError();
-}
-
-// Number of runs of equal values in x[lo, hi) (a sorted range): one per
-// position i with i == lo or x[i] != x[i-1].  Adds the count to *out with one
-// atomic per wave.
-__global__ void count_runs_kernel(const int32_t* __restrict__ x, uint64_t lo, uint64_t hi,
-                                  unsigned long long* __restrict__ out) {
-    uint32_t c = 0;
-    for (uint64_t i = lo + blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < hi; i += (uint64_t)gridDim.x * blockDim.x)
-        c += (i == lo || x[i] != x[i - 1]) ? 1u : 0u;
-    c = wave_sum(c);
-    if (mq::lane() == 0 && c) atomicAdd(out, (unsigned long long)c);
-}
-hipError_t launch_count_runs(const int32_t* x, uint64_t lo, uint64_t hi, unsigned long long* out,
-                             hipStream_t stream) {
-    if (hi <= lo) return hipSuccess;
-    count_runs_kernel<<<grid_for(hi - lo, 256 * 16, 512), 256, 0, stream>>>(x, lo, hi, out);
     return hipGetLastError();
 }
 

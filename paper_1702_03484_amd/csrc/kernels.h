@@ -85,17 +85,18 @@ hipError_t launch_key_dot(const int32_t* keys, uint32_t n, int32_t base, uint64_
 hipError_t launch_side_records(const int32_t* keys, uint32_t n, int32_t base, uint32_t id_base,
                                const uint32_t* at_dev, uint32_t* kout, uint32_t* vout, hipStream_t stream);
 
-// Digit histograms of `passes` passes into hist[passes][2^rb] (overwritten).
+// Digit histograms of `passes` passes into hist[passes][2^rb] (overwritten);
+// the first digit's lowest bit is bit `shift0` of the key.
 // keys == nullptr: read the keys from `src`.  `part` is scratch of
 // radix_hist_part_words(rb, passes) words.
-hipError_t launch_radix_hist(const SortSrc& src, const uint32_t* keys, uint32_t n, int rb, int passes,
+hipError_t launch_radix_hist(const SortSrc& src, const uint32_t* keys, uint32_t n, int rb, int shift0, int passes,
                              uint32_t* part, uint32_t* hist, hipStream_t stream);
 uint32_t radix_hist_part_words(int rb, int passes);
-// One stable pass on digit `pass`.  kin == nullptr: first-pass mode from
+// One stable pass on the digit whose lowest bit is `shift`.  kin == nullptr: first-pass mode from
 // `src` (vin ignored).  hist_pass = this pass's histogram; status holds
 // radix_tiles(n,kpt,rb,true) * 2^rb words; tile_ctr is zero before the launch.
 hipError_t launch_radix_pass(int rb, int kpt, const SortSrc& src, const uint32_t* kin, const uint32_t* vin,
-                             uint32_t* kout, uint32_t* vout, uint32_t n, int pass, const uint32_t* hist_pass,
+                             uint32_t* kout, uint32_t* vout, uint32_t n, int shift, const uint32_t* hist_pass,
                              uint64_t* status, uint32_t* tile_ctr, uint32_t epoch, hipStream_t stream);
 // record tiles of a radix pass over n records (gen: the first pass, reading
 // the input columns; its tiles are never larger than the other passes')
@@ -331,6 +332,32 @@ hipError_t launch_dict_decode(const DictDev& d, const int32_t* ids, uint32_t n, 
 hipError_t launch_dict_gather(const DictDev& d, const int32_t* ids, uint32_t n, const uint64_t* pos, uint8_t* out,
                               hipStream_t s);
 
+// ---- loading and indexing a store (k_index.hip) ---------------------------
+// Bounds of s and o together and of p, and the IDs outside [0, 2^31 - 1).
+struct IngestOut {
+    int32_t so_min, so_max, p_min, p_max;
+    uint32_t bad, pad;
+};
+// *out over n triples; unless ds == s the columns are copied to ds, dp, dq.
+hipError_t launch_ingest(const int32_t* s, const int32_t* p, const int32_t* o, int32_t* ds, int32_t* dp, int32_t* dq,
+                         uint64_t n, IngestOut* out, hipStream_t stream);
+// w1 << 32 | w0 = (p - pmin) << 2 so | s << so | o (the caller makes sure it
+// fits 64 bits; so in [0, 31]).
+hipError_t launch_pack_triples(const int32_t* s, const int32_t* p, const int32_t* o, uint64_t n, int32_t pmin, int so,
+                               uint32_t* w0, uint32_t* w1, hipStream_t stream);
+// Sorted words back to columns; r0, r1 get the words with first and second
+// exchanged, and (p - pmin, position) of every predicate's first row is appended to
+// pred/pred_pos at atomicAdd(npred) (entries past cap are only counted).
+hipError_t launch_unpack_pso(const uint32_t* w0, const uint32_t* w1, uint64_t n, int so, int32_t* first, int32_t* second,
+                             uint32_t* r0, uint32_t* r1, int32_t* pred, int64_t* pred_pos,
+                             uint32_t* npred, uint32_t cap, hipStream_t stream);
+hipError_t launch_unpack_pos(const uint32_t* w0, const uint32_t* w1, uint64_t n, int so, int32_t* first,
+                             int32_t* second, hipStream_t stream);
+// Runs of equal values per predicate (rows [off[q], off[q + 1]), np + 1
+// offsets) added to cnt[q] (pso_s) and cnt[np + q] (pos_o).
+hipError_t launch_distinct(const int32_t* pso_s, const int32_t* pos_o, int64_t n, const int64_t* off, uint32_t np,
+                           unsigned long long* cnt, hipStream_t stream);
+
 // ---- utilities (k_util.hip) -----------------------------------------------
 // Between the two passes of a two-pass scan: the run totals tot[0..nruns)
 // (nruns <= 1024) become their exclusive prefix sums, in place, capped at
@@ -380,10 +407,5 @@ hipError_t launch_run_bounds(const int32_t* v, uint64_t n, int32_t* out_val, int
 // i differs from triple i-1 (or i == 0), else 0.
 hipError_t launch_dup_flags(const int32_t* p, const int32_t* s, const int32_t* o, const uint32_t* perm,
                             uint64_t n, int32_t* keep, hipStream_t stream);
-// Runs of equal values in the sorted range x[lo, hi), added to *out.
-hipError_t launch_count_runs(const int32_t* x, uint64_t lo, uint64_t hi, unsigned long long* out,
-                             hipStream_t stream);
-// IDs outside [0, 2^31-1): count into *bad.
-hipError_t launch_check_ids(const int32_t* a, uint64_t n, uint32_t* bad, hipStream_t stream);
 
 }  // namespace mq

@@ -339,7 +339,7 @@ mapsq_status mapsq_poll_next(mapsq_ctx* ctx, uint64_t* ticket, int32_t* done, ma
  * Table 1 writes the example with string terms; the join works on their
  * identifiers.  A context holds one dictionary on the device that maps byte
  * strings to dense identifiers 0, 1, 2, ... in order of first appearance
- * and back: a batch of terms is hashed (FNV-1a, 64-bit) and inserted into an
+ * and back: a batch of terms is hashed (64-bit) and inserted into an
  * open-addressing table with a 64-bit CAS per claimed slot, the first
  * occurrences of terms it did not hold are numbered in batch order after the
  * terms it held, and their bytes are appended to its byte store.  Encoding a

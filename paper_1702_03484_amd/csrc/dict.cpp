@@ -79,18 +79,18 @@ mapsq_status dict_encode(Ctx* ctx, const uint8_t* bytes, const int64_t* offsets,
     const uint8_t* tb = bytes;
     const int64_t* to = offsets;
     int64_t total = 0;
-    Block sc = alloc_block(ctx, 64);  // scalars: err, new terms, new bytes, total
+    Block sc = alloc_block(ctx, 64);  // scalars: err, new terms, new bytes, text bytes
     if (!sc.ok()) return ctx->fail(MAPSQ_ERR_CAPACITY, "arena: no room for dictionary scalars");
     uint32_t* err = sc.as<uint32_t>();
     uint32_t* new_terms = err + 2;
     uint64_t* new_bytes = reinterpret_cast<uint64_t*>(err + 4);
     HIPCHK_D(launch_fill_u32(err, 16, 0u, ctx->stream));
     if (dev) {
-        HIPCHK_D(launch_dict_check_offsets(offsets, nn, err, ctx->stream));
-        uint32_t e = 0;
-        if (mapsq_status st = sync_read(ctx, err, 4, &e)) return st;
-        if (e) return ctx->fail(MAPSQ_ERR_INVALID_ARG, "offsets must start at 0 and not decrease");
-        if (mapsq_status st = sync_read(ctx, offsets + n, 8, &total)) return st;
+        HIPCHK_D(launch_dict_check_offsets(offsets, nn, err, reinterpret_cast<int64_t*>(err + 6), ctx->stream));
+        uint32_t e[8];
+        if (mapsq_status st = sync_read(ctx, err, sizeof(e), e)) return st;
+        if (e[0]) return ctx->fail(MAPSQ_ERR_INVALID_ARG, "offsets must start at 0 and not decrease");
+        std::memcpy(&total, &e[6], 8);
     } else {
         if (offsets[0] != 0) return ctx->fail(MAPSQ_ERR_INVALID_ARG, "offsets must start at 0 and not decrease");
         for (int64_t i = 0; i < n; i++)
@@ -108,21 +108,18 @@ mapsq_status dict_encode(Ctx* ctx, const uint8_t* bytes, const int64_t* offsets,
     }
     if (total > 0 && !tb) return ctx->fail(MAPSQ_ERR_INVALID_ARG, "null bytes");
 
-    const size_t a4 = align_up(size_t(n) * 4, ARENA_ALIGN), a8 = align_up(size_t(n) * 8, ARENA_ALIGN);
-    Block ws = alloc_block(ctx, 4 * a4 + 2 * a8 + align_up(scan_part_bytes(nn), ARENA_ALIGN) +
-                                    (dev ? 0 : a4));
+    const size_t a4 = align_up(size_t(n) * 4, ARENA_ALIGN);
+    Block ws = alloc_block(ctx, 4 * a4 + align_up(scan_part_bytes(nn), ARENA_ALIGN) + (dev ? 0 : a4));
     if (!ws.ok()) return ctx->fail(MAPSQ_ERR_CAPACITY, "arena: no room for dictionary scratch");
     char* w0 = ctx->arena.ptr(ws.off);
     DictScratch w{};
     w.rep = reinterpret_cast<uint32_t*>(w0);
     w.first = reinterpret_cast<uint32_t*>(w0 + a4);
-    w.flag = reinterpret_cast<uint32_t*>(w0 + 2 * a4);
-    w.rank = reinterpret_cast<uint32_t*>(w0 + 3 * a4);
-    w.blen = reinterpret_cast<uint64_t*>(w0 + 4 * a4);
-    w.boff = reinterpret_cast<uint64_t*>(w0 + 4 * a4 + a8);
-    w.part = w0 + 4 * a4 + 2 * a8;
-    int32_t* ids_dev = dev ? ids : reinterpret_cast<int32_t*>(w0 + 4 * a4 + 2 * a8 +
-                                                             align_up(scan_part_bytes(nn), ARENA_ALIGN));
+    w.rank = reinterpret_cast<uint32_t*>(w0 + 2 * a4);
+    w.index = reinterpret_cast<uint32_t*>(w0 + 3 * a4);
+    w.part = w0 + 4 * a4;
+    int32_t* ids_dev =
+        dev ? ids : reinterpret_cast<int32_t*>(w0 + 4 * a4 + align_up(scan_part_bytes(nn), ARENA_ALIGN));
     w.err = err;
     w.new_terms = new_terms;
     w.new_bytes = new_bytes;
@@ -133,23 +130,23 @@ mapsq_status dict_encode(Ctx* ctx, const uint8_t* bytes, const int64_t* offsets,
     uint32_t sv[6];  // err, pad, new terms, pad, new bytes (2 words)
     if (mapsq_status st = sync_read(ctx, err, sizeof(sv), sv)) return st;
     if (sv[0] & 2) {
-        if (insert) (void)launch_dict_commit(dd, t, w, (uint32_t)d.nterms, d.nbytes, 0, ctx->stream);
+        if (insert) (void)launch_dict_fix(dd, w, (uint32_t)d.nterms, 0, ctx->stream);
         return ctx->fail(MAPSQ_ERR_HIP, "dictionary table full");
     }
     uint32_t added = insert ? sv[2] : 0;
     uint64_t added_bytes = 0;
     if (insert) std::memcpy(&added_bytes, &sv[4], 8);
     if (insert && (d.nterms + (int64_t)added > d.cap_terms || d.nbytes + (int64_t)added_bytes > d.cap_bytes)) {
-        HIPCHK_D(launch_dict_commit(dd, t, w, (uint32_t)d.nterms, d.nbytes, 0, ctx->stream));
+        HIPCHK_D(launch_dict_fix(dd, w, (uint32_t)d.nterms, 0, ctx->stream));
         HIPCHK_D(hipStreamSynchronize(ctx->stream));
         return ctx->fail(MAPSQ_ERR_CAPACITY, "dictionary full: " + std::to_string(d.nterms + added) + " terms, " +
                                                  std::to_string(d.nbytes + (int64_t)added_bytes) + " bytes");
     }
+    if (insert && added)
+        HIPCHK_D(launch_dict_append(dd, t, w, (uint32_t)d.nterms, d.nbytes, added, (int64_t)added_bytes, ctx->stream));
     HIPCHK_D(launch_dict_ids(t, w, (uint32_t)d.nterms, ids_dev, ctx->stream));
-    if (insert) {
-        HIPCHK_D(launch_dict_commit(dd, t, w, (uint32_t)d.nterms, d.nbytes, 1, ctx->stream));
-        HIPCHK_D(launch_fill_u64(reinterpret_cast<uint64_t*>(d.off + d.nterms + added), 1,
-                                 (uint64_t)(d.nbytes + (int64_t)added_bytes), ctx->stream));
+    if (insert && added) {
+        HIPCHK_D(launch_dict_fix(dd, w, (uint32_t)d.nterms, 1, ctx->stream));
         d.nterms += added;
         d.nbytes += (int64_t)added_bytes;
     }
@@ -179,23 +176,24 @@ mapsq_status dict_decode(Ctx* ctx, const int32_t* ids, int64_t n, uint32_t flags
         return MAPSQ_OK;
     }
     const uint32_t nn = (uint32_t)n;
-    const size_t a8 = align_up(size_t(n) * 8, ARENA_ALIGN), a4 = align_up(size_t(n) * 4, ARENA_ALIGN);
-    Block ws = alloc_block(ctx, 2 * a8 + a4 + align_up(scan_part_bytes(nn), ARENA_ALIGN) + 64);
+    // scalars (err, the count, the total), scan partials; host calls stage the offsets and identifiers
+    const size_t a8 = align_up(size_t(n + 1) * 8, ARENA_ALIGN), a4 = align_up(size_t(n) * 4, ARENA_ALIGN);
+    const size_t ap = align_up(scan_part_bytes(nn), ARENA_ALIGN);
+    Block ws = alloc_block(ctx, ARENA_ALIGN + ap + (dev ? 0 : a8 + a4));
     if (!ws.ok()) return ctx->fail(MAPSQ_ERR_CAPACITY, "arena: no room for decode scratch");
     char* w0 = ctx->arena.ptr(ws.off);
-    uint64_t* len = reinterpret_cast<uint64_t*>(w0);
-    uint64_t* pos = reinterpret_cast<uint64_t*>(w0 + a8);
-    int32_t* ids_dev = reinterpret_cast<int32_t*>(w0 + 2 * a8);
-    void* part = w0 + 2 * a8 + a4;
-    uint32_t* err = reinterpret_cast<uint32_t*>(w0 + 2 * a8 + a4 + align_up(scan_part_bytes(nn), ARENA_ALIGN));
+    uint32_t* err = reinterpret_cast<uint32_t*>(w0);
     uint64_t* total = reinterpret_cast<uint64_t*>(err + 2);
+    void* part = w0 + ARENA_ALIGN;
+    int64_t* pos = dev ? offsets : reinterpret_cast<int64_t*>(w0 + ARENA_ALIGN + ap);
+    int32_t* ids_dev = reinterpret_cast<int32_t*>(w0 + ARENA_ALIGN + ap + a8);
     HIPCHK_D(launch_fill_u32(err, 4, 0u, ctx->stream));
     if (dev)
         ids_dev = const_cast<int32_t*>(ids);
     else
         HIPCHK_D(hipMemcpyAsync(ids_dev, ids, size_t(n) * 4, hipMemcpyHostToDevice, ctx->stream));
     const DictDev dd = dev_of(d);
-    HIPCHK_D(launch_dict_decode(dd, ids_dev, nn, len, pos, total, part, err, ctx->stream));
+    HIPCHK_D(launch_dict_decode_size(dd, ids_dev, nn, err + 1, total, part, err, ctx->stream));
     uint32_t sv[4];
     if (mapsq_status st = sync_read(ctx, err, sizeof(sv), sv)) return st;
     if (sv[0]) return ctx->fail(MAPSQ_ERR_INVALID_ARG, "an identifier outside the dictionary");
@@ -212,10 +210,8 @@ mapsq_status dict_decode(Ctx* ctx, const int32_t* ids, int64_t n, uint32_t flags
         if (!ob.ok()) return ctx->fail(MAPSQ_ERR_CAPACITY, "arena: no room to stage decoded terms");
         out = ob.as<uint8_t>();
     }
-    HIPCHK_D(launch_dict_gather(dd, ids_dev, nn, pos, out, ctx->stream));
-    const hipMemcpyKind k = dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-    HIPCHK_D(hipMemcpyAsync(offsets, pos, size_t(n) * 8, k, ctx->stream));
-    HIPCHK_D(hipMemcpyAsync(offsets + n, total, 8, k, ctx->stream));
+    HIPCHK_D(launch_dict_decode(dd, ids_dev, nn, (int64_t)need, part, pos, out, ctx->stream));
+    if (!dev) HIPCHK_D(hipMemcpyAsync(offsets, pos, size_t(n + 1) * 8, hipMemcpyDeviceToHost, ctx->stream));
     if (!dev && need > 0) HIPCHK_D(hipMemcpyAsync(bytes, out, size_t(need), hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK_D(hipStreamSynchronize(ctx->stream));
     return MAPSQ_OK;

@@ -300,12 +300,12 @@ struct TermsDev {
     const int64_t* off;
     uint32_t n;
 };
-// Per-batch device scratch: u32 arrays of n (rep, first, flag, rank), u64
-// arrays of n (blen, boff), scalars and the scan partials
-// (scan_part_bytes(n)).  first must hold ~0 before the launch and err 0.
+// Per-batch device scratch: u32 arrays of n (rep, first; rank of each first
+// occurrence of a new term, and its batch index by rank), scalars and the
+// scan partials (scan_part_bytes(n)).  first must hold ~0 before the launch
+// and err 0.
 struct DictScratch {
-    uint32_t *rep, *first, *flag, *rank;
-    uint64_t *blen, *boff;
+    uint32_t *rep, *first, *rank, *index;
     uint32_t* new_terms;
     uint64_t* new_bytes;
     void* part;
@@ -313,24 +313,29 @@ struct DictScratch {
 };
 constexpr uint32_t DICT_SCAN_MAX = 1u << 26;  // terms per batch
 size_t scan_part_bytes(uint32_t n);
-// err |= 1 unless off[0] == 0 and off is non-decreasing over n + 1 entries
-hipError_t launch_dict_check_offsets(const int64_t* off, uint32_t n, uint32_t* err, hipStream_t s);
-// hash and insert (insert = 0: look up only), then number the new terms:
-// *new_terms, *new_bytes, rank and boff of their first occurrences
+// err |= 1 unless off[0] == 0 and off is non-decreasing over n + 1 entries;
+// *total = off[n]
+hipError_t launch_dict_check_offsets(const int64_t* off, uint32_t n, uint32_t* err, int64_t* total, hipStream_t s);
+// hash and insert (insert = 0: look up only), then count the new terms:
+// *new_terms, *new_bytes and the scan partials
 hipError_t launch_dict_encode_front(const DictDev& d, const TermsDev& t, int insert, DictScratch w, hipStream_t s);
+// number the new terms (identifiers from base) and append them to the byte
+// store from bbase on: rank, index, their offsets and bytes (after
+// launch_dict_encode_front, with the totals it counted)
+hipError_t launch_dict_append(const DictDev& d, const TermsDev& t, DictScratch w, uint32_t base, int64_t bbase,
+                              uint32_t new_terms, int64_t new_bytes, hipStream_t s);
 // ids[i]: the identifier of term i (new terms: base + rank; absent: -1)
 hipError_t launch_dict_ids(const TermsDev& t, DictScratch w, uint32_t base, int32_t* ids, hipStream_t s);
-// commit = 1: append the new terms (identifiers from base, bytes from
-// bbase) and re-point their slots; commit = 0: empty the slots the batch
-// claimed, restoring the table
-hipError_t launch_dict_commit(const DictDev& d, const TermsDev& t, DictScratch w, uint32_t base, int64_t bbase,
-                              int commit, hipStream_t s);
-// decoding: len[i] of each identifier (err |= 1 for one outside the
-// dictionary), pos = their exclusive scan, *total = the sum
-hipError_t launch_dict_decode(const DictDev& d, const int32_t* ids, uint32_t n, uint64_t* len, uint64_t* pos,
-                              uint64_t* total, void* part, uint32_t* err, hipStream_t s);
-hipError_t launch_dict_gather(const DictDev& d, const int32_t* ids, uint32_t n, const uint64_t* pos, uint8_t* out,
-                              hipStream_t s);
+// the slots the batch claimed: commit = 1 re-points them to identifiers,
+// commit = 0 empties them, restoring the table
+hipError_t launch_dict_fix(const DictDev& d, DictScratch w, uint32_t base, int commit, hipStream_t s);
+// decoding: *total bytes of n identifiers and the scan partials (err |= 1
+// for one outside the dictionary; *count is scratch); then their offsets
+// pos[0 .. n] and bytes
+hipError_t launch_dict_decode_size(const DictDev& d, const int32_t* ids, uint32_t n, uint32_t* count, uint64_t* total,
+                                   void* part, uint32_t* err, hipStream_t s);
+hipError_t launch_dict_decode(const DictDev& d, const int32_t* ids, uint32_t n, int64_t total, void* part,
+                              int64_t* pos, uint8_t* out, hipStream_t s);
 
 // ---- loading and indexing a store (k_index.hip) ---------------------------
 // Bounds of s and o together and of p, and the IDs outside [0, 2^31 - 1).

@@ -243,7 +243,7 @@ mapsq_status join_batch(Ctx* ctx, const mapsq_join_desc* d, int32_t n, mapsq_tab
         }
         H.seg_off = reinterpret_cast<uint64_t*>(sb + nb4 * 4);
         H.hist = reinterpret_cast<uint32_t*>(sb + nb4 * 6);
-        H.ctr = ctx->small + SMALL_CTR;
+        H.ctr = ctx->small + SMALL_BCTR;
         H.status = ctx->status;
         H.out_base = region.ok() ? region.as<int32_t>() : nullptr;
         H.nsval = nsval;

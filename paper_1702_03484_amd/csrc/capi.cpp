@@ -62,10 +62,11 @@ mapsq_status mapsq_create(int device, void* arena, size_t arena_bytes, void* hip
     ctx->arena.init(reinterpret_cast<char*>(arena), arena_bytes);
     ctx->small_off = ctx->arena.alloc(mq::SMALL_WORDS * 4);
     ctx->small = reinterpret_cast<uint32_t*>(ctx->arena.ptr(ctx->small_off));
-    if (hipHostMalloc(&ctx->pinned, 4096, hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc(&ctx->pinned, mq::PINNED_BYTES, hipHostMallocCoherent | hipHostMallocMapped) != hipSuccess) {
         delete c;
         return MAPSQ_ERR_HIP;
     }
+    std::memset(ctx->pinned, 0, mq::PINNED_BYTES);
     if (mq::launch_fill_u32(ctx->small, mq::SMALL_WORDS, 0u, ctx->stream) != hipSuccess ||
         !ctx->ensure_status(1 << 16) || mq::join_into_setup(device) != MAPSQ_OK) {
         (void)hipHostFree(ctx->pinned);

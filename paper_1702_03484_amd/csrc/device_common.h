@@ -8,7 +8,17 @@
 #define MQ_BLOCK 256
 #define MQ_WAVES (MQ_BLOCK / MQ_WAVE)
 
+#include "mail.h"
+
 namespace mq {
+
+// Posts the words the calling thread has stored to m.data (its wave's, when
+// every lane of the wave calls the fence first): the host sees them once it
+// sees the flag.
+__device__ __forceinline__ void mail_post(const Mail& m) {
+    __threadfence_system();
+    __hip_atomic_store(m.flag, m.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 // Bounds-checked build (-DMQ_DEBUG; `python -m paper_1702_03484_amd.build
 // --debug` writes libmapsq_debug.so, loaded when MAPSQ_LIB=debug): every
@@ -212,8 +222,14 @@ __device__ __forceinline__ uint64_t tile_prefix_wave0(uint64_t* status, uint32_t
 }
 
 // Next dynamic tile id from a counter (thread 0), broadcast through LDS.
-__device__ __forceinline__ uint32_t next_tile(uint32_t* counter, uint32_t* s_slot) {
-    if (threadIdx.x == 0) *s_slot = atomicAdd(counter, 1u);
+// takes > 0: the ids the whole launch will take; whoever takes the last one
+// sets the counter back to 0, so it needs no clearing before the next launch.
+__device__ __forceinline__ uint32_t next_tile(uint32_t* counter, uint32_t* s_slot, uint32_t takes = 0) {
+    if (threadIdx.x == 0) {
+        const uint32_t t = atomicAdd(counter, 1u);
+        if (t + 1 == takes) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *s_slot = t;
+    }
     __syncthreads();
     uint32_t t = *s_slot;
     __syncthreads();

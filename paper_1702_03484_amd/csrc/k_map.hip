@@ -211,8 +211,9 @@ __device__ __forceinline__ void load_first_test(const int32_t* A, const int32_t*
 // first test compares two columns (else a column with a constant, or none)
 template <bool MULTI, bool PAIR>
 __global__ __launch_bounds__(MQ_BLOCK) void compact_fused_kernel(CompactArgs a, uint64_t* __restrict__ status,
-                                                                 uint32_t* __restrict__ run_ctr,
-                                                                 uint64_t* __restrict__ mask, CompactGrid g) {
+                                                                 uint32_t* __restrict__ run_ctr, uint32_t epoch,
+                                                                 uint64_t* __restrict__ mask, CompactGrid g,
+                                                                 Mail mail) {
     __shared__ uint32_t s_wtot[2][MQ_WAVES];
     __shared__ uint32_t s_tloc[CMP_FUSED_CHUNK];
     __shared__ uint32_t s_wofs[CMP_FUSED_CHUNK][MQ_WAVES];
@@ -221,7 +222,7 @@ __global__ __launch_bounds__(MQ_BLOCK) void compact_fused_kernel(CompactArgs a, 
     __shared__ uint64_t s_pos;
     const uint32_t w = threadIdx.x / MQ_WAVE;
     const uint64_t lt = lanemask_lt();
-    const uint32_t run_id = next_tile(run_ctr, &s_slot);
+    const uint32_t run_id = next_tile(run_ctr, &s_slot, gridDim.x);
     const uint64_t t0 = (uint64_t)run_id * g.chunk;
     const uint64_t t1 = t0 + g.chunk < g.ntiles ? t0 + g.chunk : g.ntiles;
     const int32_t* A0 = a.nterm > 0 ? a.in[a.term_a[0]] : nullptr;
@@ -306,10 +307,16 @@ __global__ __launch_bounds__(MQ_BLOCK) void compact_fused_kernel(CompactArgs a, 
     }
     __syncthreads();  // s_wofs, s_tloc and s_list complete
     if (w == 0) {
-        const uint64_t ex = tile_prefix_wave0(status, run_id, 1u, run_tot);
+        const uint64_t ex = tile_prefix_wave0(status, run_id, epoch, run_tot);
         if (lane() == 0) {
             s_pos = ex;
-            if (run_id == g.blocks - 1) *a.count = ex + run_tot;
+            if (run_id == g.blocks - 1) {
+                const uint64_t kept = ex + run_tot;
+                *a.count = kept;
+                mail.data[0] = (uint32_t)kept;
+                mail.data[1] = (uint32_t)(kept >> 32);
+                mail_post(mail);
+            }
         }
     }
     __syncthreads();
@@ -359,13 +366,15 @@ __global__ __launch_bounds__(MQ_BLOCK) void compact_fused_kernel(CompactArgs a, 
 size_t compact_scratch_words(uint64_t n) {
     const CompactGrid g = compact_grid(n);
     // run totals (u64 per run), in-run tile offsets (u32 per tile), the mask
-    // words of whole tiles, then the fused kernel's run counter (one word)
-    // and its look-back status words (one per run)
-    return (size_t)(g.blocks + (g.ntiles + 1) / 2 + g.ntiles * CMP_TILE_WORDS + 1 + CMP_FUSED_BLOCKS);
+    // words of whole tiles
+    return (size_t)(g.blocks + (g.ntiles + 1) / 2 + g.ntiles * CMP_TILE_WORDS);
 }
 
-hipError_t launch_compact(const CompactArgs& a, uint64_t* scratch, hipStream_t stream) {
-    if (a.n == 0) return hipSuccess;
+uint32_t compact_status_words() { return (uint32_t)CMP_FUSED_BLOCKS; }
+
+hipError_t launch_compact(const CompactArgs& a, uint64_t* scratch, uint64_t* status, uint32_t* run_ctr, uint32_t epoch,
+                          Mail mail, hipStream_t stream) {
+    if (a.n == 0) return hipErrorInvalidValue;
     const CompactGrid g = compact_grid(a.n);
     if (g.ntiles * MQ_BLOCK > 0xffffffffull) return hipErrorInvalidValue;  // grid size in work-items is 32-bit
     uint64_t* counts = scratch;
@@ -373,18 +382,15 @@ hipError_t launch_compact(const CompactArgs& a, uint64_t* scratch, hipStream_t s
     uint64_t* mask = scratch + g.blocks + (g.ntiles + 1) / 2;
     const CompactGrid gf = compact_grid_fused(a.n);
     if (gf.chunk <= CMP_FUSED_CHUNK) {
-        uint64_t* ctr = mask + g.ntiles * CMP_TILE_WORDS;  // word 0: run counter; then status words
-        hipError_t e = launch_fill_u64(ctr, 1 + gf.blocks, 0ull, stream);
-        if (e != hipSuccess) return e;
         const bool multi = a.nterm > 1, pair = a.nterm > 0 && a.term_b[0] >= 0;
         auto* k = multi ? (pair ? compact_fused_kernel<true, true> : compact_fused_kernel<true, false>)
                         : (pair ? compact_fused_kernel<false, true> : compact_fused_kernel<false, false>);
-        k<<<(uint32_t)gf.blocks, MQ_BLOCK, 0, stream>>>(a, ctr + 1, reinterpret_cast<uint32_t*>(ctr), mask, gf);
+        k<<<(uint32_t)gf.blocks, MQ_BLOCK, 0, stream>>>(a, status, run_ctr, epoch, mask, gf, mail);
         return hipGetLastError();
     }
     compact_test_kernel<<<(uint32_t)g.blocks, MQ_BLOCK, 0, stream>>>(a, counts, tloc, mask, g);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = launch_scan_runs(counts, (uint32_t)g.blocks, a.count, nullptr, nullptr, nullptr, stream);
+    if (e == hipSuccess) e = launch_scan_runs(counts, (uint32_t)g.blocks, a.count, nullptr, nullptr, nullptr, &mail, stream);
     if (e != hipSuccess) return e;
     compact_write_kernel<<<(uint32_t)g.ntiles, MQ_BLOCK, 0, stream>>>(a, counts, tloc, mask, g);
     return hipGetLastError();
@@ -413,13 +419,10 @@ __device__ __forceinline__ int64_t wave_bound(const int32_t* __restrict__ c, int
     return lo;
 }
 
-// one wave per query
-__global__ __launch_bounds__(MQ_WAVE) void locate_kernel(const LocateQuery* __restrict__ q, int32_t nq,
-                                                         int64_t* __restrict__ out) {
-    const int i = blockIdx.x;
-    if (i >= nq) return;
-    const LocateQuery x = q[i];
-    int64_t lo = x.lo, hi = x.hi;
+// the range of one query, by one wave
+__device__ __forceinline__ void locate(const LocateQuery& x, int64_t& lo, int64_t& hi) {
+    lo = x.lo;
+    hi = x.hi;
     if (x.col1) {
         const int64_t l = wave_bound(x.col1, lo, hi, x.v1, false);
         hi = wave_bound(x.col1, l, hi, x.v1, true);
@@ -430,15 +433,45 @@ __global__ __launch_bounds__(MQ_WAVE) void locate_kernel(const LocateQuery* __re
         hi = wave_bound(x.col2, l, hi, x.v2, true);
         lo = l;
     }
+}
+
+__global__ __launch_bounds__(MQ_WAVE) void locate_one_kernel(LocateQuery q, Mail mail) {
+    int64_t lo, hi;
+    locate(q, lo, hi);
     if (lane() == 0) {
-        out[2 * i] = lo;
-        out[2 * i + 1] = hi;
+        mail.data[0] = (uint32_t)lo;
+        mail.data[1] = (uint32_t)((uint64_t)lo >> 32);
+        mail.data[2] = (uint32_t)hi;
+        mail.data[3] = (uint32_t)((uint64_t)hi >> 32);
+        mail_post(mail);
     }
 }
 
-hipError_t launch_locate(const LocateQuery* q_dev, int32_t nq, int64_t* out, hipStream_t stream) {
-    if (nq <= 0) return hipSuccess;
-    locate_kernel<<<nq, MQ_WAVE, 0, stream>>>(q_dev, nq, out);
+// one wave per query; q and out are host-visible memory
+__global__ __launch_bounds__(MQ_WAVE) void locate_kernel(const LocateQuery* __restrict__ q, int64_t* __restrict__ out,
+                                                         uint32_t* __restrict__ done_ctr, Mail mail) {
+    int64_t lo, hi;
+    locate(q[blockIdx.x], lo, hi);
+    if (lane() == 0) {
+        out[2 * blockIdx.x] = lo;
+        out[2 * blockIdx.x + 1] = hi;
+        __threadfence_system();
+        if (atomicAdd(done_ctr, 1u) + 1 == gridDim.x) {  // every range is written
+            atomicExch(done_ctr, 0u);
+            mail_post(mail);
+        }
+    }
+}
+
+hipError_t launch_locate_one(const LocateQuery& q, Mail mail, hipStream_t stream) {
+    locate_one_kernel<<<1, MQ_WAVE, 0, stream>>>(q, mail);
+    return hipGetLastError();
+}
+
+hipError_t launch_locate(const LocateQuery* q, int32_t nq, int64_t* out, uint32_t* done_ctr, Mail mail,
+                         hipStream_t stream) {
+    if (nq <= 0) return hipErrorInvalidValue;
+    locate_kernel<<<nq, MQ_WAVE, 0, stream>>>(q, out, done_ctr, mail);
     return hipGetLastError();
 }
 

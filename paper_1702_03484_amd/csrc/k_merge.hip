@@ -98,7 +98,8 @@ __device__ __forceinline__ void bounds_i32(const int32_t* __restrict__ b, uint32
 }
 
 __global__ __launch_bounds__(MQ_BLOCK) void merge_segments_kernel(MergeArgs a, uint64_t* __restrict__ status,
-                                                                  uint32_t* __restrict__ tile_ctr, uint32_t epoch) {
+                                                                  uint32_t* __restrict__ tile_ctr, uint32_t epoch,
+                                                                  Mail mail) {
     constexpr uint32_t TILE = MQ_BLOCK * MRG_IPT;
     __shared__ uint32_t s_tile;
     __shared__ uint32_t s_wseg[MQ_WAVES];
@@ -114,7 +115,7 @@ __global__ __launch_bounds__(MQ_BLOCK) void merge_segments_kernel(MergeArgs a, u
     for (uint32_t j = threadIdx.x; j < MRG_SAMPLES; j += MQ_BLOCK) s_samp[j] = a.bkey[sample_pos(j, a.nb)];
     __syncthreads();
     for (;;) {
-        const uint32_t tile = next_tile(tile_ctr, &s_tile);
+        const uint32_t tile = next_tile(tile_ctr, &s_tile, ntiles + gridDim.x);
         if (tile >= ntiles) break;
         const uint32_t base = tile * TILE;
         uint32_t bl[MRG_IPT], bc[MRG_IPT], sc[MRG_IPT];
@@ -168,8 +169,12 @@ __global__ __launch_bounds__(MQ_BLOCK) void merge_segments_kernel(MergeArgs a, u
                 s_ex[0] = es;
                 s_ex[1] = er;
                 if (tile == ntiles - 1) {
+                    const uint64_t total = sat_add(er, row_tot > SAT40 ? SAT40 : row_tot);
                     *a.nseg = (uint32_t)(es + seg_tot);
-                    *a.total = sat_add(er, row_tot > SAT40 ? SAT40 : row_tot);
+                    mail.data[0] = (uint32_t)(es + seg_tot);
+                    mail.data[2] = (uint32_t)total;
+                    mail.data[3] = (uint32_t)(total >> 32);
+                    mail_post(mail);
                 }
             }
         }
@@ -198,11 +203,11 @@ __global__ __launch_bounds__(MQ_BLOCK) void merge_segments_kernel(MergeArgs a, u
 
 uint32_t merge_tiles(uint32_t ns) { return (ns + MQ_BLOCK * MRG_IPT - 1) / (MQ_BLOCK * MRG_IPT); }
 
-hipError_t launch_merge_segments(const MergeArgs& a, uint64_t* status, uint32_t* tile_ctr, uint32_t epoch,
+hipError_t launch_merge_segments(const MergeArgs& a, uint64_t* status, uint32_t* tile_ctr, uint32_t epoch, Mail mail,
                                  hipStream_t stream) {
     if (a.ns == 0) return hipSuccess;
     const uint32_t blocks = std::min<uint32_t>(merge_tiles(a.ns), 256u * 8u);
-    merge_segments_kernel<<<blocks, MQ_BLOCK, 0, stream>>>(a, status, tile_ctr, epoch);
+    merge_segments_kernel<<<blocks, MQ_BLOCK, 0, stream>>>(a, status, tile_ctr, epoch, mail);
     return hipGetLastError();
 }
 

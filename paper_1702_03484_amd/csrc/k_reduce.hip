@@ -217,7 +217,7 @@ hipError_t launch_seg_heads(const uint32_t* keys, const uint32_t* vals, uint32_t
     else
         heads_sum_kernel<false><<<g.blocks, MQ_BLOCK, 0, stream>>>(keys, nullptr, n, fs, ss.h_run, ss.h_tloc, g);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = launch_scan_runs(ss.h_run, g.blocks, nullptr, nseg, nullptr, nullptr, stream);
+    if (e == hipSuccess) e = launch_scan_runs(ss.h_run, g.blocks, nullptr, nseg, nullptr, nullptr, nullptr, stream);
     if (e != hipSuccess) return e;
     if (brk)
         heads_write_kernel<true><<<g.ntiles, MQ_BLOCK, 0, stream>>>(keys, brk, fs ? nullptr : vals, n, n_left, fs,
@@ -351,15 +351,15 @@ __global__ __launch_bounds__(MQ_BLOCK) void count_write_kernel(uint32_t n, const
 }
 
 hipError_t launch_seg_count(uint32_t n, const uint32_t* seg_start, const uint32_t* nseg, uint32_t max_seg,
-                            const uint32_t* seg_split, uint64_t* seg_off, uint64_t* total, uint64_t* max_pairs,
-                            void* scratch, hipStream_t stream) {
+                            const uint32_t* seg_split, uint64_t* seg_off, Mail mail, void* scratch,
+                            hipStream_t stream) {
     if (max_seg > n) return hipErrorInvalidValue;  // the scratch is laid out for n
     const RunGrid g = count_grid(max_seg);
     const SegScratch ss = seg_scratch(scratch, n);
     count_sum_kernel<<<g.blocks, MQ_BLOCK, 0, stream>>>(n, seg_start, nseg, seg_split, ss.c_run, ss.c_max, ss.c_tloc,
                                                        g);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = launch_scan_runs(ss.c_run, g.blocks, total, nullptr, ss.c_max, max_pairs, stream);
+    if (e == hipSuccess) e = launch_scan_runs(ss.c_run, g.blocks, nullptr, nullptr, ss.c_max, nseg, &mail, stream);
     if (e != hipSuccess) return e;
     count_write_kernel<<<g.ntiles, MQ_BLOCK, 0, stream>>>(n, seg_start, nseg, seg_split, ss.c_run, ss.c_tloc, g,
                                                          seg_off);

@@ -39,7 +39,8 @@ __global__ __launch_bounds__(MQ_BLOCK) void bitmap_set_kernel(const int32_t* __r
 // wave totals scanned in LDS, the tile's output offset from a decoupled
 // look-back; kept records are written in input order.
 __global__ __launch_bounds__(MQ_BLOCK) void semi_filter_kernel(SemiArgs a, uint64_t* __restrict__ status,
-                                                               uint32_t* __restrict__ tile_ctr, uint32_t epoch) {
+                                                               uint32_t* __restrict__ tile_ctr, uint32_t epoch,
+                                                               Mail mail) {
     constexpr uint32_t TILE = MQ_BLOCK * SEMI_IPT;
     __shared__ uint32_t s_tile;
     __shared__ uint32_t s_wtot[MQ_WAVES];
@@ -48,7 +49,7 @@ __global__ __launch_bounds__(MQ_BLOCK) void semi_filter_kernel(SemiArgs a, uint6
     const uint32_t w = threadIdx.x / MQ_WAVE;
     const uint64_t lt = lanemask_lt();
     for (;;) {
-        const uint32_t tile = next_tile(tile_ctr, &s_tile);
+        const uint32_t tile = next_tile(tile_ctr, &s_tile, ntiles + gridDim.x);
         if (tile >= ntiles) break;
         const uint32_t base = tile * TILE;
         uint32_t key[SEMI_IPT];
@@ -78,7 +79,11 @@ __global__ __launch_bounds__(MQ_BLOCK) void semi_filter_kernel(SemiArgs a, uint6
             const uint64_t ex = tile_prefix_wave0(status, tile, epoch, ttot);
             if (lane() == 0) {
                 s_excl = ex;
-                if (tile == ntiles - 1) *a.count = (uint32_t)(ex + ttot);
+                if (tile == ntiles - 1) {
+                    *a.count = (uint32_t)(ex + ttot);
+                    mail.data[0] = (uint32_t)(ex + ttot);
+                    mail_post(mail);
+                }
             }
         }
         __syncthreads();
@@ -116,12 +121,12 @@ hipError_t launch_bitmap_set(const int32_t* keys, uint32_t n, int32_t base, uint
     return hipGetLastError();
 }
 
-hipError_t launch_semi_filter(const SemiArgs& a, uint64_t* status, uint32_t* tile_ctr, uint32_t epoch,
+hipError_t launch_semi_filter(const SemiArgs& a, uint64_t* status, uint32_t* tile_ctr, uint32_t epoch, Mail mail,
                               hipStream_t stream) {
     if (a.n == 0) return hipSuccess;
     const uint32_t tiles = (a.n + MQ_BLOCK * SEMI_IPT - 1) / (MQ_BLOCK * SEMI_IPT);
     const uint32_t blocks = std::min<uint32_t>(tiles, 256u * 8u);
-    semi_filter_kernel<<<blocks, MQ_BLOCK, 0, stream>>>(a, status, tile_ctr, epoch);
+    semi_filter_kernel<<<blocks, MQ_BLOCK, 0, stream>>>(a, status, tile_ctr, epoch, mail);
     return hipGetLastError();
 }
 

@@ -153,7 +153,7 @@ __global__ __launch_bounds__(NW * MQ_WAVE, GEN ? 4 : 1) void radix_pass_kernel(S
     constexpr int TILE = NW * MQ_WAVE * KPT;
     __shared__ SortSmem<RB, KPT, NW> sm;
     __shared__ uint32_t s_tile;
-    const uint32_t tile = next_tile(tile_ctr, &s_tile);
+    const uint32_t tile = next_tile(tile_ctr, &s_tile, gridDim.x);
     const uint32_t base = tile * (uint32_t)TILE;
     const uint32_t valid_n = min((uint32_t)TILE, n - base);
     const uint32_t w = threadIdx.x / MQ_WAVE;

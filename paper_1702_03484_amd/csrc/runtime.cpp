@@ -156,7 +156,10 @@ void pick_tuning(Ctx* ctx, int key_bits, int& rb, int& kpt, uint64_t nrec) {
             kpt = (int)(it->second & 0xff);
         }
     }
-    if (!kpt) kpt = 16;
+    // small sorts are latency-bound and want more, smaller tiles: 8 keys per
+    // thread were the faster up to 2^19 records at every key width (2^15
+    // records of 24 bits: 51 against 52-75 us; 2^20: 101 against 89)
+    if (!kpt) kpt = nrec && nrec < (uint64_t(1) << 19) ? 8 : 16;
     if (!rb) {
         // fewest passes with digits of at most 8 bits, spread evenly
         int passes = std::max(1, (key_bits + 7) / 8);
@@ -1170,6 +1173,7 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
             (left_big ? nLs : nRs) = kept;
             js.path = MAPSQ_PATH_SEMIJOIN;
             js.sorted_records = Ns;
+            pick_tuning(ctx, key_bits, rb, kpt, (uint64_t)Ns);  // the size that is sorted
             ctx->last = js;
             if (kept == 0) {  // no key in common
                 set_meta(out);
@@ -1188,8 +1192,9 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
     // in sorted order instead of gathering them through the positions.
     const bool carry =
         !composite && js.path != MAPSQ_PATH_SEMIJOIN && lv.size() <= 1 && rv.size() <= 1 && key_bits <= 31;
-    const int sort_bits = carry ? key_bits + 1 : key_bits;
-    if (carry) pick_tuning(ctx, sort_bits, rb, kpt, (uint64_t)Ns);
+    // the side bit below a carried key rides along unsorted: every LEFT record
+    // enters ahead of every RIGHT one and the passes are stable
+    const int lo_bit = carry ? 1 : 0;
     SortSrc src{lkey, nL, rkey, nR, kmin, nullptr, nullptr, carry ? 1 : 0};
     if (carry) {
         src.v0 = lv.empty() ? lkey : L->col[lv[0]];  // payloads of a side without values go unused
@@ -1263,8 +1268,8 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
         // ids and 4N cells per further variable, write N)
         sort_bytes = 16.0 * Ns * passes + 12.0 * (nkeys - 1) * Ns + (4.0 + 4.0 * (nkeys - 1) + 1.0) * Ns;
     } else {
-        if ((st = radix_sort(ctx, js.path == MAPSQ_PATH_SEMIJOIN ? nullptr : &src, Ns, sort_bits, rb, kpt, b, &res,
-                             &passes)))
+        if ((st = radix_sort(ctx, js.path == MAPSQ_PATH_SEMIJOIN ? nullptr : &src, Ns, key_bits, rb, kpt, b, &res,
+                             &passes, lo_bit)))
             return st;
         // histogram reads 4N; the first pass reads 4N keys (8N records after a
         // semi-join, plus the carried value cells), later passes 8N; every pass
@@ -1278,21 +1283,27 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
     uint32_t* seg_start = b.k[1 - res];
     uint32_t* seg_split = b.v[1 - res];
     // ReduceDuplicate: segments, counts, offsets
-    Block ss = alloc_block(ctx, seg_scratch_bytes(Ns));
+    Block ss = alloc_block(ctx, seg_scratch_bytes(Ns, brk != nullptr));
     if (!ss.ok()) return ctx->fail(MAPSQ_ERR_CAPACITY, "arena: no room for the segment scans");
     ph = ctx->prof_begin(2);
-    HIPCHK(launch_seg_heads(skeys, svals, Ns, nL, carry ? 1 : 0, seg_start, seg_split, scalar32(ctx, SC_NSEG),
-                            ss.as<void>(), ctx->stream, brk));
     const Mail mail = ctx->next_mail();
-    HIPCHK(launch_seg_count(Ns, seg_start, scalar32(ctx, SC_NSEG), Ns, seg_split, seg_off, mail, ss.as<void>(),
-                            ctx->stream));
+    if (brk) {
+        HIPCHK(launch_seg_heads(skeys, svals, brk, Ns, nL, seg_start, seg_split, scalar32(ctx, SC_NSEG),
+                                ss.as<void>(), ctx->stream));
+        HIPCHK(launch_seg_count(Ns, seg_start, scalar32(ctx, SC_NSEG), Ns, seg_split, seg_off, mail, ss.as<void>(),
+                                ctx->stream));
+    } else {
+        HIPCHK(launch_seg_sum(skeys, svals, Ns, nL, carry ? 1 : 0, scalar32(ctx, SC_NSEG), ss.as<void>(), mail,
+                              ctx->stream));
+    }
     ctx->prof_end(ph, 0.0);  // bytes are filled in once the segment count is known (below)
     if ((st = wait_mail(ctx, mail))) return st;
     const uint32_t nseg = mail.data[0];
     const uint64_t total = mail64(mail, 2), max_pairs = mail64(mail, 4);
-    // heads: read 4N keys and 4N payloads, write 4S starts and 4S splits;
-    // count: read 8S starts and 4S splits, write 8S offsets
-    if (ph >= 0) ctx->pending[ph].bytes = (brk ? 9.0 : 8.0) * Ns + 28.0 * nseg;
+    // reads 4N keys, and 4N payloads unless they are carried; with break flags
+    // also N flags, then 12S read and 16S written
+    const double seg_bytes = (carry ? 4.0 : 8.0) * Ns;
+    if (ph >= 0) ctx->pending[ph].bytes = brk ? 9.0 * Ns + 28.0 * nseg : seg_bytes;
     js.segments = nseg;
     js.out_rows = (int64_t)total;
     js.radix_bits = rb;
@@ -1329,7 +1340,20 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
     a.row_begin = 0;
     a.row_end = total;
     a.sparse = total < SPARSE_ROWS_PER_SEG * (uint64_t)nseg ? 1 : 0;
-    a.seg_major = mat_seg_use(total, nseg, max_pairs) ? 1 : 0;
+    // few pairs per key: the rows come straight from the records; else the
+    // segments are written out for the row-chunk kernel
+    const bool sparse_keys = mat_seg_use(total, nseg, max_pairs);
+    a.seg_major = sparse_keys ? 1 : 0;
+    if (!brk && !sparse_keys) {
+        ph = ctx->prof_begin(2);
+        const hipError_t se = launch_seg_write(skeys, svals, Ns, nL, carry ? 1 : 0, seg_start, seg_split, seg_off,
+                                               ss.as<void>(), ctx->stream);
+        ctx->prof_end(ph, seg_bytes + 16.0 * nseg);
+        if (se != hipSuccess) {
+            free_table(ctx, &m);
+            return ctx->fail(MAPSQ_ERR_HIP, std::string("segments: ") + hipGetErrorString(se));
+        }
+    }
     a.seg_count = nseg;
     a.max_blocks = ctx->mat_blocks(total);
     // values in sorted record order when output rows outnumber records
@@ -1368,7 +1392,8 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
         }
     }
     ph = ctx->prof_begin(3);
-    hipError_t e = launch_materialize(a, ctx->stream);
+    hipError_t e = sparse_keys && !brk ? launch_mat_tiles(a, carry ? 1 : 0, ss.as<void>(), ctx->stream)
+                                       : launch_materialize(a, ctx->stream);
     // writes 4 B per output cell; reads each segment's key and table entries
     // and each value cell once (from the gathered copy when there is one,
     // else through every record's payload)

@@ -45,12 +45,16 @@ __host__ __device__ inline RunGrid run_grid(uint32_t ntiles) {
 }
 
 // ---- segments straight from the sorted records -----------------------------
-// A tile of 4,096 sorted records is turned into two bit maps, segment heads
-// and RIGHT records, one __ballot word per 64 records.  Everything about a
+// A tile of sorted records is turned into two bit maps, segment heads and
+// RIGHT records, one __ballot word per 64 records.  Everything about a
 // segment whose head lies in the tile then comes from bit scans: its end is
 // the next head, its split the first RIGHT record (within a key LEFT records
 // come first), so one read of the keys gives the segments, their cL * cR
-// pairs and the pairs' running sum together.  Only the tile's last segment
+// pairs and the pairs' running sum together.  Each wave walks its words from
+// the last to the first, carrying the next head and RIGHT record after the
+// word in scalar registers, so a word costs some 25 vector instructions and
+// no branch (looking the next bits up in LDS per head: 2,650 instructions a
+// tile, and the sum pass of 32M records 87 us).  Only the tile's last segment
 // can end past the tile; one wave looks for its end in the next 64 records
 // and then by a 64-ary search.
 //
@@ -61,10 +65,12 @@ __host__ __device__ inline RunGrid run_grid(uint32_t ntiles) {
 //              materialisation, or
 //   mat_tile   the output rows themselves (small key products): the segments
 //              never leave LDS.
-constexpr int ST_IPT = 16;
-constexpr uint32_t ST_TILE = MQ_BLOCK * ST_IPT;
-constexpr uint32_t ST_ROWS = ST_TILE / MQ_WAVE;  // ballot words per tile
-static_assert(ST_ROWS == 64, "one bit per ballot word");
+// Tiles have 16 words per wave, or 4 for few records (below 2^18, where 4,096-
+// record tiles would leave most of the chip idle).
+constexpr int ST_IPT = 16, ST_IPT_FEW = 4;
+constexpr uint32_t ST_FEW = 1u << 18;
+constexpr uint32_t st_tile(int ipt) { return MQ_BLOCK * (uint32_t)ipt; }
+static_assert(MQ_WAVES * ST_IPT <= 64, "one bit per ballot word");
 
 struct SegIn {
     const uint32_t* keys;
@@ -73,12 +79,8 @@ struct SegIn {
 };
 
 struct SegTile {  // LDS
-    uint64_t hm[ST_ROWS], rm[ST_ROWS];
-    union Any {  // one bit per ballot word that is not empty; a wave writes its 16
-        uint16_t part[MQ_WAVES];
-        uint64_t all;
-    } hany, rany;
-    uint32_t open, open_cl, open_cr;          // the segment that reaches the tile's end (open = ~0: none)
+    uint64_t hm[MQ_WAVES * ST_IPT], rm[MQ_WAVES * ST_IPT];
+    uint32_t hany[MQ_WAVES], rany[MQ_WAVES];  // per wave: one bit per ballot word that is not empty
 };
 
 // lane - 1's value; lane 0 gets `first` (DPP: the wave shifted right by one)
@@ -99,28 +101,53 @@ __device__ __forceinline__ uint32_t wave_incl_u32(uint32_t x) {
     return x;
 }
 
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
+#define MQ_DPP_MAX(ctrl, rows) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, rows, 0xf, false))
+    MQ_DPP_MAX(0x111, 0xf);
+    MQ_DPP_MAX(0x112, 0xf);
+    MQ_DPP_MAX(0x114, 0xf);
+    MQ_DPP_MAX(0x118, 0xf);
+    MQ_DPP_MAX(0x142, 0xa);
+    MQ_DPP_MAX(0x143, 0xc);
+#undef MQ_DPP_MAX
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, MQ_WAVE - 1);
+}
+
 __device__ __forceinline__ uint32_t last_lane(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, MQ_WAVE - 1);
 }
 
-// The bit maps of the tile at `base` (this wave's 16 words also in
-// registers), and the keys.  Ends with a barrier.
-template <int FS>
-__device__ __forceinline__ void seg_masks(SegTile& sm, const SegIn& a, uint32_t base, uint32_t (&k)[ST_IPT],
-                                          uint64_t (&hm)[ST_IPT], uint64_t (&rm)[ST_IPT]) {
-    const uint32_t w = threadIdx.x / MQ_WAVE;
-    const uint32_t first = base + w * ST_IPT * MQ_WAVE;  // of this wave
-    uint32_t v[ST_IPT];
+// a wave's records of the tile at `base` (clamped to the last record), and the
+// key before them
+template <int IPT>
+struct SegRecs {
+    uint32_t k[IPT], v[IPT], kp;
+};
+template <int FS, int IPT>
+__device__ __forceinline__ void seg_load(const SegIn& a, uint32_t base, SegRecs<IPT>& r) {
+    const uint32_t first = base + threadIdx.x / MQ_WAVE * IPT * MQ_WAVE;  // of this wave
 #pragma unroll
-    for (int i = 0; i < ST_IPT; i++) {
+    for (int i = 0; i < IPT; i++) {
         const uint32_t idx = min(first + i * MQ_WAVE + lane(), a.n - 1);
-        k[i] = a.keys[idx];
-        if (!FS) v[i] = a.vals[idx];
+        r.k[i] = a.keys[idx];
+        r.v[i] = FS ? 0u : a.vals[idx];
     }
-    uint32_t kp = first > 0 ? a.keys[min(first, a.n) - 1] : 0u;
+    r.kp = first > 0 ? a.keys[min(first, a.n) - 1] : 0u;
+}
+
+// The bit maps of the tile at `base` (this wave's words also in registers).
+// Ends with a barrier.
+template <int FS, int IPT>
+__device__ __forceinline__ void seg_masks(SegTile& sm, const SegIn& a, uint32_t base, const SegRecs<IPT>& rec,
+                                          uint64_t (&hm)[IPT], uint64_t (&rm)[IPT]) {
+    const uint32_t w = threadIdx.x / MQ_WAVE;
+    const uint32_t first = base + w * IPT * MQ_WAVE;  // of this wave
+    const uint32_t(&k)[IPT] = rec.k;
+    const uint32_t(&v)[IPT] = rec.v;
+    uint32_t kp = rec.kp;
     uint32_t hany = 0, rany = 0;
 #pragma unroll
-    for (int i = 0; i < ST_IPT; i++) {
+    for (int i = 0; i < IPT; i++) {
         const uint32_t idx = first + i * MQ_WAVE + lane();
         const uint32_t p = wave_prev(k[i], kp);
         kp = last_lane(k[i]);
@@ -128,42 +155,64 @@ __device__ __forceinline__ void seg_masks(SegTile& sm, const SegIn& a, uint32_t 
         rm[i] = __ballot(idx < a.n && (FS ? (k[i] & 1u) != 0 : v[i] >= a.n_left));
         hany |= (hm[i] ? 1u : 0u) << i;
         rany |= (rm[i] ? 1u : 0u) << i;
-        if (lane() == 0) {
-            sm.hm[w * ST_IPT + i] = hm[i];
-            sm.rm[w * ST_IPT + i] = rm[i];
-        }
     }
     if (lane() == 0) {
-        sm.hany.part[w] = (uint16_t)hany;
-        sm.rany.part[w] = (uint16_t)rany;
+#pragma unroll
+        for (int i = 0; i < IPT; i++) {
+            sm.hm[w * IPT + i] = hm[i];
+            sm.rm[w * IPT + i] = rm[i];
+        }
+        sm.hany[w] = hany;
+        sm.rany[w] = rany;
     }
-    if (threadIdx.x == 0) sm.open = ~0u;
     __syncthreads();
 }
 
-// first set bit of the tile's map at or after ballot word `row` (ST_TILE: none)
-__device__ __forceinline__ uint32_t next_bit(const uint64_t* words, uint64_t any, uint32_t row) {
-    if (row >= ST_ROWS) return ST_TILE;
-    const uint64_t rows = any >> row;
-    if (!rows) return ST_TILE;
-    const uint32_t r = row + (uint32_t)__builtin_ctzll(rows);
+template <int IPT>
+__device__ __forceinline__ uint64_t any_words(const uint32_t (&any)[MQ_WAVES]) {
+    uint64_t all = 0;
+#pragma unroll
+    for (int w = 0; w < MQ_WAVES; w++) all |= (uint64_t)any[w] << (w * IPT);
+    return all;
+}
+
+// first set bit of the tile's map at or after position `from` (none: `none`)
+__device__ __forceinline__ uint32_t next_bit(const uint64_t* words, uint64_t any, uint32_t from, uint32_t nwords,
+                                             uint32_t none) {
+    uint32_t r = from / MQ_WAVE;
+    if (r >= nwords) return none;
+    const uint64_t here = words[r] >> (from % MQ_WAVE);
+    if (here) return from + (uint32_t)__builtin_ctzll(here);
+    const uint64_t rows = r + 1 < 64 ? any >> (r + 1) : 0ull;
+    if (!rows) return none;
+    r += 1 + (uint32_t)__builtin_ctzll(rows);
     return r * MQ_WAVE + (uint32_t)__builtin_ctzll(words[r]);
 }
 
-// The segment whose head is this lane's record of ballot word `row`: its
-// LEFT and RIGHT counts up to the tile's end (`lim` records).
-__device__ __forceinline__ void seg_counts(const SegTile& sm, uint64_t hm, uint64_t rm, uint32_t row, uint32_t lim,
-                                           uint32_t& cl, uint32_t& cr, bool& to_end) {
-    const uint32_t pos = row * MQ_WAVE + lane();
-    const uint64_t h = lane() == MQ_WAVE - 1 ? 0ull : hm >> (lane() + 1);
-    const uint64_t r = rm >> lane();
-    uint32_t nh = h ? pos + 1 + (uint32_t)__builtin_ctzll(h) : next_bit(sm.hm, sm.hany.all, row + 1);
-    uint32_t sp = r ? pos + (uint32_t)__builtin_ctzll(r) : next_bit(sm.rm, sm.rany.all, row + 1);
-    to_end = nh >= lim;
-    nh = min(nh, lim);
-    sp = min(sp, nh);
-    cl = sp - pos;
-    cr = nh - sp;
+// This lane's segments: for word i, LEFT and RIGHT counts of the segment
+// headed by its record, up to the tile's last record (`lim` records), 0 and 0
+// where it heads none, and RIGHT 0 for the tile's last segment when it may go
+// on past the tile (`past`: seg_last has that one).
+template <int IPT>
+__device__ __forceinline__ void seg_counts(const SegTile& sm, const uint64_t (&hm)[IPT], const uint64_t (&rm)[IPT],
+                                           uint32_t lim, bool past, uint32_t (&cl)[IPT], uint32_t (&cr)[IPT]) {
+    constexpr uint32_t WORDS = MQ_WAVES * IPT;
+    const uint32_t w = uni(threadIdx.x / MQ_WAVE);
+    // the next head and RIGHT record after this wave's words
+    uint32_t nh = uni(next_bit(sm.hm, any_words<IPT>(sm.hany), (w + 1) * IPT * MQ_WAVE, WORDS, lim));
+    uint32_t nr = uni(next_bit(sm.rm, any_words<IPT>(sm.rany), (w + 1) * IPT * MQ_WAVE, WORDS, lim));
+#pragma unroll
+    for (int i = IPT - 1; i >= 0; i--) {
+        const uint32_t word = (w * IPT + i) * MQ_WAVE, pos = word + lane();
+        const uint64_t h = hm[i] >> 1 >> lane(), r = rm[i] >> lane();
+        const uint32_t end = h ? pos + 1 + (uint32_t)__builtin_ctzll(h) : nh;
+        const uint32_t sp = min(r ? pos + (uint32_t)__builtin_ctzll(r) : nr, end);
+        const bool head = (hm[i] >> lane()) & 1ull;
+        cl[i] = head ? sp - pos : 0u;
+        cr[i] = head && !(past && end >= lim) ? end - sp : 0u;
+        nh = hm[i] ? word + (uint32_t)__builtin_ctzll(hm[i]) : nh;
+        nr = rm[i] ? word + (uint32_t)__builtin_ctzll(rm[i]) : nr;
+    }
 }
 
 // first index in [lo, hi) where pred holds (false, then true), by 64 probes a
@@ -181,29 +230,37 @@ __device__ __forceinline__ uint32_t wave_first(uint32_t lo, uint32_t hi, Pred pr
     return lo;
 }
 
-// The open segment's counts past the tile's end at `end` (< n), by one wave.
-// key: its last record's in the tile; ek, ev: the keys and payloads of the
-// 64 records from `end` on (clamped to the last record).
-template <int FS>
-__device__ __forceinline__ void seg_beyond(const SegIn& a, uint32_t end, uint32_t key, uint32_t ek, uint32_t ev,
-                                           uint32_t& cl, uint32_t& cr) {
+// The tile's last segment when records follow the tile (`end` < n is the
+// first of them): its head's position in the tile (false: the tile has no
+// head) and its whole counts, by one wave.  ek, ev: keys and payloads of the
+// 64 records from `end` on (clamped to the last record); key: the tile's last.
+template <int FS, int IPT>
+__device__ __forceinline__ bool seg_last(const SegTile& sm, const SegIn& a, uint32_t end, uint32_t key, uint32_t ek,
+                                         uint32_t ev, uint32_t& pos, uint32_t& cl, uint32_t& cr) {
+    constexpr uint32_t WORDS = MQ_WAVES * IPT, TILE = st_tile(IPT);
+    const uint64_t hall = any_words<IPT>(sm.hany);
+    if (!hall) return false;
+    const uint32_t hw = 63u - (uint32_t)__builtin_clzll(hall);
+    pos = hw * MQ_WAVE + 63u - (uint32_t)__builtin_clzll(sm.hm[hw]);
+    uint32_t sp = next_bit(sm.rm, any_words<IPT>(sm.rany), pos, WORDS, TILE);
     const bool in = end + lane() < a.n;
     const uint64_t other = __ballot(!in || (ek >> FS) != (key >> FS));
     const uint32_t near = other ? (uint32_t)__builtin_ctzll(other) : (uint32_t)MQ_WAVE;  // records that follow, so far
     uint32_t stop = end + near;
     if (!other)
         stop = wave_first(end + MQ_WAVE, a.n, [&](uint32_t i) { return (a.keys[i] >> FS) != (key >> FS); });
-    if (cr == 0) {  // no RIGHT record in the tile: find the first one
+    cl = sp - pos;
+    cr = TILE - sp + (stop - end);
+    if (sp == TILE) {  // no RIGHT record in the tile: find the first one
         const uint64_t right = __ballot(FS ? (ek & 1u) != 0 : ev >= a.n_left) & (other ? (1ull << near) - 1ull : ~0ull);
-        uint32_t sp = right ? end + (uint32_t)__builtin_ctzll(right) : stop;
+        sp = right ? end + (uint32_t)__builtin_ctzll(right) : stop;
         if (!right && !other)
             sp = wave_first(end + MQ_WAVE, stop,
                             [&](uint32_t i) { return FS ? (a.keys[i] & 1u) != 0 : a.vals[i] >= a.n_left; });
         cl += sp - end;
         cr = stop - sp;
-    } else {
-        cr += stop - end;
     }
+    return true;
 }
 
 __device__ __forceinline__ uint64_t seg_pairs_of(uint32_t cl, uint32_t cr) {
@@ -212,55 +269,48 @@ __device__ __forceinline__ uint64_t seg_pairs_of(uint32_t cl, uint32_t cr) {
 }
 
 // per tile: segments before it in its run (tseg) and pairs (trow); per run
-// the totals and the largest single product.  HBM-bound on one read of the
-// keys (and of the payloads where they tell the side).
-template <int FS>
+// the totals and the largest single product.  One read of the keys (and of
+// the payloads where they tell the side).
+template <int FS, int IPT>
 __global__ __launch_bounds__(MQ_BLOCK) void seg_sum_kernel(SegIn a, RunGrid g, uint32_t* __restrict__ tseg,
                                                            uint64_t* __restrict__ trow,
                                                            uint64_t* __restrict__ run_seg,
                                                            uint64_t* __restrict__ run_row,
                                                            uint64_t* __restrict__ run_max) {
+    constexpr uint32_t TILE = st_tile(IPT);
     __shared__ SegTile sm;
-    __shared__ uint32_t s_seg[MQ_WAVES];
-    __shared__ uint32_t s_row[MQ_WAVES], s_max[MQ_WAVES];
+    __shared__ uint32_t s_seg[MQ_WAVES], s_row[MQ_WAVES], s_max[MQ_WAVES];
     const uint32_t w = threadIdx.x / MQ_WAVE;
     uint32_t segs = 0;
     uint64_t rows = 0, mx = 0;  // of the run so far (wave 0)
     const uint32_t t0 = blockIdx.x * g.chunk, t1 = min(t0 + g.chunk, g.ntiles);
+    SegRecs<IPT> rec;  // the next tile's records are in flight while one is worked on
+    seg_load<FS, IPT>(a, t0 * TILE, rec);
     for (uint32_t tile = t0; tile < t1; tile++) {
-        const uint32_t base = tile * ST_TILE, lim = min(ST_TILE, a.n - base);
-        const bool past = base + ST_TILE < a.n;
+        const uint32_t base = tile * TILE, lim = min(TILE, a.n - base);
+        const bool past = base + TILE < a.n;
         uint32_t ek = 0, ev = 0, lk = 0;
-        if (w == 0 && past) {  // in flight with the tile's own loads
-            const uint32_t e = min(base + ST_TILE + lane(), a.n - 1);
+        if (w == 0 && past) {
+            const uint32_t e = min(base + TILE + lane(), a.n - 1);
             ek = a.keys[e];
             if (!FS) ev = a.vals[e];
-            lk = a.keys[base + ST_TILE - 1];
+            lk = a.keys[base + TILE - 1];
         }
-        uint32_t k[ST_IPT];
-        uint64_t hm[ST_IPT], rm[ST_IPT];
-        seg_masks<FS>(sm, a, base, k, hm, rm);
-        uint32_t sum = 0, m = 0, heads = 0;
+        uint32_t cl[IPT], cr[IPT];
+        uint64_t hm[IPT], rm[IPT];
+        seg_masks<FS, IPT>(sm, a, base, rec, hm, rm);
+        if (tile + 1 < t1) seg_load<FS, IPT>(a, base + TILE, rec);
+        seg_counts<IPT>(sm, hm, rm, lim, past, cl, cr);
+        uint32_t sum = 0, m = 0, heads = 0;  // the products of a tile add up to at most 2^22
 #pragma unroll
-        for (int i = 0; i < ST_IPT; i++) {
+        for (int i = 0; i < IPT; i++) {
+            const uint32_t c = __umul24(cl[i], cr[i]);
             heads += (uint32_t)__popcll(hm[i]);
-            if ((hm[i] >> lane()) & 1ull) {
-                uint32_t cl, cr;
-                bool to_end;
-                seg_counts(sm, hm[i], rm[i], w * ST_IPT + i, lim, cl, cr, to_end);
-                if (to_end && past) {
-                    sm.open_cl = cl;
-                    sm.open_cr = cr;
-                    sm.open = 0;
-                } else {  // inside the tile: the products of a tile add up to at most 2^22
-                    sum += cl * cr;
-                    m = max(m, cl * cr);
-                }
-            }
+            sum += c;
+            m = max(m, c);
         }
         sum = last_lane(wave_incl_u32(sum));
-#pragma unroll
-        for (int o = MQ_WAVE / 2; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o, MQ_WAVE));
+        m = wave_max_u32(m);
         if (lane() == 0) {
             s_seg[w] = heads;
             s_row[w] = sum;
@@ -277,11 +327,8 @@ __global__ __launch_bounds__(MQ_BLOCK) void seg_sum_kernel(SegIn a, RunGrid g, u
                 tm = max(tm, s_max[i]);
             }
             uint64_t oc = 0;
-            if (sm.open != ~0u) {
-                uint32_t cl = sm.open_cl, cr = sm.open_cr;
-                seg_beyond<FS>(a, base + ST_TILE, lk, ek, ev, cl, cr);
-                oc = seg_pairs_of(cl, cr);
-            }
+            uint32_t pos, ol, orr;
+            if (past && seg_last<FS, IPT>(sm, a, base + TILE, lk, ek, ev, pos, ol, orr)) oc = seg_pairs_of(ol, orr);
             if (lane() == 0) {
                 tseg[tile] = segs;
                 trow[tile] = rows;
@@ -369,7 +416,7 @@ __device__ __forceinline__ TileBefore waves_before(uint32_t seg, uint32_t row, u
 }
 
 // segment starts, splits and output offsets; one tile per block
-template <int FS>
+template <int FS, int IPT>
 __global__ __launch_bounds__(MQ_BLOCK) void seg_write_kernel(SegIn a, RunGrid g, const uint32_t* __restrict__ tseg,
                                                              const uint64_t* __restrict__ trow,
                                                              const uint64_t* __restrict__ run_seg,
@@ -377,64 +424,51 @@ __global__ __launch_bounds__(MQ_BLOCK) void seg_write_kernel(SegIn a, RunGrid g,
                                                              uint32_t* __restrict__ seg_start,
                                                              uint32_t* __restrict__ seg_split,
                                                              uint64_t* __restrict__ seg_off) {
+    constexpr uint32_t TILE = st_tile(IPT);
     __shared__ SegTile sm;
     __shared__ uint32_t s_a[MQ_WAVES], s_b[MQ_WAVES];
     const uint32_t w = threadIdx.x / MQ_WAVE;
-    const uint32_t tile = blockIdx.x, base = tile * ST_TILE, lim = min(ST_TILE, a.n - base);
-    const bool past = base + ST_TILE < a.n;
-    uint32_t k[ST_IPT];
-    uint64_t hm[ST_IPT], rm[ST_IPT];
-    seg_masks<FS>(sm, a, base, k, hm, rm);
-    uint32_t cl[ST_IPT], c[ST_IPT];  // this lane's heads: LEFT count, pairs (0 past the tile)
+    const uint32_t tile = blockIdx.x, base = tile * TILE, lim = min(TILE, a.n - base);
+    const bool past = base + TILE < a.n;
+    SegRecs<IPT> rec;
+    uint32_t cl[IPT], cr[IPT];
+    uint64_t hm[IPT], rm[IPT];
+    seg_load<FS, IPT>(a, base, rec);
+    seg_masks<FS, IPT>(sm, a, base, rec, hm, rm);
+    seg_counts<IPT>(sm, hm, rm, lim, past, cl, cr);
     uint32_t heads = 0, rows = 0;
-    uint32_t open_row = ~0u;
 #pragma unroll
-    for (int i = 0; i < ST_IPT; i++) {
-        c[i] = cl[i] = 0;
-        if ((hm[i] >> lane()) & 1ull) {
-            uint32_t cr;
-            bool to_end;
-            seg_counts(sm, hm[i], rm[i], w * ST_IPT + i, lim, cl[i], cr, to_end);
-            c[i] = cl[i] * cr;
-            if (to_end && past && cr == 0) {
-                open_row = i;
-                c[i] = 0;  // the tile's last segment: nothing in the tile comes after its pairs
-            }
-        }
+    for (int i = 0; i < IPT; i++) {
         heads += (uint32_t)__popcll(hm[i]);
-        rows += c[i];
+        rows += __umul24(cl[i], cr[i]);  // the last segment's come after every other offset
     }
     const TileBefore t = waves_before(heads, last_lane(wave_incl_u32(rows)), s_a, s_b);
-    uint32_t sid = (uint32_t)run_seg[tile / g.chunk] + tseg[tile] + t.seg;
+    const uint32_t seg0 = (uint32_t)run_seg[tile / g.chunk] + tseg[tile];
+    uint32_t sid = seg0 + t.seg;
     uint64_t off = sat_add(sat_add(run_row[tile / g.chunk], trow[tile]), t.row);
     const uint64_t lt = lanemask_lt();
 #pragma unroll
-    for (int i = 0; i < ST_IPT; i++) {
-        const uint32_t incl = wave_incl_u32(c[i]);
+    for (int i = 0; i < IPT; i++) {
+        const uint32_t c = __umul24(cl[i], cr[i]), incl = wave_incl_u32(c);
         if ((hm[i] >> lane()) & 1ull) {
             const uint32_t at = sid + (uint32_t)__popcll(hm[i] & lt);
-            const uint32_t idx = base + (w * ST_IPT + i) * MQ_WAVE + lane();
+            const uint32_t idx = base + (w * IPT + i) * MQ_WAVE + lane();
             if (MQ_IN_BOUNDS(at, a.n)) {
                 seg_start[at] = idx;
-                if (open_row != (uint32_t)i) seg_split[at] = idx + cl[i];
-                seg_off[at] = sat_add(off, incl - c[i]);
-            }
-            if (open_row == (uint32_t)i) {
-                sm.open = at;
-                sm.open_cl = cl[i];
+                if (!past || idx + cl[i] < base + TILE) seg_split[at] = idx + cl[i];  // else below
+                seg_off[at] = sat_add(off, incl - c);
             }
         }
         sid += (uint32_t)__popcll(hm[i]);
         off = sat_add(off, last_lane(incl));
     }
-    if (!past) return;
-    __syncthreads();
-    if (w == 0 && sm.open != ~0u) {  // its split lies past the tile
-        const uint32_t end = base + ST_TILE, e = min(end + lane(), a.n - 1);
-        uint32_t l = sm.open_cl, r = 0;
-        seg_beyond<FS>(a, end, a.keys[end - 1], a.keys[e], FS ? 0u : a.vals[e], l, r);
-        if (lane() == 0 && MQ_IN_BOUNDS(sm.open, a.n)) seg_split[sm.open] = end - sm.open_cl + l;
-    }
+    if (!past || w != MQ_WAVES - 1) return;
+    // the tile's last segment when no RIGHT record of it lies in the tile
+    const uint32_t end = base + TILE, e = min(end + lane(), a.n - 1);
+    uint32_t pos, ol, orr;
+    if (seg_last<FS, IPT>(sm, a, end, a.keys[end - 1], a.keys[e], FS ? 0u : a.vals[e], pos, ol, orr) &&
+        pos + ol >= TILE && lane() == 0 && MQ_IN_BOUNDS(sid - 1, a.n))
+        seg_split[sid - 1] = base + pos + ol;
 }
 
 // Scratch: run totals of segments and of pairs and run maxima (RUN_BLOCKS
@@ -443,7 +477,11 @@ struct SegScratch {
     uint64_t *run_seg, *run_row, *run_max, *trow;
     uint32_t* tseg;
 };
-static RunGrid seg_grid(uint32_t n) { return run_grid((n + ST_TILE - 1) / ST_TILE); }
+static bool seg_few(uint32_t n) { return n < ST_FEW; }
+static RunGrid seg_grid(uint32_t n) {
+    const uint32_t tile = st_tile(seg_few(n) ? ST_IPT_FEW : ST_IPT);
+    return run_grid((n + tile - 1) / tile);
+}
 static SegScratch seg_tiles(void* p, uint32_t n) {
     const RunGrid g = seg_grid(n);
     SegScratch s;
@@ -461,7 +499,8 @@ hipError_t launch_seg_sum(const uint32_t* keys, const uint32_t* vals, uint32_t n
     const RunGrid g = seg_grid(n);
     const SegScratch s = seg_tiles(scratch, n);
     const SegIn a{keys, vals, n, n_left};
-    auto* k = side_bit ? seg_sum_kernel<1> : seg_sum_kernel<0>;
+    auto* k = seg_few(n) ? (side_bit ? seg_sum_kernel<1, ST_IPT_FEW> : seg_sum_kernel<0, ST_IPT_FEW>)
+                         : (side_bit ? seg_sum_kernel<1, ST_IPT> : seg_sum_kernel<0, ST_IPT>);
     k<<<g.blocks, MQ_BLOCK, 0, stream>>>(a, g, s.tseg, s.trow, s.run_seg, s.run_row, s.run_max);
     seg_scan_kernel<<<1, MQ_BLOCK, 0, stream>>>(s.run_seg, s.run_row, s.run_max, g.blocks, nseg, mail);
     return hipGetLastError();
@@ -474,7 +513,8 @@ hipError_t launch_seg_write(const uint32_t* keys, const uint32_t* vals, uint32_t
     const RunGrid g = seg_grid(n);
     const SegScratch s = seg_tiles(scratch, n);
     const SegIn a{keys, vals, n, n_left};
-    auto* k = side_bit ? seg_write_kernel<1> : seg_write_kernel<0>;
+    auto* k = seg_few(n) ? (side_bit ? seg_write_kernel<1, ST_IPT_FEW> : seg_write_kernel<0, ST_IPT_FEW>)
+                         : (side_bit ? seg_write_kernel<1, ST_IPT> : seg_write_kernel<0, ST_IPT>);
     k<<<g.ntiles, MQ_BLOCK, 0, stream>>>(a, g, s.tseg, s.trow, s.run_seg, s.run_row, seg_start, seg_split, seg_off);
     return hipGetLastError();
 }
@@ -865,113 +905,130 @@ __global__ __launch_bounds__(MQ_BLOCK) void materialize_kernel(MatArgs a) {
 // to LDS as head position, cL and cR in one word, output key and row offset;
 // the tile's rows then go out with consecutive threads on consecutive rows,
 // each finding its segment by a binary search over the offsets in LDS.
-template <int NC, int NLC, int FS>
+template <int NC, int NLC, int FS, int IPT>
 __global__ __launch_bounds__(MQ_BLOCK) void mat_tile_kernel(MatArgs a, RunGrid g, const uint64_t* __restrict__ trow,
                                                             const uint64_t* __restrict__ run_row) {
-    constexpr uint32_t MAXE = ST_TILE / 2 + 1;  // the last segment may have one record here
-    static_assert(MAT_SEG_MAX_PAIRS <= 127 && ST_TILE <= 4096, "a segment in one word");
+    constexpr uint32_t TILE = st_tile(IPT), MAXE = TILE / 2 + 1;  // the last segment may have one record here
+    static_assert(MAT_SEG_MAX_PAIRS <= 127 && TILE <= 4096, "a segment in one word");
     __shared__ SegTile sm;
     __shared__ uint32_t s_a[MQ_WAVES], s_b[MQ_WAVES];
     __shared__ uint32_t s_ent[MAXE], s_off[MAXE], s_key[MAXE];
     const int nl = NLC >= 0 ? NLC : a.nl, nr = NLC >= 0 ? NC - 1 - NLC : a.nr;
     const int nc = 1 + nl + nr;
     const uint32_t w = threadIdx.x / MQ_WAVE;
-    const uint32_t tile = blockIdx.x, base = tile * ST_TILE, lim = min(ST_TILE, a.n - base);
-    const bool past = base + ST_TILE < a.n;
+    const uint32_t tile = blockIdx.x, base = tile * TILE, lim = min(TILE, a.n - base);
+    const bool past = base + TILE < a.n;
     const SegIn in{a.keys, a.vals, a.n, a.n_left};
-    uint32_t k[ST_IPT];
-    uint64_t hm[ST_IPT], rm[ST_IPT];
-    seg_masks<FS>(sm, in, base, k, hm, rm);
-    uint32_t cc[ST_IPT];  // cL << 16 | cR of this lane's heads that have pairs
+    uint32_t ek = 0, ev = 0, lk = 0;
+    if (w == MQ_WAVES - 1 && past) {
+        const uint32_t e = min(base + TILE + lane(), a.n - 1);
+        ek = a.keys[e];
+        if (!FS) ev = a.vals[e];
+        lk = a.keys[base + TILE - 1];
+    }
+    SegRecs<IPT> rec;
+    uint32_t cl[IPT], cr[IPT];
+    uint64_t hm[IPT], rm[IPT];
+    seg_load<FS, IPT>(in, base, rec);
+    seg_masks<FS, IPT>(sm, in, base, rec, hm, rm);
+    seg_counts<IPT>(sm, hm, rm, lim, past, cl, cr);
     uint32_t ents = 0, rows = 0;
 #pragma unroll
-    for (int i = 0; i < ST_IPT; i++) {
-        cc[i] = 0;
-        bool open = false;
-        if ((hm[i] >> lane()) & 1ull) {
-            uint32_t cl, cr;
-            bool to_end;
-            seg_counts(sm, hm[i], rm[i], w * ST_IPT + i, lim, cl, cr, to_end);
-            open = to_end && past;
-            if (open) {  // counted below, by wave 0
-                sm.open = (w * ST_IPT + i) * MQ_WAVE + lane();
-                sm.open_cl = cl;
-                sm.open_cr = cr;
-            } else if (cl && cr) {
-                cc[i] = cl << 16 | cr;
-            }
-        }
-        ents += (uint32_t)__popcll(__ballot(cc[i] != 0));
-        rows += (cc[i] >> 16) * (cc[i] & 0xffffu);
+    for (int i = 0; i < IPT; i++) {
+        const uint32_t c = __umul24(cl[i], cr[i]);
+        ents += (uint32_t)__popcll(__ballot(c != 0));
+        rows += c;
     }
     const TileBefore t = waves_before(ents, last_lane(wave_incl_u32(rows)), s_a, s_b);
     uint32_t at = t.seg, off = t.row;
     const uint64_t lt = lanemask_lt();
 #pragma unroll
-    for (int i = 0; i < ST_IPT; i++) {
-        const uint64_t m = __ballot(cc[i] != 0);
-        const uint32_t c = (cc[i] >> 16) * (cc[i] & 0xffffu);
-        const uint32_t incl = wave_incl_u32(c);
-        if (cc[i]) {
+    for (int i = 0; i < IPT; i++) {
+        const uint32_t c = __umul24(cl[i], cr[i]), incl = wave_incl_u32(c);
+        const uint64_t m = __ballot(c != 0);
+        if (c) {
             const uint32_t e = at + (uint32_t)__popcll(m & lt);
-            s_ent[e] = ((w * ST_IPT + i) * MQ_WAVE + lane()) | ((cc[i] >> 16) << 12) | ((cc[i] & 0xffffu) << 19);
+            s_ent[e] = ((w * IPT + i) * MQ_WAVE + lane()) | (cl[i] << 12) | (cr[i] << 19);
             s_off[e] = off + incl - c;
-            s_key[e] = k[i];
+            s_key[e] = rec.k[i];
         }
         at += (uint32_t)__popcll(m);
         off += last_lane(incl);
     }
-    __syncthreads();  // s_a, s_b have been read; sm.open is set
+    __syncthreads();  // s_a and s_b have been read
     if (w == MQ_WAVES - 1) {
-        // this wave's `at` and `off` count the whole tile
-        uint32_t oc = 0;
-        if (past && sm.open != ~0u) {
-            const uint32_t end = base + ST_TILE, e = min(end + lane(), a.n - 1);
-            uint32_t cl = sm.open_cl, cr = sm.open_cr;
-            const uint32_t last = a.keys[end - 1];
-            seg_beyond<FS>(in, end, last, a.keys[e], FS ? 0u : a.vals[e], cl, cr);
-            oc = cl && cr ? cl * cr : 0u;  // at most MAT_SEG_MAX_PAIRS
-            if (oc && lane() == 0) {
-                s_ent[at] = sm.open | (cl << 12) | (cr << 19);
-                s_off[at] = off;
-                s_key[at] = last;
-            }
-        }
+        // this wave's `at` and `off` count the whole tile; its last segment follows
+        uint32_t pos = 0, ol = 0, orr = 0, oc = 0;
+        if (past && seg_last<FS, IPT>(sm, in, base + TILE, lk, ek, ev, pos, ol, orr))
+            oc = ol && orr ? ol * orr : 0u;  // at most MAT_SEG_MAX_PAIRS
         if (lane() == 0) {
+            if (oc) {
+                s_ent[at] = pos | (ol << 12) | (orr << 19);
+                s_off[at] = off;
+                s_key[at] = lk;
+            }
             s_a[0] = at + (oc ? 1u : 0u);
             s_b[0] = off + oc;
         }
     }
     __syncthreads();
     const uint32_t ne = s_a[0], nrow = s_b[0];
+    if (nrow == 0) return;
     const uint64_t row0 = run_row[tile / g.chunk] + trow[tile];
     const bool sorted_vals = a.use_sval != 0;
-    for (uint32_t r = threadIdx.x; r < nrow; r += MQ_BLOCK) {
-        uint32_t x = 0, y = ne - 1;
-        while (x < y) {
-            const uint32_t mid = (x + y + 1) >> 1;
-            if (s_off[mid] <= r) x = mid;
-            else y = mid - 1;
+    const uint32_t top = 1u << (31 - __builtin_clz(ne));  // the search's first step
+    // MR rows per thread at once: their searches and loads overlap
+    constexpr int MR = NC <= 4 ? 4 : 2;
+    for (uint32_t r0 = threadIdx.x; r0 < nrow; r0 += MR * MQ_BLOCK) {
+        uint32_t r[MR], x[MR];
+#pragma unroll
+        for (int q = 0; q < MR; q++) {
+            r[q] = min(r0 + q * MQ_BLOCK, nrow - 1);
+            x[q] = 0;
         }
-        const uint32_t ent = s_ent[x], rr = r - s_off[x];
-        const uint32_t st = base + (ent & 4095u), cl = (ent >> 12) & 127u, cr = ent >> 19;
-        const bool left_in = left_inner_of(cl, cr, nl, nr);
-        const uint32_t ci = left_in ? cl : cr;
-        const uint32_t outer = rr / ci, inner = rr - outer * ci;
-        const uint32_t lpos = st + (left_in ? inner : outer), rpos = st + cl + (left_in ? outer : inner);
-        const uint64_t j = row0 + r;
-        if (!MQ_IN_BOUNDS(j, a.row_end)) continue;
-        a.out[0][j] = (int32_t)((s_key[x] >> a.key_shift) + (uint32_t)a.key_base);
-        if (sorted_vals) {
+        for (uint32_t step = top; step; step >>= 1) {
+#pragma unroll
+            for (int q = 0; q < MR; q++) {
+                const uint32_t y = x[q] + step;
+                if (y < ne && s_off[y] <= r[q]) x[q] = y;
+            }
+        }
+        uint32_t lpos[MR], rpos[MR];
+        int32_t v[MR][NC];
+#pragma unroll
+        for (int q = 0; q < MR; q++) {
+            const uint32_t ent = s_ent[x[q]], rr = r[q] - s_off[x[q]];
+            const uint32_t st = base + (ent & 4095u), l = (ent >> 12) & 127u, rn = ent >> 19;
+            const bool left_in = left_inner_of(l, rn, nl, nr);
+            const uint32_t ci = left_in ? l : rn;
+            const uint32_t outer = rr / ci, inner = rr - outer * ci;
+            lpos[q] = st + (left_in ? inner : outer);
+            rpos[q] = st + l + (left_in ? outer : inner);
+            v[q][0] = (int32_t)((s_key[x[q]] >> a.key_shift) + (uint32_t)a.key_base);
+        }
+        if (!sorted_vals) {  // record ids to rows of the tables
+#pragma unroll
+            for (int q = 0; q < MR; q++) {
+                lpos[q] = nl > 0 ? a.vals[lpos[q]] : 0u;
+                rpos[q] = nr > 0 ? a.vals[rpos[q]] - a.n_left : 0u;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < MR; q++)
 #pragma unroll
             for (int col = 1; col < NC; col++)
-                if (col < nc) a.out[col][j] = col <= nl ? a.sval[col - 1][lpos] : a.sval[col - 1 - nl][rpos];
-        } else {
-            const uint32_t lrow = nl > 0 ? a.vals[lpos] : 0u;
-            const uint32_t rrow = nr > 0 ? a.vals[rpos] - a.n_left : 0u;
+                if (col < nc) {
+                    const int32_t* src = sorted_vals ? a.sval[col <= nl ? col - 1 : col - 1 - nl]
+                                                     : (col <= nl ? a.lcol[col - 1] : a.rcol[col - 1 - nl]);
+                    v[q][col] = src[col <= nl ? lpos[q] : rpos[q]];
+                }
 #pragma unroll
-            for (int col = 1; col < NC; col++)
-                if (col < nc) a.out[col][j] = col <= nl ? a.lcol[col - 1][lrow] : a.rcol[col - 1 - nl][rrow];
+        for (int q = 0; q < MR; q++) {
+            const uint64_t j = row0 + r0 + q * MQ_BLOCK;
+            if (r0 + q * MQ_BLOCK >= nrow || !MQ_IN_BOUNDS(j, a.row_end)) continue;
+#pragma unroll
+            for (int col = 0; col < NC; col++)
+                if (col < nc) a.out[col][j] = v[q][col];
         }
     }
 }
@@ -1016,7 +1073,11 @@ hipError_t launch_mat_tiles(const MatArgs& a, int side_bit, void* scratch, hipSt
     if (side_bit && (a.nl > 1 || a.nr > 1)) return hipErrorInvalidValue;
     const RunGrid g = seg_grid(a.n);
     const SegScratch s = seg_tiles(scratch, a.n);
-#define MQ_LAUNCH(C, L, F) mat_tile_kernel<C, L, F><<<g.ntiles, MQ_BLOCK, 0, stream>>>(a, g, s.trow, s.run_row)
+#define MQ_LAUNCH(C, L, F)                                                                              \
+    if (seg_few(a.n))                                                                                   \
+        mat_tile_kernel<C, L, F, ST_IPT_FEW><<<g.ntiles, MQ_BLOCK, 0, stream>>>(a, g, s.trow, s.run_row); \
+    else                                                                                                \
+        mat_tile_kernel<C, L, F, ST_IPT><<<g.ntiles, MQ_BLOCK, 0, stream>>>(a, g, s.trow, s.run_row)
 #define MQ_CASE(C)                 \
     case C:                        \
         MQ_LAUNCH(C, -1, 0);       \

@@ -1,6 +1,6 @@
 """Segments and rows straight from the sorted records at the tile's edges:
-segments that end, split or reach past a tile of 4,096 records (by a few, by
-more than 64 and by many tiles), one-sided segments there, key products on
+segments that end, split or reach past a tile of 1,024 (few records) or 4,096
+records (by a few, by more than 64 and by many tiles), one-sided segments there, key products on
 both sides of the 64-pair rule, for carried values, record ids and a packed
 composite key.  Each result must equal the one the definition gives, row for
 row: keys ascending, the side with fewer value bytes inside."""
@@ -11,7 +11,7 @@ import torch
 from tests.conftest import announce
 
 pytestmark = pytest.mark.gpu
-T = 4096
+T = 4096  # a multiple of the smaller tile too; `many` lifts a case to the larger one
 
 
 def rows_of(lk, rk, nlv, nrv):
@@ -54,12 +54,13 @@ NAMES = ["ends_on_the_tile", "head_is_last_record", "split_past_the_tile", "ends
          "single_records", "exactly_one_tile"]
 
 
+@pytest.mark.parametrize("many", [False, True])
 @pytest.mark.parametrize("values", [(1, 1), (0, 1), (2, 1), (1, 3)])
 @pytest.mark.parametrize("name", NAMES)
-def test_rows(sess, name, values):
-    announce(f"segments {name}, {values[0]} + {values[1]} value columns")
+def test_rows(sess, name, values, many):
+    announce(f"segments {name}, {values[0]} + {values[1]} value columns{', many' if many else ''}")
     nlv, nrv = values
-    c = np.array(counts(name))
+    c = np.array(counts(name) + ([(1, 0), (0, 1)] * (1 << 17) if many else []))
     r = np.random.default_rng(5)
     lk = r.permutation(np.repeat(np.arange(len(c)) + 3, c[:, 0])).astype(np.int32)
     rk = r.permutation(np.repeat(np.arange(len(c)) + 3, c[:, 1])).astype(np.int32)

@@ -59,6 +59,40 @@ __device__ __forceinline__ T wave_sum(T v) {
     return v;
 }
 
+// lane - 1's value; lane 0 gets `first` (DPP: the wave shifted right by one)
+__device__ __forceinline__ uint32_t wave_prev(uint32_t v, uint32_t first) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)v, 0x138, 0xf, 0xf, false);
+}
+
+// inclusive wave sum by DPP: within rows of 16, then across them
+__device__ __forceinline__ uint32_t wave_incl_u32(uint32_t x) {
+#define MQ_DPP_ADD(ctrl, rows) x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, rows, 0xf, false)
+    MQ_DPP_ADD(0x111, 0xf);  // row_shr 1, 2, 4, 8
+    MQ_DPP_ADD(0x112, 0xf);
+    MQ_DPP_ADD(0x114, 0xf);
+    MQ_DPP_ADD(0x118, 0xf);
+    MQ_DPP_ADD(0x142, 0xa);  // row_bcast 15 into rows 1 and 3
+    MQ_DPP_ADD(0x143, 0xc);  // row_bcast 31 into rows 2 and 3
+#undef MQ_DPP_ADD
+    return x;
+}
+
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
+#define MQ_DPP_MAX(ctrl, rows) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, rows, 0xf, false))
+    MQ_DPP_MAX(0x111, 0xf);
+    MQ_DPP_MAX(0x112, 0xf);
+    MQ_DPP_MAX(0x114, 0xf);
+    MQ_DPP_MAX(0x118, 0xf);
+    MQ_DPP_MAX(0x142, 0xa);
+    MQ_DPP_MAX(0x143, 0xc);
+#undef MQ_DPP_MAX
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, MQ_WAVE - 1);
+}
+
+__device__ __forceinline__ uint32_t last_lane(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, MQ_WAVE - 1);
+}
+
 // Exclusive scan over the block (MQ_BLOCK threads).  `tmp` is MQ_WAVES
 // entries of LDS.  Returns the exclusive prefix; *total gets the block sum.
 // Contains __syncthreads(); every thread of the block must call it.

@@ -131,78 +131,98 @@ __global__ __launch_bounds__(HRED_WAVES * MQ_WAVE) void hist_reduce_kernel(const
 
 uint32_t radix_hist_part_words(int rb, int passes) { return HIST_BLOCKS * (uint32_t)passes << rb; }
 
-// Waves per block of a radix pass for digits of up to 8 bits at 16 keys per
-// thread: 16 for a carried pass (16,384-record tiles in 140 KB of LDS, one
-// block and 4 waves per SIMD on a CU) and 8 for the first pass (8,192-record
-// tiles, two blocks per CU at its 128-VGPR bound), else 4.  Fewer, larger
-// tiles mean fewer tile-id atomics and look-backs: on a 16M + 16M-record
-// sort 4- and 8-wave blocks took 0.79 ms, 8 and 8 0.76 ms, 8 and 16 0.75 ms.
-__host__ __device__ constexpr int sort_waves(int rb, int kpt, bool gen) {
-    return rb <= 8 && kpt == 16 ? (gen ? 8 : 16) : 4;
-}
+// Shape of a radix pass.  Digits of up to 8 bits at 16 keys per thread run in
+// 16-wave blocks, two to a CU within 64 VGPRs and 75 KB of LDS each, tiles of
+// 16,384 records (32M records, carried pass: 148 us, against 181 us in 8-wave
+// blocks of half the tile, four to a CU: a pass pays for tiles in look-backs).
+// Carried passes of 2^24.6 records and more take 32 keys per thread, tiles of
+// 32,768 records in 137 KB: 133 us at 32M records, but 93 against 88 us at
+// 20M, where 610 tiles fill 256 CUs unevenly.  The first pass (its keys come
+// from two columns) stays at 16: 132 us, against 148.  Everything else, small
+// sorts and wide digits, runs in 4-wave blocks.
+constexpr uint32_t SORT_BIG = 3u << 23;
+__host__ __device__ constexpr bool sort_wide(int rb, int kpt) { return rb <= 8 && kpt == 16; }
+__host__ __device__ constexpr int sort_waves(int rb, int kpt) { return sort_wide(rb, kpt) ? 16 : 4; }
 
-// the first pass is held to 128 VGPRs (4 waves per SIMD instead of 3, no spills)
-template <int RB, int KPT, bool GEN, int NW = sort_waves(RB, KPT, GEN)>
-__global__ __launch_bounds__(NW * MQ_WAVE, GEN ? 4 : 1) void radix_pass_kernel(SortSrc src, const uint32_t* __restrict__ kin,
-                                                                  const uint32_t* __restrict__ vin,
-                                                                  uint32_t* __restrict__ kout,
-                                                                  uint32_t* __restrict__ vout, uint32_t n, int shift,
-                                                                  const uint32_t* __restrict__ ghist,
-                                                                  uint64_t* __restrict__ status,
-                                                                  uint32_t* __restrict__ tile_ctr, uint32_t epoch) {
-    constexpr int TILE = NW * MQ_WAVE * KPT;
-    __shared__ SortSmem<RB, KPT, NW> sm;
-    __shared__ uint32_t s_tile;
-    const uint32_t tile = next_tile(tile_ctr, &s_tile, gridDim.x);
-    const uint32_t base = tile * (uint32_t)TILE;
-    const uint32_t valid_n = min((uint32_t)TILE, n - base);
-    const uint32_t w = threadIdx.x / MQ_WAVE;
-    // wave-striped slice: element i of this lane is base + (w*KPT + i)*64 + lane
-    uint32_t key[KPT], val[KPT];
+// One tile: wave-striped slices, element i of a lane is base + (w*KPT + i)*64 +
+// lane; loads are unconditional (FULL: whole tiles; else clamped into range)
+// and all in flight at once.
+template <int RB, int KPT, bool GEN, int NW, bool FULL>
+__device__ __forceinline__ void radix_tile(SplitSmem<RB, KPT, NW>& sm, const SortSrc& src,
+                                           const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin,
+                                           uint32_t* __restrict__ kout, uint32_t* __restrict__ vout, uint32_t n,
+                                           uint32_t base, uint32_t valid_n, int shift,
+                                           const uint32_t* __restrict__ ghist, uint64_t* __restrict__ status,
+                                           uint32_t tile, uint32_t epoch) {
+    constexpr uint32_t TILE = NW * MQ_WAVE * KPT;
+    const uint32_t o0 = threadIdx.x / MQ_WAVE * KPT * MQ_WAVE + lane();
+    // a first-pass tile on one side of the join loads from a uniform base
+    const bool right = GEN && base >= src.n0;
+    const bool one = GEN && (right || base + TILE <= src.n0);
+    uint32_t key[KPT];
     if (GEN) {
-        // every load first (clamped into range), then the keys and payloads
-        int32_t rk[KPT], rv[KPT];
-        if (base + (uint32_t)TILE <= src.n0 || base >= src.n0) {
-            // the whole tile on one side: loads from a uniform base
-            const bool right = base >= src.n0;
-            const uint32_t b0 = right ? base - src.n0 : base;
-            const int32_t* kt = (right ? src.k1 : src.k0) + b0;
-            const int32_t* vt = (right ? src.v1 : src.v0) + b0;
+        int32_t raw[KPT];
+        if (one) {
+            const int32_t* kt = right ? src.k1 + (base - src.n0) : src.k0 + base;
 #pragma unroll
-            for (int i = 0; i < KPT; i++) {
-                const uint32_t off = min((w * KPT + i) * MQ_WAVE + lane(), valid_n - 1);
-                rk[i] = kt[off];
-                rv[i] = src.carry ? vt[off] : 0;
-            }
+            for (int i = 0; i < KPT; i++) raw[i] = kt[FULL ? o0 + i * MQ_WAVE : min(o0 + i * MQ_WAVE, valid_n - 1)];
         } else {
 #pragma unroll
-            for (int i = 0; i < KPT; i++) {
-                const uint32_t idx = min(base + (w * KPT + i) * MQ_WAVE + lane(), n - 1);
-                rk[i] = src_load(src.k0, src.k1, src.n0, idx);
-                rv[i] = src.carry ? src_load(src.v0, src.v1, src.n0, idx) : 0;
-            }
+            for (int i = 0; i < KPT; i++)
+                raw[i] = src_load(src.k0, src.k1, src.n0, base + min(o0 + i * MQ_WAVE, valid_n - 1));
         }
 #pragma unroll
         for (int i = 0; i < KPT; i++) {
-            const uint32_t off = (w * KPT + i) * MQ_WAVE + lane();
-            const uint32_t idx = base + off;
-            const bool ok = off < valid_n;
-            key[i] = ok ? src_key_of(src, rk[i], idx) : 0u;
-            val[i] = ok ? (src.carry ? (uint32_t)rv[i] : idx) : 0u;
+            key[i] = src_key_of(src, raw[i], base + o0 + i * MQ_WAVE);
+            if (!FULL && o0 + i * MQ_WAVE >= valid_n) key[i] = 0xffffffffu;
         }
     } else {
-        // from the tile's (uniform) base with 32-bit offsets: scalar-base loads
         const uint32_t* kt = kin + base;
-        const uint32_t* vt = vin + base;
 #pragma unroll
         for (int i = 0; i < KPT; i++) {
-            const uint32_t off = (w * KPT + i) * MQ_WAVE + lane();
-            const bool ok = off < valid_n;
-            key[i] = ok ? kt[off] : 0u;
-            val[i] = ok ? vt[off] : 0u;
+            key[i] = kt[FULL ? o0 + i * MQ_WAVE : min(o0 + i * MQ_WAVE, valid_n - 1)];
+            if (!FULL && o0 + i * MQ_WAVE >= valid_n) key[i] = 0xffffffffu;
         }
     }
-    sort_tile<RB, KPT, NW>(sm, key, val, valid_n, shift, ghist, status, tile, 0, epoch, kout, vout, n);
+    const uint32_t* vt = GEN ? nullptr : vin + base;
+    const int32_t* gt = GEN && src.carry && one ? (right ? src.v1 + (base - src.n0) : src.v0 + base) : nullptr;
+    auto load_vals = [&](uint32_t(&val)[KPT]) {
+        if (!GEN) {
+#pragma unroll
+            for (int i = 0; i < KPT; i++) val[i] = vt[FULL ? o0 + i * MQ_WAVE : min(o0 + i * MQ_WAVE, valid_n - 1)];
+        } else if (!src.carry) {
+#pragma unroll
+            for (int i = 0; i < KPT; i++) val[i] = base + o0 + i * MQ_WAVE;
+        } else if (one) {
+#pragma unroll
+            for (int i = 0; i < KPT; i++)
+                val[i] = (uint32_t)gt[FULL ? o0 + i * MQ_WAVE : min(o0 + i * MQ_WAVE, valid_n - 1)];
+        } else {
+#pragma unroll
+            for (int i = 0; i < KPT; i++)
+                val[i] = (uint32_t)src_load(src.v0, src.v1, src.n0, base + min(o0 + i * MQ_WAVE, valid_n - 1));
+        }
+    };
+    sort_tile_split<RB, KPT, NW, FULL>(sm, key, valid_n, shift, ghist, status, tile, epoch, kout, vout, n, load_vals);
+}
+
+template <int RB, int KPT, bool GEN, int NW>
+__global__ __launch_bounds__(NW * MQ_WAVE, NW == 16 && KPT == 16 ? 8 : 4) void radix_pass_kernel(
+    SortSrc src, const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout,
+    uint32_t* __restrict__ vout, uint32_t n, int shift, const uint32_t* __restrict__ ghist,
+    uint64_t* __restrict__ status, uint32_t* __restrict__ tile_ctr, uint32_t epoch) {
+    constexpr uint32_t TILE = NW * MQ_WAVE * KPT;
+    __shared__ SplitSmem<RB, KPT, NW> sm;
+    __shared__ uint32_t s_tile;
+    const uint32_t tile = uni(next_tile(tile_ctr, &s_tile, gridDim.x));
+    const uint32_t base = tile * TILE;
+    const uint32_t valid_n = min(TILE, n - base);
+    if (valid_n == TILE)
+        radix_tile<RB, KPT, GEN, NW, true>(sm, src, kin, vin, kout, vout, n, base, TILE, shift, ghist, status, tile,
+                                           epoch);
+    else
+        radix_tile<RB, KPT, GEN, NW, false>(sm, src, kin, vin, kout, vout, n, base, valid_n, shift, ghist, status,
+                                            tile, epoch);
 }
 
 #define MQ_RB_LIST(X) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11)
@@ -236,20 +256,22 @@ hipError_t launch_radix_pass(int rb, int kpt, const SortSrc& src, const uint32_t
     if (n == 0) return hipSuccess;
     if (shift < 0 || shift > 31) return hipErrorInvalidValue;
     bool gen = kin == nullptr;
-#define MQ_P(B, K)                                                                                          \
-    {                                                                                                       \
-        const uint32_t tiles = radix_tiles(n, K, B, gen);                                                   \
-        if (gen)                                                                                            \
-            radix_pass_kernel<B, K, true><<<tiles, sort_waves(B, K, true) * MQ_WAVE, 0, stream>>>(          \
-                src, kin, vin, kout, vout, n, shift, hist_pass, status, tile_ctr, epoch);                   \
-        else                                                                                                \
-            radix_pass_kernel<B, K, false><<<tiles, sort_waves(B, K, false) * MQ_WAVE, 0, stream>>>(        \
-                src, kin, vin, kout, vout, n, shift, hist_pass, status, tile_ctr, epoch);                   \
-    }
-#define MQ_PK(B)                     \
-    case B:                          \
-        if (kpt == 8) MQ_P(B, 8)     \
-        else MQ_P(B, 16)             \
+#define MQ_P(B, K, KE, G)                                                                                \
+    radix_pass_kernel<B, KE, G, sort_waves(B, K)><<<radix_tiles(n, K, B, G), sort_waves(B, K) * MQ_WAVE, 0, stream>>>( \
+        src, kin, vin, kout, vout, n, shift, hist_pass, status, tile_ctr, epoch)
+    const bool big = n >= SORT_BIG;
+#define MQ_PK(B)                                                  \
+    case B:                                                       \
+        if (kpt == 8) {                                           \
+            if (gen) MQ_P(B, 8, 8, true);                         \
+            else MQ_P(B, 8, 8, false);                            \
+        } else if (gen) {                                         \
+            MQ_P(B, 16, 16, true);                                \
+        } else if (sort_wide(B, 16) && big) {                     \
+            MQ_P(B, 16, (sort_wide(B, 16) ? 32 : 16), false);     \
+        } else {                                                  \
+            MQ_P(B, 16, 16, false);                               \
+        }                                                         \
         break;
     switch (rb) {
         MQ_RB_LIST(MQ_PK)
@@ -261,7 +283,8 @@ hipError_t launch_radix_pass(int rb, int kpt, const SortSrc& src, const uint32_t
 }
 
 uint32_t radix_tiles(uint32_t n, int kpt, int rb, bool gen) {
-    const uint32_t tile = (uint32_t)(sort_waves(rb, kpt, gen) * MQ_WAVE * kpt);
+    const uint32_t per = sort_wide(rb, kpt) && !gen && n >= SORT_BIG ? 32u : (uint32_t)kpt;
+    const uint32_t tile = (uint32_t)(sort_waves(rb, kpt) * MQ_WAVE) * per;
     return (n + tile - 1) / tile;
 }
 

@@ -179,6 +179,198 @@ __device__ __forceinline__ void sort_tile(SortSmem<RB, KPT, NW>& sm, const uint3
     }
 }
 
+// d & ~(a ^ b): one three-input operation
+__device__ __forceinline__ uint32_t and_xnor(uint32_t d, uint32_t a, uint32_t b) {
+    return (uint32_t)__builtin_amdgcn_bitop3_b32((int)d, (int)a, (int)b, 0xf0 & ~(0xcc ^ 0xaa) & 0xff);
+}
+
+// bit b of x, all over the word (the compiler makes two shifts of it)
+__device__ __forceinline__ uint32_t bit_spread(uint32_t x, int b) {
+    uint32_t r;
+    asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(r) : "v"(x), "i"(b));
+    return r;
+}
+
+// The same pass with the tile's keys and payloads staged one after the other
+// in one buffer (half the LDS: two blocks share a CU and one's memory phases
+// overlap the other's ranking).  The payloads are loaded only once the keys
+// are in LDS (load_vals fills the array in key order), so a thread holds one
+// of the two at a time.  Records past valid_n are padding: keys of all ones.
+template <int RB, int KPT, int NW>
+struct SplitSmem {
+    static constexpr int TILE = NW * MQ_WAVE * KPT;
+    uint32_t rec[TILE];
+    uint16_t wcnt[NW][Radix<RB>::BUCKETS];  // per wave and digit: count, then first place in the tile
+    uint32_t goff[Radix<RB>::BUCKETS];      // output place of the digit's first record here, minus its tile place
+    uint32_t tmp[2][NW];
+};
+
+// Values the compiler may not derive again from what it computed before (it
+// would keep 16 addresses per phase alive instead, and spill).
+template <int N>
+__device__ __forceinline__ void opaque(uint32_t (&v)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; i++) asm volatile("" : "+v"(v[i]));
+}
+
+template <int RB, int KPT, int NW, bool FULL, class LoadVals>
+__device__ __forceinline__ void sort_tile_split(SplitSmem<RB, KPT, NW>& sm, uint32_t (&key)[KPT], uint32_t valid_n,
+                                                int shift, const uint32_t* __restrict__ ghist,
+                                                uint64_t* __restrict__ status, uint32_t tile, uint32_t epoch,
+                                                uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
+                                                uint32_t n_out, LoadVals load_vals) {
+    using R = Radix<RB>;
+    constexpr int NT = NW * MQ_WAVE;                 // threads of the block
+    constexpr int BPT = (R::BUCKETS + NT - 1) / NT;  // digits per thread, consecutive
+    static_assert(SplitSmem<RB, KPT, NW>::TILE <= 65536 && KPT % 2 == 0 && R::BUCKETS % 2 == 0, "16-bit places");
+    constexpr uint32_t TILE = SplitSmem<RB, KPT, NW>::TILE;
+    const uint32_t w = threadIdx.x / MQ_WAVE;
+    const uint32_t ln = lane();
+    uint16_t* cnt = sm.wcnt[w];
+    // padding ranks like any key: its digit is the largest and it comes last
+    const uint32_t pad_digit = (0xffffffffu >> shift) & R::MASK;
+    // the wave clears its own counters; the digit threads fetch the histogram
+    for (uint32_t d = ln; d < R::BUCKETS / 2; d += MQ_WAVE) reinterpret_cast<uint32_t*>(cnt)[d] = 0;
+    uint32_t gh[BPT];
+#pragma unroll
+    for (int k = 0; k < BPT; k++) {
+        const uint32_t d = threadIdx.x * BPT + k;
+        gh[k] = d < (uint32_t)R::BUCKETS ? ghist[d] : 0u;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+
+    // stable rank within the wave, digit by digit through the wave's counters
+    // (two 16-bit ranks per register).  Peers of a lane, those with its digit:
+    // per bit, the lanes whose ballot agrees with this lane's bit spread over
+    // 64 bits; one extract, one compare and two three-input operations a bit.
+    // This is what bounds the pass: 41 vector instructions a key at 4 cycles
+    // each, half of a tile's time (75 of them, and 187 us for a pass over 32M
+    // records, with shifts for extracts and population counts of masks).
+    uint32_t place[KPT / 2];
+#pragma unroll
+    for (int i = 0; i < KPT; i++) {
+        const uint32_t x = key[i] >> shift, dg = x & R::MASK;
+        const uint32_t old = cnt[dg];
+        uint32_t lo = ~0u, hi = ~0u;
+#pragma unroll
+        for (int b = 0; b < RB; b++) {
+            const uint32_t spread = bit_spread(x, b);
+            const uint64_t m = __ballot(spread != 0);
+            lo = and_xnor(lo, (uint32_t)m, spread);
+            hi = and_xnor(hi, (uint32_t)(m >> 32), spread);
+        }
+        // the peers below this lane on top of the digit's count so far; the
+        // lowest peer moves the count on
+        const uint32_t rank = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, old));
+        if (rank == old) cnt[dg] = (uint16_t)(old + __popc(lo) + __popc(hi));
+        if (i % 2 == 0)
+            place[i / 2] = rank;
+        else
+            place[i / 2] |= rank << 16;
+        // one key at a time, finished: interleaving keys spills
+        asm volatile("" : "+v"(place[i / 2]));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();
+
+    // per digit: exclusive prefix over the waves, the tile's total (published
+    // at once), and the prefixes over the digits of both the tile's totals
+    // and the pass's histogram
+    uint32_t tot[BPT], sum_t = 0, sum_g = 0;
+    uint64_t* st = status + (uint64_t)tile * R::BUCKETS;
+#pragma unroll
+    for (int k = 0; k < BPT; k++) {
+        const uint32_t d = threadIdx.x * BPT + k;
+        uint32_t run = 0;
+        if (d < (uint32_t)R::BUCKETS) {
+#pragma unroll
+            for (int i = 0; i < NW; i++) {
+                const uint32_t c = sm.wcnt[i][d];
+                sm.wcnt[i][d] = (uint16_t)run;
+                run += c;
+            }
+            if (!FULL && d == pad_digit) run -= TILE - valid_n;
+            st_store(st + d, st_pack(epoch, tile == 0 ? ST_INC : ST_AGG, run));
+        }
+        tot[k] = run;
+        sum_t += run;
+        sum_g += gh[k];
+    }
+    const uint32_t inc_t = wave_incl_u32(sum_t), inc_g = wave_incl_u32(sum_g);
+    if (ln == MQ_WAVE - 1) {
+        sm.tmp[0][w] = inc_t;
+        sm.tmp[1][w] = inc_g;
+    }
+    __syncthreads();
+    uint32_t ex_t = inc_t - sum_t, ex_g = inc_g - sum_g;
+    constexpr int DW = (R::BUCKETS / BPT + MQ_WAVE - 1) / MQ_WAVE;  // waves that own digits
+    uint32_t off[BPT];  // output place minus tile place, before the earlier tiles' records
+#pragma unroll
+    for (int i = 0; i < DW; i++)
+        if ((uint32_t)i < w) {
+            ex_t += sm.tmp[0][i];
+            ex_g += sm.tmp[1][i];
+        }
+#pragma unroll
+    for (int k = 0; k < BPT; k++) {
+        const uint32_t d = threadIdx.x * BPT + k;
+        if (d < (uint32_t)R::BUCKETS) {
+#pragma unroll
+            for (int i = 0; i < NW; i++) sm.wcnt[i][d] = (uint16_t)(sm.wcnt[i][d] + ex_t);
+        }
+        off[k] = ex_g - ex_t;
+        ex_t += tot[k];
+        ex_g += gh[k];
+    }
+    __syncthreads();
+    // keys into LDS in digit order; their places replace the ranks
+    opaque(key);
+    opaque(place);
+#pragma unroll
+    for (int i = 0; i < KPT; i++) {
+        const uint32_t dg = (key[i] >> shift) & R::MASK;
+        place[i / 2] += (uint32_t)cnt[dg] << (16 * (i % 2));
+        sm.rec[(place[i / 2] >> (16 * (i % 2))) & 0xffffu] = key[i];
+    }
+    uint32_t val[KPT];
+    load_vals(val);
+    // the earlier tiles' records of each digit, while the other waves scatter
+#pragma unroll
+    for (int k = 0; k < BPT; k++) {
+        const uint32_t d = threadIdx.x * BPT + k;
+        if (d < (uint32_t)R::BUCKETS) {
+            uint32_t ex = 0;
+            if (tile > 0) {
+                ex = (uint32_t)lookback(status + d, tile, 0, R::BUCKETS, epoch);
+                st_store(st + d, st_pack(epoch, ST_INC, ex + tot[k]));
+            }
+            sm.goff[d] = off[k] + ex;
+        }
+    }
+    __syncthreads();
+    uint32_t g[KPT];  // output place of the tile's record threadIdx.x + i * NT
+#pragma unroll
+    for (int i = 0; i < KPT; i++) {
+        const uint32_t j = threadIdx.x + i * NT;
+        if (FULL || j < valid_n) {
+            const uint32_t k = sm.rec[j];
+            g[i] = sm.goff[(k >> shift) & R::MASK] + j;
+            if (MQ_IN_BOUNDS(g[i], n_out)) kout[g[i]] = k;
+        }
+    }
+    __syncthreads();
+    opaque(place);
+#pragma unroll
+    for (int i = 0; i < KPT; i++) sm.rec[(place[i / 2] >> (16 * (i % 2))) & 0xffffu] = val[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < KPT; i++) {
+        const uint32_t j = threadIdx.x + i * NT;
+        if ((FULL || j < valid_n) && MQ_IN_BOUNDS(g[i], n_out)) vout[g[i]] = sm.rec[j];
+    }
+}
+
 // ------------------------------------------------- segment heads/splits ---
 // Within a key every LEFT record (payload < n_left) precedes every RIGHT
 // one, so exactly one record of each segment writes its split: the first

@@ -14,88 +14,142 @@
 
 namespace mq {
 
-constexpr int SEMI_IPT = 16;
+// Keys outside [base, base + range) (a caller's key bound that does not hold)
+// set nothing.  Repeated keys must not queue on their word, nor read it again
+// and again: each block remembers the keys it set last in LDS, and where most
+// of a wave's keys share a word with a neighbour (a side sorted on the key)
+// the first lane of each such run sets the bits of all of them.  59M keys, 200
+// distinct ones in no order: 115 us (770 with one look at the bitmap per
+// key, one key per thread at a time); 10.5M ascending keys: 42 (332).
+// Few, large blocks: every one of them asks for the hot words once.
+constexpr uint32_t BS_THREADS = 1024, BS_BLOCKS = 512, BS_SEEN = 4096;
 
-// keys outside [base, base + range) (a caller's key bound that does not
-// hold) set nothing.  Of a run of equal keys in consecutive lanes (a side
-// sorted on the key) only the first lane sets the bit, and a bit found set
-// already is not set again, so repeated keys do not queue on one word.
-__global__ __launch_bounds__(MQ_BLOCK) void bitmap_set_kernel(const int32_t* __restrict__ keys, uint32_t n,
+template <int UNROLL>
+__global__ __launch_bounds__(BS_THREADS) void bitmap_set_kernel(const int32_t* __restrict__ keys, uint32_t n,
                                                               int32_t base, uint64_t range, uint32_t* __restrict__ bm) {
-    for (uint32_t i0 = blockIdx.x * MQ_BLOCK; i0 < n; i0 += gridDim.x * MQ_BLOCK) {
-        const uint32_t i = i0 + threadIdx.x;
-        const uint32_t k = i < n ? (uint32_t)keys[i] - (uint32_t)base : ~0u;
-        const uint32_t kp = __shfl_up(k, 1, MQ_WAVE);
-        const bool first = lane() == 0 || kp != k;
-        if (i < n && first && k < range) {
-            const uint32_t bit = 1u << (k & 31u);
-            if (!(__hip_atomic_load(&bm[k >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit))
-                atomicOr(&bm[k >> 5], bit);
+    __shared__ uint32_t seen[BS_SEEN];  // seen[k % BS_SEEN] == k: this block has set k
+    for (uint32_t i = threadIdx.x; i < BS_SEEN; i += BS_THREADS) seen[i] = ~i;  // no key of that place
+    __syncthreads();
+    constexpr uint32_t TILE = BS_THREADS * UNROLL;
+    const uint32_t ntiles = (n + TILE - 1) / TILE;
+    for (uint32_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        const uint32_t i0 = t * TILE + threadIdx.x / MQ_WAVE * (MQ_WAVE * UNROLL) + lane();
+        uint32_t key[UNROLL];
+#pragma unroll
+        for (int u = 0; u < UNROLL; u++) key[u] = (uint32_t)keys[min(i0 + u * MQ_WAVE, n - 1)] - (uint32_t)base;
+#pragma unroll
+        for (int u = 0; u < UNROLL; u++) {
+            const uint32_t k = key[u], word = k >> 5;
+            uint32_t* mark = &seen[k % BS_SEEN];
+            bool fresh = k < range && *mark != k;
+            if (fresh) fresh = atomicExch(mark, k) != k;  // of several lanes with k, one
+            if (__ballot(fresh) == 0ull) continue;
+            uint32_t bits = fresh ? 1u << (k & 31u) : 0u;
+            const bool follows = lane() > 0 && wave_prev(word, 0u) == word;
+            if (__popcll(__ballot(follows)) >= MQ_WAVE / 2) {
+                // neighbours with one word: the run's bits meet in its first lane
+#pragma unroll
+                for (int o = 1; o < MQ_WAVE; o <<= 1) {
+                    const uint32_t w = __shfl_down(word, o, MQ_WAVE), b = __shfl_down(bits, o, MQ_WAVE);
+                    if (lane() + o < MQ_WAVE && w == word) bits |= b;
+                }
+                if (follows) bits = 0;
+            }
+            if (bits && (__hip_atomic_load(&bm[word], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bits) != bits)
+                atomicOr(&bm[word], bits);
         }
     }
 }
 
-// Persistent tiles of 256 x SEMI_IPT records: one __ballot per record slot,
-// wave totals scanned in LDS, the tile's output offset from a decoupled
-// look-back; kept records are written in input order.
-__global__ __launch_bounds__(MQ_BLOCK) void semi_filter_kernel(SemiArgs a, uint64_t* __restrict__ status,
-                                                               uint32_t* __restrict__ tile_ctr, uint32_t epoch,
-                                                               Mail mail) {
-    constexpr uint32_t TILE = MQ_BLOCK * SEMI_IPT;
-    __shared__ uint32_t s_tile;
-    __shared__ uint32_t s_wtot[MQ_WAVES];
-    __shared__ uint64_t s_excl;
-    const uint32_t ntiles = (a.n + TILE - 1) / TILE;
+// The filter in two launches over the same chunks, at most SEMI_BLOCKS of them:
+// the first leaves one mask bit per record and a count per chunk, the second
+// adds up the counts before its chunk and writes the kept records in input
+// order.  No block waits for another: with one launch, tiles numbered by a
+// counter (11 ns each) and a look-back over them took 42 us on 4M keys and 52
+// on 10.5M; this takes 29 and 37.
+constexpr uint32_t SEMI_THREADS = 1024, SEMI_IPT = 4, SEMI_BLOCKS = 2048;
+constexpr uint32_t SEMI_TILE = SEMI_THREADS * SEMI_IPT;
+
+__global__ __launch_bounds__(SEMI_THREADS) void semi_mask_kernel(SemiArgs a, uint32_t tiles_per) {
+    __shared__ uint32_t s_wtot[SEMI_THREADS / MQ_WAVE];
+    const uint32_t w = threadIdx.x / MQ_WAVE;
+    uint32_t run = 0;
+    for (uint32_t t = 0; t < tiles_per; t++) {
+        const uint64_t at = ((uint64_t)blockIdx.x * tiles_per + t) * SEMI_TILE + w * (SEMI_IPT * MQ_WAVE);
+        if (at >= a.n) break;
+        const uint32_t base = (uint32_t)at;
+        uint32_t key[SEMI_IPT], word[SEMI_IPT];
+#pragma unroll
+        for (uint32_t i = 0; i < SEMI_IPT; i++)
+            key[i] = (uint32_t)a.keys[min(base + i * MQ_WAVE + lane(), a.n - 1)] - (uint32_t)a.base;
+#pragma unroll
+        for (uint32_t i = 0; i < SEMI_IPT; i++) word[i] = a.bm[key[i] < a.range ? key[i] >> 5 : 0u];
+#pragma unroll
+        for (uint32_t i = 0; i < SEMI_IPT; i++) {
+            const uint32_t first = base + i * MQ_WAVE;
+            const uint64_t m =
+                __ballot(first + lane() < a.n && key[i] < a.range && ((word[i] >> (key[i] & 31u)) & 1u));
+            if (lane() == 0 && first < a.n) a.masks[first / MQ_WAVE] = m;
+            run += (uint32_t)__popcll(m);
+        }
+    }
+    if (lane() == 0) s_wtot[w] = run;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (uint32_t i = 1; i < SEMI_THREADS / MQ_WAVE; i++) run += s_wtot[i];
+        a.counts[blockIdx.x] = run;
+    }
+}
+
+__global__ __launch_bounds__(SEMI_THREADS) void semi_write_kernel(SemiArgs a, uint32_t tiles_per, Mail mail) {
+    constexpr uint32_t WAVES = SEMI_THREADS / MQ_WAVE;
+    __shared__ uint32_t s_w[2][WAVES];
     const uint32_t w = threadIdx.x / MQ_WAVE;
     const uint64_t lt = lanemask_lt();
-    for (;;) {
-        const uint32_t tile = next_tile(tile_ctr, &s_tile, ntiles + gridDim.x);
-        if (tile >= ntiles) break;
-        const uint32_t base = tile * TILE;
-        uint32_t key[SEMI_IPT];
+    uint32_t before = 0;
+    for (uint32_t i = threadIdx.x; i < blockIdx.x; i += SEMI_THREADS) before += a.counts[i];
+    before = (uint32_t)wave_sum((uint64_t)before);
+    if (lane() == 0) s_w[0][w] = before;
+    __syncthreads();
+    uint32_t pos = 0;
+    for (uint32_t i = 0; i < WAVES; i++) pos += s_w[0][i];
+    const uint32_t mine = a.counts[blockIdx.x];
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        *a.count = pos + mine;
+        mail.data[0] = pos + mine;
+        mail_post(mail);
+    }
+    if (mine == 0) return;
+    for (uint32_t t = 0; t < tiles_per; t++) {
+        const uint64_t tile0 = ((uint64_t)blockIdx.x * tiles_per + t) * SEMI_TILE;
+        if (tile0 >= a.n) break;
+        const uint64_t at0 = tile0 + w * (SEMI_IPT * MQ_WAVE);
         uint64_t km[SEMI_IPT];
-#pragma unroll
-        for (int i = 0; i < SEMI_IPT; i++) {
-            const uint32_t idx = base + (w * SEMI_IPT + i) * MQ_WAVE + lane();
-            key[i] = idx < a.n ? (uint32_t)a.keys[idx] - (uint32_t)a.base : 0u;
-        }
         uint32_t run = 0;
 #pragma unroll
-        for (int i = 0; i < SEMI_IPT; i++) {
-            const uint32_t idx = base + (w * SEMI_IPT + i) * MQ_WAVE + lane();
-            const bool ok = idx < a.n && key[i] < a.range && ((a.bm[key[i] >> 5] >> (key[i] & 31u)) & 1u);
-            km[i] = __ballot(ok);
+        for (uint32_t i = 0; i < SEMI_IPT; i++) {
+            km[i] = at0 + i * MQ_WAVE < a.n ? a.masks[at0 / MQ_WAVE + i] : 0ull;
             run += (uint32_t)__popcll(km[i]);
         }
-        if (lane() == 0) s_wtot[w] = run;
+        if (lane() == 0) s_w[(t + 1) & 1][w] = run;  // the other buffer: the last one is still read
         __syncthreads();
-        uint32_t wex = 0, ttot = 0;
+        uint32_t wex = 0, all = 0;
+        for (uint32_t i = 0; i < WAVES; i++) {
+            const uint32_t c = s_w[(t + 1) & 1][i];
+            wex += i < w ? c : 0u;
+            all += c;
+        }
+        uint32_t at = pos + wex;
+        pos += all;
 #pragma unroll
-        for (int i = 0; i < MQ_WAVES; i++) {
-            if ((uint32_t)i < w) wex += s_wtot[i];
-            ttot += s_wtot[i];
-        }
-        if (w == 0) {
-            const uint64_t ex = tile_prefix_wave0(status, tile, epoch, ttot);
-            if (lane() == 0) {
-                s_excl = ex;
-                if (tile == ntiles - 1) {
-                    *a.count = (uint32_t)(ex + ttot);
-                    mail.data[0] = (uint32_t)(ex + ttot);
-                    mail_post(mail);
-                }
-            }
-        }
-        __syncthreads();
-        uint32_t pos = (uint32_t)s_excl + wex;
-        for (int i = 0; i < SEMI_IPT; i++) {  // fully unrolled by the compiler (km stays in registers)
+        for (uint32_t i = 0; i < SEMI_IPT; i++) {
             if ((km[i] >> lane()) & 1ull) {
-                const uint32_t idx = base + (w * SEMI_IPT + i) * MQ_WAVE + lane();
-                const uint32_t at = pos + (uint32_t)__popcll(km[i] & lt);
-                a.kout[at] = key[i];
-                a.vout[at] = a.id_base + idx;
+                const uint32_t idx = (uint32_t)at0 + i * MQ_WAVE + lane();
+                const uint32_t o = at + (uint32_t)__popcll(km[i] & lt);
+                a.kout[o] = (uint32_t)a.keys[idx] - (uint32_t)a.base;
+                a.vout[o] = a.id_base + idx;
             }
-            pos += (uint32_t)__popcll(km[i]);
+            at += (uint32_t)__popcll(km[i]);
         }
     }
 }
@@ -116,21 +170,31 @@ __global__ __launch_bounds__(MQ_BLOCK) void side_records_kernel(const int32_t* _
 hipError_t launch_bitmap_set(const int32_t* keys, uint32_t n, int32_t base, uint64_t range, uint32_t* bm,
                              hipStream_t stream) {
     if (n == 0) return hipSuccess;
-    const uint32_t blocks = std::min<uint32_t>((n + MQ_BLOCK - 1) / MQ_BLOCK, 2048u);
-    bitmap_set_kernel<<<blocks, MQ_BLOCK, 0, stream>>>(keys, n, base, range, bm);
+    // a small side: one key per thread, all chains of loads and atomics side by side
+    if (n <= BS_THREADS * BS_BLOCKS)
+        bitmap_set_kernel<1><<<(n - 1) / BS_THREADS + 1, BS_THREADS, 0, stream>>>(keys, n, base, range, bm);
+    else
+        bitmap_set_kernel<16><<<BS_BLOCKS, BS_THREADS, 0, stream>>>(keys, n, base, range, bm);
     return hipGetLastError();
 }
 
-hipError_t launch_semi_filter(const SemiArgs& a, uint64_t* status, uint32_t* tile_ctr, uint32_t epoch, Mail mail,
-                              hipStream_t stream) {
-    if (a.n == 0) return hipSuccess;
-    const uint32_t tiles = (a.n + MQ_BLOCK * SEMI_IPT - 1) / (MQ_BLOCK * SEMI_IPT);
-    const uint32_t blocks = std::min<uint32_t>(tiles, 256u * 8u);
-    semi_filter_kernel<<<blocks, MQ_BLOCK, 0, stream>>>(a, status, tile_ctr, epoch, mail);
+static uint32_t semi_tiles(uint32_t n) { return (n - 1) / SEMI_TILE + 1; }
+
+hipError_t launch_semi_filter(const SemiArgs& args, void* scratch, Mail mail, hipStream_t stream) {
+    if (args.n == 0) return hipSuccess;
+    const uint32_t tiles = semi_tiles(args.n), per = (tiles - 1) / SEMI_BLOCKS + 1;
+    const uint32_t blocks = (tiles - 1) / per + 1;
+    SemiArgs a = args;
+    a.masks = static_cast<uint64_t*>(scratch);
+    a.counts = reinterpret_cast<uint32_t*>(a.masks + ((size_t)a.n - 1) / MQ_WAVE + 1);
+    semi_mask_kernel<<<blocks, SEMI_THREADS, 0, stream>>>(a, per);
+    semi_write_kernel<<<blocks, SEMI_THREADS, 0, stream>>>(a, per, mail);
     return hipGetLastError();
 }
 
-uint32_t semi_filter_tiles(uint32_t n) { return (n + MQ_BLOCK * SEMI_IPT - 1) / (MQ_BLOCK * SEMI_IPT); }
+size_t semi_scratch_bytes(uint32_t n) {
+    return n == 0 ? 0 : (((size_t)n - 1) / MQ_WAVE + 1) * 8 + (size_t)std::min(semi_tiles(n), SEMI_BLOCKS) * 4;
+}
 
 hipError_t launch_side_records(const int32_t* keys, uint32_t n, int32_t base, uint32_t id_base,
                                const uint32_t* at_dev, uint32_t* kout, uint32_t* vout, hipStream_t stream) {

@@ -61,7 +61,8 @@ uint32_t merge_tiles(uint32_t ns);
 // (range bits, cleared by the caller); the filter keeps the records of
 // `keys` whose relative key is set, writing (relative key, id_base + index)
 // in input order to kout/vout and the kept count to *count and the mail's
-// first word.  tile_ctr is 0 before and after the launch.
+// first word.  scratch: semi_scratch_bytes(n), 8-byte aligned, at most 8 bytes
+// per record of both sides; masks and counts are set from it.
 struct SemiArgs {
     const int32_t* keys;
     uint32_t n;
@@ -72,12 +73,13 @@ struct SemiArgs {
     uint32_t* kout;
     uint32_t* vout;
     uint32_t* count;
+    uint64_t* masks;
+    uint32_t* counts;
 };
 hipError_t launch_bitmap_set(const int32_t* keys, uint32_t n, int32_t base, uint64_t range, uint32_t* bm,
                              hipStream_t stream);
-hipError_t launch_semi_filter(const SemiArgs& a, uint64_t* status, uint32_t* tile_ctr, uint32_t epoch, Mail mail,
-                              hipStream_t stream);
-uint32_t semi_filter_tiles(uint32_t n);
+hipError_t launch_semi_filter(const SemiArgs& a, void* scratch, Mail mail, hipStream_t stream);
+size_t semi_scratch_bytes(uint32_t n);
 // Exact join size: cnt[k - base] += 1 over one side's keys (cnt cleared by
 // the caller, range entries), then *total += sum of cnt[k - base] over the
 // other side's keys (*total cleared by the caller).

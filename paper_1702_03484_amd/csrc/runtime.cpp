@@ -97,7 +97,7 @@ static inline uint32_t* counter(Ctx* ctx, int i) { return ctx->small + SMALL_CTR
 // scalar slots (u32 word index inside the scalar area)
 enum { SC_NSEG = 0, SC_NPRED = 2, SC_COUNT = 4, SC_INGEST = 6, SC_SEMI = 12, SC_PRECOUNT = 14 };
 // counter slots (running bounds: three words each)
-enum { CT_PASS0 = 0, CT_COUNT = 9, CT_SEMI = 11, CT_COMPACT = 12, CT_LOCATE = 13, CT_MINMAX = 14, CT_SAMPLE = 24 };
+enum { CT_PASS0 = 0, CT_COUNT = 9, CT_COMPACT = 12, CT_LOCATE = 13, CT_MINMAX = 14, CT_SAMPLE = 24 };
 
 // Polls the flag: a short wait ends within a microsecond of the report (a
 // stream synchronisation takes about 5 us to return).  After 5 ms, when that
@@ -1152,13 +1152,11 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
             uint32_t* bits = bm.as<uint32_t>();
             HIPCHK(launch_fill_u32(bits, words, 0u, ctx->stream));
             HIPCHK(launch_bitmap_set(left_big ? rkey : lkey, nsm, kmin, range, bits, ctx->stream));
-            if (!ctx->ensure_status(semi_filter_tiles(nb) + 1))
-                return ctx->fail(MAPSQ_ERR_CAPACITY, "arena: status words");
             const uint32_t at = left_big ? 0u : nL;
             SemiArgs sa{left_big ? lkey : rkey, nb, kmin, range, bits, at, b.k[0] + at, b.v[0] + at,
-                        scalar32(ctx, SC_SEMI)};
+                        scalar32(ctx, SC_SEMI), nullptr, nullptr};
             const Mail mail = ctx->next_mail();
-            HIPCHK(launch_semi_filter(sa, ctx->status, counter(ctx, CT_SEMI), ctx->next_epoch(), mail, ctx->stream));
+            HIPCHK(launch_semi_filter(sa, seg_off, mail, ctx->stream));  // its scratch fits the later offsets' room
             if (left_big)  // the RIGHT records follow the kept LEFT ones
                 HIPCHK(launch_side_records(rkey, nR, kmin, nL, scalar32(ctx, SC_SEMI), b.k[0], b.v[0], ctx->stream));
             else

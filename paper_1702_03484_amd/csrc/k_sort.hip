@@ -129,6 +129,12 @@ __global__ __launch_bounds__(HRED_WAVES * MQ_WAVE) void hist_reduce_kernel(const
     }
 }
 
+hipError_t launch_hist_reduce(const uint32_t* part, uint32_t rows, uint32_t width, uint32_t* hist,
+                              hipStream_t stream) {
+    hist_reduce_kernel<<<(width + MQ_WAVE - 1) / MQ_WAVE, HRED_WAVES * MQ_WAVE, 0, stream>>>(part, rows, width, hist);
+    return hipGetLastError();
+}
+
 uint32_t radix_hist_part_words(int rb, int passes) { return HIST_BLOCKS * (uint32_t)passes << rb; }
 
 // Shape of a radix pass.  Digits of up to 8 bits at 16 keys per thread run in
@@ -186,7 +192,7 @@ __device__ __forceinline__ void radix_tile(SplitSmem<RB, KPT, NW>& sm, const Sor
     }
     const uint32_t* vt = GEN ? nullptr : vin + base;
     const int32_t* gt = GEN && src.carry && one ? (right ? src.v1 + (base - src.n0) : src.v0 + base) : nullptr;
-    auto load_vals = [&](uint32_t(&val)[KPT]) {
+    auto load_vals = [&](int, uint32_t(&val)[KPT]) {
         if (!GEN) {
 #pragma unroll
             for (int i = 0; i < KPT; i++) val[i] = vt[FULL ? o0 + i * MQ_WAVE : min(o0 + i * MQ_WAVE, valid_n - 1)];
@@ -203,7 +209,8 @@ __device__ __forceinline__ void radix_tile(SplitSmem<RB, KPT, NW>& sm, const Sor
                 val[i] = (uint32_t)src_load(src.v0, src.v1, src.n0, base + min(o0 + i * MQ_WAVE, valid_n - 1));
         }
     };
-    sort_tile_split<RB, KPT, NW, FULL>(sm, key, valid_n, shift, ghist, status, tile, epoch, kout, vout, n, load_vals);
+    sort_tile_split<RB, KPT, NW, FULL>(sm, key, valid_n, shift, ghist, status, tile, epoch, kout, n, 1, load_vals,
+                                       [&](int) { return vout; });
 }
 
 template <int RB, int KPT, bool GEN, int NW>
@@ -246,8 +253,7 @@ hipError_t launch_radix_hist(const SortSrc& src, const uint32_t* keys, uint32_t 
     }
 #undef MQ_H
     const uint32_t width = (uint32_t)passes << rb;
-    hist_reduce_kernel<<<(width + MQ_WAVE - 1) / MQ_WAVE, HRED_WAVES * MQ_WAVE, 0, stream>>>(part, blocks, width, hist);
-    return hipGetLastError();
+    return launch_hist_reduce(part, blocks, width, hist, stream);
 }
 
 hipError_t launch_radix_pass(int rb, int kpt, const SortSrc& src, const uint32_t* kin, const uint32_t* vin,

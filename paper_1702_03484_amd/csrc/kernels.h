@@ -97,6 +97,49 @@ hipError_t launch_key_sample(const int32_t* a, uint32_t na, const int32_t* b, ui
 hipError_t launch_side_records(const int32_t* keys, uint32_t n, int32_t base, uint32_t id_base,
                                const uint32_t* at_dev, uint32_t* kout, uint32_t* vout, hipStream_t stream);
 
+// Counting shuffle of a join with few distinct keys (k_few.hip).  Every word
+// of a bitmap of range bits becomes an entry (bits, bits set in the words
+// before); the first FEW_KEYS set bits' positions go to keys (base added) and
+// their number to the mail (2 words).  status: few_table_tiles look-back words.
+constexpr uint32_t FEW_KEYS = 1023;  // a digit of 10 bits, its last value left for records without a partner
+struct FewEntry {
+    uint32_t bits, before;
+};
+hipError_t launch_few_table(const uint32_t* bm, uint64_t range, int32_t base, FewEntry* table, int32_t* keys,
+                            uint64_t* status, uint32_t* tile_ctr, uint32_t epoch, Mail mail, hipStream_t stream);
+uint32_t few_table_tiles(uint64_t range);
+// One side of that shuffle: rows whose key - base is in the table, grouped by
+// the key's rank in it, in input order inside a group.  Row i's values are
+// in[c][ids[i]] (ids null: in[c][i]) and go to out[c].
+constexpr int FEW_COLS = 3;
+struct FewSide {
+    const int32_t* keys;
+    const uint32_t* ids;
+    uint32_t n;
+    int32_t base;
+    uint64_t range;
+    const FewEntry* table;
+    int32_t nv;
+    const int32_t* in[FEW_COLS];
+    int32_t* out[FEW_COLS];
+};
+// digit width for a table of nkeys <= FEW_KEYS keys
+int few_bits(uint32_t nkeys);
+// rows of each rank into hist[2^rb]; part: few_part_words(rb)
+hipError_t launch_few_hist(const FewSide& s, int rb, uint32_t* part, uint32_t* hist, hipStream_t stream);
+uint32_t few_part_words(int rb);
+// Segments of nkeys keys from both sides' histograms; every key has rows on
+// both sides.  Runs, output offsets and *nseg as launch_merge_segments writes
+// them; lkey[first row of the LEFT run] = the key; mail as launch_seg_sum's,
+// then the LEFT rows that have a partner.
+hipError_t launch_few_segments(const uint32_t* lhist, const uint32_t* rhist, const int32_t* keys, uint32_t nkeys,
+                               uint32_t* seg_ls, uint32_t* seg_lc, uint32_t* seg_rs, uint32_t* seg_rc,
+                               uint64_t* seg_off, uint32_t* nseg, int32_t* lkey, Mail mail, hipStream_t stream);
+// the rows of s into their n_out places; s.nv >= 1; status: few_status_words
+hipError_t launch_few_pass(const FewSide& s, int rb, const uint32_t* hist, uint32_t n_out, uint64_t* status,
+                           uint32_t* tile_ctr, uint32_t epoch, hipStream_t stream);
+size_t few_status_words(uint32_t n, int rb);
+
 // Digit histograms of `passes` passes into hist[passes][2^rb] (overwritten);
 // the first digit's lowest bit is bit `shift0` of the key.
 // keys == nullptr: read the keys from `src`.  `part` is scratch of
@@ -104,6 +147,9 @@ hipError_t launch_side_records(const int32_t* keys, uint32_t n, int32_t base, ui
 hipError_t launch_radix_hist(const SortSrc& src, const uint32_t* keys, uint32_t n, int rb, int shift0, int passes,
                              uint32_t* part, uint32_t* hist, hipStream_t stream);
 uint32_t radix_hist_part_words(int rb, int passes);
+// hist[c] = the sum of part[r * width + c] over r < rows
+hipError_t launch_hist_reduce(const uint32_t* part, uint32_t rows, uint32_t width, uint32_t* hist,
+                              hipStream_t stream);
 // One stable pass on the digit whose lowest bit is `shift`.  kin == nullptr: first-pass mode from
 // `src` (vin ignored).  hist_pass = this pass's histogram; status holds
 // radix_tiles(n,kpt,rb,true) * 2^rb words; tile_ctr is 0 before and after the

@@ -7,6 +7,7 @@
 // each join to the GPU.
 #include <algorithm>
 #include <cstring>
+#include <map>
 
 #include "runtime.h"
 
@@ -313,19 +314,32 @@ mapsq_status query(Ctx* ctx, const mapsq_pattern* pats, int32_t npats, const int
     }
     std::vector<mapsq_plan_step> plan;
     mapsq_table cur{};
+    // distinct values a variable can have in the result so far: no more than
+    // the rows of any table it came through
+    std::map<int32_t, int64_t> values;
+    auto bound = [&](const mapsq_table& t) {
+        for (int c = 0; c < t.ncols; c++) {
+            auto at = values.emplace(t.var[c], t.nrows).first;
+            at->second = std::min(at->second, t.nrows);
+        }
+    };
     // one join step: cur JOIN tabs[pick] (a cross product when key < 0);
     // est_rows is the step's expected output (negative: none)
     auto step = [&](int pick, int32_t key, int32_t candidates, double est_rows) -> mapsq_status {
         mapsq_table nxt{};
+        bound(cur);
         ctx->join_est_rows = key < 0 ? -1.0 : est_rows;
+        ctx->join_left_keys = key < 0 ? -1 : values[key];
         mapsq_status st = key < 0 ? cross_join(ctx, cur, tabs[pick], &nxt)
                                   : join_tables(ctx, &cur, &tabs[pick], key, &nxt);
         ctx->join_est_rows = -1.0;
+        ctx->join_left_keys = -1;
         if (st) {
             free_table(ctx, &cur);
             cleanup();
             return st;
         }
+        bound(tabs[pick]);
         free_table(ctx, &cur);
         free_table(ctx, &tabs[pick]);
         used[pick] = true;

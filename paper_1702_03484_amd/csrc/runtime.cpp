@@ -764,10 +764,171 @@ static mapsq_status result_room(Ctx* ctx, uint64_t rows, int nc) {
     return MAPSQ_OK;
 }
 
+// The join of a LEFT side with at most FEW_KEYS distinct keys (k_few.hip):
+// *done stays false when there is no room for the scratch or more keys than
+// that, and nothing has happened then.
+template <class SetMeta, class Finish>
+static mapsq_status few_join(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, int lk, int rk,
+                             const std::vector<int>& lv, const std::vector<int>& rv, int32_t kmin, uint64_t range,
+                             int key_bits, mapsq_join_stats& js, SetMeta set_meta, Finish finish, mapsq_table* out,
+                             bool* done) {
+    const uint32_t nL = (uint32_t)L->nrows, nR = (uint32_t)R->nrows;
+    const int nl = (int)lv.size(), nr = (int)rv.size(), nc = 1 + nl + nr;
+    const uint64_t words = (range + 31) / 32;
+    const size_t lb = align_up(size_t(nL) * 4, ARENA_ALIGN), rb4 = align_up(size_t(nR) * 4, ARENA_ALIGN);
+    const size_t bmb = align_up(words * 4, ARENA_ALIGN), tabb = align_up(words * sizeof(FewEntry), ARENA_ALIGN);
+    constexpr size_t SEGB = (FEW_KEYS + 1) * 4;  // one array of a word per key
+    const int rb_max = few_bits(FEW_KEYS);
+    Block keys = alloc_block(ctx, bmb + tabb + SEGB);
+    Block kept_rows = alloc_block(ctx, 2 * rb4 + semi_scratch_bytes(nR));
+    Block left = alloc_block(ctx, lb * (1 + nl));
+    Block segs = alloc_block(ctx, SEGB * 6);
+    Block part = alloc_block(ctx, size_t(few_part_words(rb_max)) * 4);
+    if (!keys.ok() || !kept_rows.ok() || !left.ok() || !segs.ok() || !part.ok()) return MAPSQ_OK;
+    if (!ctx->ensure_status(std::max({few_status_words(nL, rb_max), few_status_words(nR, rb_max),
+                                      (size_t)few_table_tiles(range)})))
+        return MAPSQ_OK;
+    uint32_t* bm = keys.as<uint32_t>();
+    FewEntry* table = reinterpret_cast<FewEntry*>(ctx->arena.ptr(keys.off) + bmb);
+    int32_t* klist = reinterpret_cast<int32_t*>(ctx->arena.ptr(keys.off) + bmb + tabb);
+    uint32_t* rkeys = kept_rows.as<uint32_t>();
+    uint32_t* rids = reinterpret_cast<uint32_t*>(ctx->arena.ptr(kept_rows.off) + rb4);
+    mapsq_status st;
+
+    // RIGHT records whose key the LEFT side has, then the keys those have
+    int ph = ctx->prof_begin(8);
+    HIPCHK(launch_fill_u32(bm, words, 0u, ctx->stream));
+    HIPCHK(launch_bitmap_set(L->col[lk], nL, kmin, range, bm, ctx->stream));
+    SemiArgs sa{R->col[rk], nR, kmin, range, bm, 0u, rkeys, rids, scalar32(ctx, SC_SEMI),
+                nullptr, nullptr};
+    Mail mail = ctx->next_mail();
+    HIPCHK(launch_semi_filter(sa, ctx->arena.ptr(kept_rows.off) + 2 * rb4, mail, ctx->stream));
+    if ((st = wait_mail(ctx, mail))) return *done = true, st;
+    const uint32_t kept = mail.data[0];
+    uint64_t nkeys = 0;
+    if (kept) {
+        HIPCHK(launch_fill_u32(bm, words, 0u, ctx->stream));
+        HIPCHK(launch_bitmap_set(reinterpret_cast<const int32_t*>(rkeys), kept, 0, range, bm, ctx->stream));
+        mail = ctx->next_mail();
+        HIPCHK(launch_few_table(bm, range, kmin, table, klist, ctx->status, counter(ctx, CT_COUNT), ctx->next_epoch(),
+                                mail, ctx->stream));
+        if ((st = wait_mail(ctx, mail))) return *done = true, st;
+        nkeys = mail64(mail, 0);
+    }
+    // bitmap cleared twice and read once, every key read, the kept rows written and their keys read
+    ctx->prof_end(ph, 20.0 * words + 4.0 * nL + 4.0 * nR + 12.0 * kept);
+    if (nkeys > FEW_KEYS) return MAPSQ_OK;
+    Block right;
+    if (kept && nr) {
+        right = alloc_block(ctx, align_up(size_t(kept) * 4, ARENA_ALIGN) * nr);
+        if (!right.ok()) return MAPSQ_OK;
+    }
+    *done = true;
+    js.path = MAPSQ_PATH_SEMIJOIN;
+    js.sorted_records = nL + kept;
+    js.key_bits = key_bits;
+    ctx->last = js;
+    if (kept == 0) {
+        set_meta(out);
+        out->owned = 1;
+        out->nrows = 0;
+        return MAPSQ_OK;
+    }
+
+    // rows per key and side, segments
+    const int rb = few_bits((uint32_t)nkeys);
+    FewSide sl{L->col[lk], nullptr, nL, kmin, range, table, nl, {}, {}};
+    FewSide sr{reinterpret_cast<const int32_t*>(rkeys), rids, kept, 0, range, table, nr, {}, {}};
+    int32_t* lkeys = left.as<int32_t>();  // only the first row of each key's run is written
+    for (int c = 0; c < nl; c++) {
+        sl.in[c] = L->col[lv[c]];
+        sl.out[c] = reinterpret_cast<int32_t*>(ctx->arena.ptr(left.off) + lb * (1 + c));
+    }
+    for (int c = 0; c < nr; c++) {
+        sr.in[c] = R->col[rv[c]];
+        sr.out[c] = reinterpret_cast<int32_t*>(ctx->arena.ptr(right.off) +
+                                               align_up(size_t(kept) * 4, ARENA_ALIGN) * c);
+    }
+    uint32_t* hist_l = ctx->small + SMALL_HIST;
+    uint32_t* hist_r = hist_l + (FEW_KEYS + 1);
+    char* sp = ctx->arena.ptr(segs.off);
+    uint32_t* seg[4];
+    for (int i = 0; i < 4; i++) seg[i] = reinterpret_cast<uint32_t*>(sp + SEGB * (2 + i));
+    uint64_t* seg_off = reinterpret_cast<uint64_t*>(sp);
+    ph = ctx->prof_begin(2);
+    HIPCHK(launch_few_hist(sl, rb, part.as<uint32_t>(), hist_l, ctx->stream));
+    HIPCHK(launch_few_hist(sr, rb, part.as<uint32_t>(), hist_r, ctx->stream));
+    mail = ctx->next_mail();
+    HIPCHK(launch_few_segments(hist_l, hist_r, klist, (uint32_t)nkeys, seg[0], seg[1], seg[2], seg[3], seg_off,
+                               scalar32(ctx, SC_NSEG), lkeys, mail, ctx->stream));
+    ctx->prof_end(ph, 4.0 * nL + 4.0 * kept);
+    if ((st = wait_mail(ctx, mail))) return st;
+    const uint64_t total = mail64(mail, 2);
+    const uint32_t rows_l = mail.data[6];
+    js.segments = (int64_t)nkeys;
+    js.out_rows = (int64_t)total;
+    js.radix_bits = rb;
+    js.passes = 1;
+    ctx->last = js;
+    if (total >= SAT40_HOST) return ctx->fail(MAPSQ_ERR_TOO_LARGE, "join result exceeds 2^40 rows");
+    set_meta(out);
+    if (ctx->count_only) {
+        out->owned = 1;
+        out->nrows = (int64_t)total;
+        return MAPSQ_OK;
+    }
+    mapsq_table m{};
+    if ((st = result_room(ctx, total, nc))) return st;
+    if (alloc_table(ctx, (int64_t)total, nc, &m))
+        return ctx->fail(MAPSQ_ERR_TOO_LARGE, "join result exceeds the arena's free space");
+    // a launch that fails frees the result first
+    auto step = [&](hipError_t e, const char* what) -> mapsq_status {
+        if (e == hipSuccess) return MAPSQ_OK;
+        free_table(ctx, &m);
+        return ctx->fail(MAPSQ_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
+    };
+    ph = ctx->prof_begin(1);
+    if (nl && (st = step(launch_few_pass(sl, rb, hist_l, rows_l, ctx->status, counter(ctx, CT_PASS0),
+                                         ctx->next_epoch(), ctx->stream), "shuffle")))
+        return st;
+    if (nr && (st = step(launch_few_pass(sr, rb, hist_r, kept, ctx->status, counter(ctx, CT_PASS0 + 1),
+                                         ctx->next_epoch(), ctx->stream), "shuffle")))
+        return st;
+    // each side's keys and values read, the values of rows with a partner written
+    ctx->prof_end(ph, (nl ? 4.0 * (1 + nl) * nL + 4.0 * nl * rows_l : 0.0) + (nr ? (8.0 + 8.0 * nr) * kept : 0.0));
+    MatArgs a{};
+    a.keys = reinterpret_cast<const uint32_t*>(lkeys);
+    a.seg_start = seg[0];
+    a.seg_cl = seg[1];
+    a.seg_split = seg[2];
+    a.seg_cr = seg[3];
+    a.seg_off = seg_off;
+    a.nseg = scalar32(ctx, SC_NSEG);
+    a.key_base = 0;
+    a.nl = nl;
+    a.nr = nr;
+    for (int i = 0; i < nl; i++) a.lcol[i] = sl.out[i];
+    for (int i = 0; i < nr; i++) a.rcol[i] = sr.out[i];
+    for (int c = 0; c < nc; c++) a.out[c] = m.col[c];
+    a.row_begin = 0;
+    a.row_end = total;
+    a.sparse = total < SPARSE_ROWS_PER_SEG * nkeys ? 1 : 0;
+    a.max_blocks = ctx->mat_blocks(total);
+    ph = ctx->prof_begin(3);
+    st = step(launch_materialize(a, ctx->stream), "materialize");
+    ctx->prof_end(ph, 4.0 * nc * (double)total + 4.0 * nl * (double)rows_l + 4.0 * nr * (double)kept);
+    if (st) return st;
+    ctx->acc.joins += 1;
+    ctx->acc.rows_out += (int64_t)total;
+    return finish(m, total);
+}
+
 mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, int32_t key_var, mapsq_table* out) {
     zero_table(out);
     const double est_rows = ctx->join_est_rows;  // this call's estimate only
     ctx->join_est_rows = -1.0;
+    const int64_t left_keys = ctx->join_left_keys;
+    ctx->join_left_keys = -1;
     mapsq_status st;
     if ((st = check_table(ctx, L, "left")) || (st = check_table(ctx, R, "right"))) return st;
     const int lk = col_of(L, key_var), rk = col_of(R, key_var);
@@ -1046,6 +1207,18 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
     const bool packed = composite && key_bits <= 32 && low_bits <= 31;
     int rb, kpt;
     pick_tuning(ctx, key_bits, rb, kpt, (uint64_t)nL + nR);
+
+    // A LEFT side known to hold few distinct keys: both sides grouped by the
+    // key's number among the shared ones, one counting pass each.  No room for
+    // its scratch: the sort below, which asks for at least as much (the bitmap and
+    // its table take 12 bytes per 32 keys, so the range is held to 16 per row).
+    const uint64_t key_range = (uint64_t)((int64_t)kmax - (int64_t)kmin) + 1;
+    if (!composite && ctx->semijoin != 1 && ctx->precount != 2 && left_keys >= 0 && left_keys <= (int64_t)FEW_KEYS &&
+        nL >= FEW_MIN_RECORDS && lv.size() <= FEW_COLS && rv.size() <= FEW_COLS && key_bits > 8 && key_range / 16 <= nL) {
+        bool done = false;
+        st = few_join(ctx, L, R, lk, rk, lv, rv, kmin, key_range, key_bits, js, set_meta, finish, out, &done);
+        if (done) return st;
+    }
 
     // A large shuffle first gets the exact |RS| from two passes over the
     // keys (dense key counts of one side, summed over the other side's

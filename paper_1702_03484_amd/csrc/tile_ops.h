@@ -213,12 +213,15 @@ __device__ __forceinline__ void opaque(uint32_t (&v)[N]) {
     for (int i = 0; i < N; i++) asm volatile("" : "+v"(v[i]));
 }
 
-template <int RB, int KPT, int NW, bool FULL, class LoadVals>
+// load_vals(c, array) fetches the payloads of column c of np; vout(c) is where
+// they go.  KEYS = false: key holds bare digits, which are not written, and a
+// record whose place is n_out or beyond is dropped.
+template <int RB, int KPT, int NW, bool FULL, bool KEYS = true, class LoadVals, class ValsOut>
 __device__ __forceinline__ void sort_tile_split(SplitSmem<RB, KPT, NW>& sm, uint32_t (&key)[KPT], uint32_t valid_n,
                                                 int shift, const uint32_t* __restrict__ ghist,
                                                 uint64_t* __restrict__ status, uint32_t tile, uint32_t epoch,
-                                                uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
-                                                uint32_t n_out, LoadVals load_vals) {
+                                                uint32_t* __restrict__ kout, uint32_t n_out, int np,
+                                                LoadVals load_vals, ValsOut vout) {
     using R = Radix<RB>;
     constexpr int NT = NW * MQ_WAVE;                 // threads of the block
     constexpr int BPT = (R::BUCKETS + NT - 1) / NT;  // digits per thread, consecutive
@@ -334,7 +337,7 @@ __device__ __forceinline__ void sort_tile_split(SplitSmem<RB, KPT, NW>& sm, uint
         sm.rec[(place[i / 2] >> (16 * (i % 2))) & 0xffffu] = key[i];
     }
     uint32_t val[KPT];
-    load_vals(val);
+    load_vals(0, val);
     // the earlier tiles' records of each digit, while the other waves scatter
 #pragma unroll
     for (int k = 0; k < BPT; k++) {
@@ -356,18 +359,25 @@ __device__ __forceinline__ void sort_tile_split(SplitSmem<RB, KPT, NW>& sm, uint
         if (FULL || j < valid_n) {
             const uint32_t k = sm.rec[j];
             g[i] = sm.goff[(k >> shift) & R::MASK] + j;
-            if (MQ_IN_BOUNDS(g[i], n_out)) kout[g[i]] = k;
+            if (KEYS && MQ_IN_BOUNDS(g[i], n_out)) kout[g[i]] = k;
         }
     }
-    __syncthreads();
-    opaque(place);
+    for (int c = 0;;) {
+        __syncthreads();
+        opaque(place);
 #pragma unroll
-    for (int i = 0; i < KPT; i++) sm.rec[(place[i / 2] >> (16 * (i % 2))) & 0xffffu] = val[i];
-    __syncthreads();
+        for (int i = 0; i < KPT; i++) sm.rec[(place[i / 2] >> (16 * (i % 2))) & 0xffffu] = val[i];
+        __syncthreads();
+        const bool more = c + 1 < np;
+        if (more) load_vals(c + 1, val);
+        uint32_t* __restrict__ vo = vout(c);
 #pragma unroll
-    for (int i = 0; i < KPT; i++) {
-        const uint32_t j = threadIdx.x + i * NT;
-        if ((FULL || j < valid_n) && MQ_IN_BOUNDS(g[i], n_out)) vout[g[i]] = sm.rec[j];
+        for (int i = 0; i < KPT; i++) {
+            const uint32_t j = threadIdx.x + i * NT;
+            if ((FULL || j < valid_n) && (KEYS ? MQ_IN_BOUNDS(g[i], n_out) : g[i] < n_out)) vo[g[i]] = sm.rec[j];
+        }
+        if (!more) break;
+        c++;
     }
 }
 

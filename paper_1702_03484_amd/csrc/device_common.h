@@ -255,6 +255,48 @@ __device__ __forceinline__ uint64_t tile_prefix_wave0(uint64_t* status, uint32_t
     return tile_prefix_wave(status, tile, 0, epoch, agg);
 }
 
+// Both bounds of v in the ascending c[lo, hi): the first element >= v and the
+// first > v, by a group of G consecutive lanes (all with the same arguments):
+// one probe of G evenly spaced elements a level, for both bounds while they lie
+// in one bracket, then half of the group for each.  A level costs one memory
+// round trip and leaves 1/G of the bracket.
+template <int G, class Pos>
+__device__ __forceinline__ void group_bounds(const int32_t* __restrict__ c, Pos lo, Pos hi, int32_t v, Pos& lower,
+                                             Pos& upper) {
+    static_assert(G >= 4 && G <= MQ_WAVE && (G & (G - 1)) == 0, "group of lanes");
+    constexpr int LOG = __builtin_ctz(G);
+    const uint32_t gl = lane() % G, g0 = lane() - gl;
+    const uint64_t gmask = G == MQ_WAVE ? ~0ull : (1ull << (G % MQ_WAVE)) - 1ull;
+    Pos l0 = lo, l1 = hi, u0 = lo, u1 = hi;
+    while (l0 < l1 || u0 < u1) {
+        const bool one = l0 == u0 && l1 == u1;
+        const bool up = !one && gl >= G / 2;  // this lane probes for the upper bound only
+        const Pos p0 = up ? u0 : l0, p1 = up ? u1 : l1;
+        const int sh = one ? LOG : LOG - 1;  // 2^sh probes a bound
+        const uint32_t at = one ? gl : gl % (G / 2);
+        const Pos up1 = ((Pos)1 << sh) - 1, step = (p1 - p0 + up1) >> sh;
+        const Pos pos = p0 + (Pos)at * step;
+        const bool in = pos < p1;
+        const int32_t x = in ? c[pos] : 0;
+        const uint64_t below = __ballot(in && x < v) >> g0 & gmask;      // probes before the lower bound (a prefix)
+        const uint64_t upto = __ballot(in && x <= v) >> g0 & gmask;      // before the upper bound
+        constexpr uint64_t LOW = (1ull << (G / 2)) - 1ull;
+        const uint32_t nl = (uint32_t)__popcll(one ? below : below & LOW);
+        const uint32_t nu = (uint32_t)__popcll(one ? upto : upto >> (G / 2));
+        const Pos sl = (l1 - l0 + up1) >> sh, su = (u1 - u0 + up1) >> sh;
+        if (l0 < l1) {
+            l1 = nl == 0 ? l0 : min(l1, l0 + (Pos)nl * sl);
+            l0 = nl == 0 ? l0 : l0 + (Pos)(nl - 1) * sl + 1;
+        }
+        if (u0 < u1) {
+            u1 = nu == 0 ? u0 : min(u1, u0 + (Pos)nu * su);
+            u0 = nu == 0 ? u0 : u0 + (Pos)(nu - 1) * su + 1;
+        }
+    }
+    lower = l0;
+    upper = u0;
+}
+
 // Next dynamic tile id from a counter (thread 0), broadcast through LDS.
 // takes > 0: the ids the whole launch will take; whoever takes the last one
 // sets the counter back to 0, so it needs no clearing before the next launch.

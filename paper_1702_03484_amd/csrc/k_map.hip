@@ -396,42 +396,21 @@ hipError_t launch_compact(const CompactArgs& a, uint64_t* scratch, uint64_t* sta
     return hipGetLastError();
 }
 
-// First index in [lo, hi) whose value is >= v (upper = false) or > v
-// (upper = true), by a 64-ary search: one coalesced probe of 64 positions and
-// one __ballot per level.  Every lane of the wave calls it with the same
-// arguments.
-__device__ __forceinline__ int64_t wave_bound(const int32_t* __restrict__ c, int64_t lo, int64_t hi, int32_t v,
-                                              bool upper) {
-    while (lo < hi) {
-        const int64_t step = (hi - lo + MQ_WAVE - 1) / MQ_WAVE;
-        const int64_t pos = lo + (int64_t)lane() * step;
-        bool below = false;
-        if (pos < hi) {
-            const int32_t x = c[pos];
-            below = upper ? x <= v : x < v;
-        }
-        const uint32_t cnt = (uint32_t)__popcll(__ballot(below));  // probes before the bound (a prefix)
-        if (cnt == 0) return lo;
-        const int64_t nlo = lo + (int64_t)(cnt - 1) * step + 1;
-        hi = std::min(hi, lo + (int64_t)cnt * step);
-        lo = nlo;
-    }
-    return lo;
-}
-
-// the range of one query, by one wave
+// the range of one query, by one wave: both ends of a level in one search
 __device__ __forceinline__ void locate(const LocateQuery& x, int64_t& lo, int64_t& hi) {
     lo = x.lo;
     hi = x.hi;
     if (x.col1) {
-        const int64_t l = wave_bound(x.col1, lo, hi, x.v1, false);
-        hi = wave_bound(x.col1, l, hi, x.v1, true);
+        int64_t l, u;
+        group_bounds<MQ_WAVE, int64_t>(x.col1, lo, hi, x.v1, l, u);
         lo = l;
+        hi = u;
     }
     if (x.col2) {
-        const int64_t l = wave_bound(x.col2, lo, hi, x.v2, false);
-        hi = wave_bound(x.col2, l, hi, x.v2, true);
+        int64_t l, u;
+        group_bounds<MQ_WAVE, int64_t>(x.col2, lo, hi, x.v2, l, u);
         lo = l;
+        hi = u;
     }
 }
 

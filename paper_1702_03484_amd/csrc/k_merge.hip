@@ -201,15 +201,105 @@ __global__ __launch_bounds__(MQ_BLOCK) void merge_segments_kernel(MergeArgs a, u
     }
 }
 
-uint32_t merge_tiles(uint32_t ns) { return (ns + MQ_BLOCK * MRG_IPT - 1) / (MQ_BLOCK * MRG_IPT); }
+// The same for a small side of at most MRG_FEW rows, where the pass above is a
+// chain: the samples' fetch, 22 steps in LDS, then a load per halving.  Here
+// MRG_GROUP lanes search for one key together, so a level takes 1/16 of the
+// bracket (500K keys: five loads one after the other), and the run's end on the
+// small side is one more load beside them; two waves look back at once.  60,
+// 1,000 and 8,000 keys in 500K: 5, 8 and 9.6 us (8, 10.5 and 12.7 above).  At
+// 64,000 keys the 16 lanes a key are too many: 33 us against 18; 16,000 are even.
+constexpr int MRG_GROUP = 16;
+constexpr uint32_t MRG_FEW = 8192;
+constexpr uint32_t FEW_THREADS = 1024, FEW_TILE = FEW_THREADS / MRG_GROUP;
+static_assert(FEW_TILE == MQ_WAVE, "one wave takes the tile's keys");
+
+__global__ __launch_bounds__(FEW_THREADS) void merge_few_kernel(MergeArgs a, uint64_t* __restrict__ status,
+                                                                uint32_t* __restrict__ tile_ctr, uint32_t epoch,
+                                                                Mail mail) {
+    __shared__ uint32_t s_tile;
+    __shared__ uint64_t s_ex[2];
+    __shared__ uint32_t s_bl[FEW_TILE], s_bc[FEW_TILE], s_sc[FEW_TILE];
+    const uint32_t ntiles = gridDim.x;
+    const uint32_t tile = next_tile(tile_ctr, &s_tile, ntiles);
+    const uint32_t slot = threadIdx.x / MRG_GROUP, gl = threadIdx.x % MRG_GROUP;
+    const uint32_t idx = tile * FEW_TILE + slot;
+    uint32_t bl = 0, bc = 0, sc = 0;
+    if (idx < a.ns) {
+        const int32_t key = a.skey[idx];
+        const int32_t prev = a.skey[idx ? idx - 1 : 0u];
+        const uint32_t ahead = idx + 1 + gl;
+        const int32_t next = a.skey[min(ahead, a.ns - 1)];
+        if (idx == 0 || prev != key) {
+            const uint64_t same = __ballot(ahead < a.ns && next == key) >> (lane() - gl) & ((1ull << MRG_GROUP) - 1);
+            uint32_t ub;
+            group_bounds<MRG_GROUP, uint32_t>(a.bkey, 0u, a.nb, key, bl, ub);
+            bc = ub - bl;
+            sc = 1 + (uint32_t)__popcll(same);
+            if (bc && sc == MRG_GROUP + 1) {  // a longer run: the rows of one key are a prefix of the rest
+                uint32_t none, end;
+                group_bounds<MRG_GROUP, uint32_t>(a.skey, idx + sc, a.ns, key, none, end);
+                sc = end - idx;
+            }
+        }
+    }
+    if (gl == 0) {
+        s_bl[slot] = bl;
+        s_bc[slot] = bc;
+        s_sc[slot] = sc;
+    }
+    __syncthreads();
+    // two waves look back side by side, one for the segments, one for the rows
+    const uint32_t w = threadIdx.x / MQ_WAVE;
+    bl = s_bl[lane()];
+    bc = s_bc[lane()];
+    sc = s_sc[lane()];
+    const uint64_t km = __ballot(bc != 0);
+    const uint64_t rows = (uint64_t)sc * bc;
+    const uint64_t rincl = wave_incl_scan(rows);
+    const uint64_t seg_tot = (uint64_t)__popcll(km), row_tot = __shfl(rincl, MQ_WAVE - 1, MQ_WAVE);
+    if (w < 2) {
+        const uint64_t ex = tile_prefix_wave0(status + w * ntiles, tile, epoch, w == 0 ? seg_tot : row_tot);
+        if (lane() == 0) s_ex[w] = ex;
+    }
+    __syncthreads();
+    if (w > 0) return;
+    const uint32_t es = (uint32_t)s_ex[0];
+    const uint64_t er = s_ex[1];
+    if (tile == ntiles - 1 && lane() == 0) {
+        const uint64_t total = sat_add(er, row_tot > SAT40 ? SAT40 : row_tot);
+        const uint32_t nseg = es + (uint32_t)seg_tot;
+        *a.nseg = nseg;
+        mail.data[0] = nseg;
+        mail.data[2] = (uint32_t)total;
+        mail.data[3] = (uint32_t)(total >> 32);
+        mail_post(mail);
+    }
+    if (bc != 0) {
+        const uint32_t at = es + (uint32_t)__popcll(km & lanemask_lt());
+        const uint32_t i = tile * FEW_TILE + lane();
+        a.seg_lstart[at] = a.small_is_left ? i : bl;
+        a.seg_lcount[at] = a.small_is_left ? sc : bc;
+        a.seg_rstart[at] = a.small_is_left ? bl : i;
+        a.seg_rcount[at] = a.small_is_left ? bc : sc;
+        a.seg_off[at] = sat_add(er, rincl - rows);
+    }
+}
+
+uint32_t merge_tiles(uint32_t ns) {
+    const uint32_t tile = ns <= MRG_FEW ? FEW_TILE : MQ_BLOCK * MRG_IPT;
+    return (ns + tile - 1) / tile;
+}
 
 hipError_t launch_merge_segments(const MergeArgs& a, uint64_t* status, uint32_t* tile_ctr, uint32_t epoch, Mail mail,
                                  hipStream_t stream) {
     if (a.ns == 0) return hipSuccess;
+    if (a.ns <= MRG_FEW) {
+        merge_few_kernel<<<merge_tiles(a.ns), FEW_THREADS, 0, stream>>>(a, status, tile_ctr, epoch, mail);
+        return hipGetLastError();
+    }
     const uint32_t blocks = std::min<uint32_t>(merge_tiles(a.ns), 256u * 8u);
     merge_segments_kernel<<<blocks, MQ_BLOCK, 0, stream>>>(a, status, tile_ctr, epoch, mail);
     return hipGetLastError();
 }
 
 }  // namespace mq
-

@@ -221,52 +221,74 @@ __global__ __launch_bounds__(MQ_BLOCK) void bhist_kernel(const BatchHdr* __restr
         }
 }
 
-// 16 keys per thread: at most 168 VGPRs (3 waves per SIMD instead of 2);
-// 32: the 72 KB tile in LDS allows 2 blocks per CU, so up to 256 VGPRs
+// A tile of 256 x KPT records is sorted by KPT / 2 waves, 8 keys per thread
+// (64 VGPRs, no spills): 16-wave blocks, two to a CU, for the default tiles.
+// 16 joins of 8M records, four passes: 96 us, 155 in 4-wave blocks of 32
+// keys per thread with both halves of a record in LDS at once.
+constexpr int BPASS_KPT = 8;
+constexpr int bpass_waves(int kpt) { return kpt * (int)MQ_BLOCK / (int)MQ_WAVE / BPASS_KPT; }
+// one resident round of blocks
+constexpr uint32_t bpass_blocks(int kpt) { return 256u * 32u / (uint32_t)bpass_waves(kpt); }
+
+template <int RB, int NW, bool GEN, bool FULL>
+__device__ __forceinline__ void bpass_tile(SplitSmem<RB, BPASS_KPT, NW>& sm, const BatchHdr* __restrict__ h,
+                                           const BatchJoin& J, const uint32_t* __restrict__ hist, uint32_t base,
+                                           uint32_t valid_n, int pass, uint32_t t, uint32_t epoch) {
+    // the first pass of an unfiltered join reads its records from the tables;
+    // every other pass (and the first one of a filtered join) reads the sorted
+    // records of the previous one (the compacted kept records)
+    const bool gen = GEN && !J.filt;
+    const int src = (pass - 1) & 1, dst = pass & 1;  // the first pass writes buffer 0
+    const uint32_t o0 = threadIdx.x / MQ_WAVE * BPASS_KPT * MQ_WAVE + lane();
+    auto at = [&](int i) { return FULL ? o0 + i * MQ_WAVE : min(o0 + i * MQ_WAVE, valid_n - 1); };
+    uint32_t key[BPASS_KPT];
+    if (gen) {
+#pragma unroll
+        for (int i = 0; i < BPASS_KPT; i++) key[i] = bsrc_key(J, base + at(i));
+    } else {
+        const uint32_t* kin = h->keys[src] + J.rec_off + base;
+#pragma unroll
+        for (int i = 0; i < BPASS_KPT; i++) key[i] = kin[at(i)];
+    }
+    if (!FULL) {
+#pragma unroll
+        for (int i = 0; i < BPASS_KPT; i++)
+            if (o0 + i * MQ_WAVE >= valid_n) key[i] = 0xffffffffu;
+    }
+    const uint32_t* vin = h->vals[src] + J.rec_off + base;
+    uint32_t* vout = h->vals[dst] + J.rec_off;
+    sort_tile_split<RB, BPASS_KPT, NW, FULL>(
+        sm, key, valid_n, pass * RB, hist, h->status, t, J.tile_off, epoch, h->keys[dst] + J.rec_off, J.nrec, 1,
+        [&](int, uint32_t(&val)[BPASS_KPT]) {
+#pragma unroll
+            for (int i = 0; i < BPASS_KPT; i++) val[i] = gen ? base + at(i) : vin[at(i)];
+        },
+        [&](int) { return vout; });
+}
+
 template <int RB, int KPT, bool GEN>
-__global__ __launch_bounds__(MQ_BLOCK, KPT > 16 ? 2 : 3) void bpass_kernel(const BatchHdr* __restrict__ h, int pass) {
-    using R = Radix<RB>;
+__global__ __launch_bounds__(bpass_waves(KPT) * MQ_WAVE, 8) void bpass_kernel(const BatchHdr* __restrict__ h, int pass) {
+    constexpr int NW = bpass_waves(KPT);
     constexpr uint32_t TILE = MQ_BLOCK * KPT;
-    __shared__ SortSmem<RB, KPT> sm;
+    static_assert(TILE == NW * MQ_WAVE * BPASS_KPT, "the waves cover the tile");
+    __shared__ SplitSmem<RB, BPASS_KPT, NW> sm;
     __shared__ uint32_t s_tile;
     const uint32_t T = h->total_tiles, passes = h->passes;
     const uint32_t epoch = h->epoch0 + pass;
-    const int src = (pass - 1) & 1, dst = pass & 1;  // the first pass writes buffer 0
-    const uint32_t w = threadIdx.x / MQ_WAVE;
     for (;;) {
-        const uint32_t t = next_tile(&h->ctr[pass], &s_tile);
+        const uint32_t t = uni(next_tile(&h->ctr[pass], &s_tile));
         if (t >= T) break;
-        const uint32_t j = h->tile_join[t];
+        const uint32_t j = uni(h->tile_join[t]);
         const BatchJoin& J = h->joins[j];
-        // the first pass of an unfiltered join reads its records from the
-        // tables; every other pass (and the first one of a filtered join)
-        // reads the sorted records of the previous one (the compacted kept
-        // records), and the join's tiles past them have nothing to do (no
-        // later tile of the join waits on them)
-        const bool gen = GEN && !J.filt;
         const uint32_t n = J.nrec;
         const uint32_t base = (t - J.tile_off) * TILE;
-        if (base >= n) continue;
+        if (base >= n) continue;  // past the kept records: no later tile of the join waits on this one
         const uint32_t valid_n = min(TILE, n - base);
-        uint32_t key[KPT], val[KPT];
-        const uint32_t* kin = h->keys[src] + J.rec_off;
-        const uint32_t* vin = h->vals[src] + J.rec_off;
-#pragma unroll
-        for (int i = 0; i < KPT; i++) {
-            const uint32_t off = (w * KPT + i) * MQ_WAVE + lane();
-            const uint32_t idx = base + off;
-            const bool ok = off < valid_n;
-            if (gen) {
-                const uint32_t k = bsrc_key(J, min(idx, n - 1));
-                key[i] = ok ? k : 0u;
-                val[i] = idx;
-            } else {
-                key[i] = ok ? kin[idx] : 0u;
-                val[i] = ok ? vin[idx] : 0u;
-            }
-        }
-        sort_tile<RB, KPT>(sm, key, val, valid_n, pass * RB, h->hist + ((uint64_t)j * passes + pass) * R::BUCKETS,
-                           h->status, t, J.tile_off, epoch, h->keys[dst] + J.rec_off, h->vals[dst] + J.rec_off, n);
+        const uint32_t* hist = h->hist + ((uint64_t)j * passes + pass) * Radix<RB>::BUCKETS;
+        if (valid_n == TILE)
+            bpass_tile<RB, NW, GEN, true>(sm, h, J, hist, base, valid_n, pass, t, epoch);
+        else
+            bpass_tile<RB, NW, GEN, false>(sm, h, J, hist, base, valid_n, pass, t, epoch);
     }
 }
 
@@ -480,8 +502,9 @@ static hipError_t launch_batch_t(const BatchHdr* hdr, int passes, hipStream_t st
     bcompact_kernel<KPT><<<BATCH_BLOCKS_5, MQ_BLOCK, 0, stream>>>(hdr);
     bhist_kernel<RB, KPT><<<BATCH_BLOCKS_8, MQ_BLOCK, 0, stream>>>(hdr);
     for (int p = 0; p < passes; p++) {
-        if (p == 0) bpass_kernel<RB, KPT, true><<<BATCH_BLOCKS, MQ_BLOCK, 0, stream>>>(hdr, p);
-        else bpass_kernel<RB, KPT, false><<<BATCH_BLOCKS, MQ_BLOCK, 0, stream>>>(hdr, p);
+        constexpr uint32_t threads = bpass_waves(KPT) * MQ_WAVE;
+        if (p == 0) bpass_kernel<RB, KPT, true><<<bpass_blocks(KPT), threads, 0, stream>>>(hdr, p);
+        else bpass_kernel<RB, KPT, false><<<bpass_blocks(KPT), threads, 0, stream>>>(hdr, p);
     }
     bheads_kernel<KPT><<<BATCH_BLOCKS_5, MQ_BLOCK, 0, stream>>>(h);
     bcount_kernel<KPT><<<BATCH_BLOCKS, MQ_BLOCK, 0, stream>>>(h);

@@ -222,7 +222,7 @@ __device__ __forceinline__ void few_tile(SplitSmem<RB, FP_KPT, NW>& sm, const Fe
                 val[i] = (uint32_t)in[FULL ? o + i * MQ_WAVE : min(o + i * MQ_WAVE, valid_n - 1)];
         }
     };
-    sort_tile_split<RB, FP_KPT, NW, FULL, false>(sm, key, valid_n, 0, hist, status, tile, epoch, nullptr, n_out, s.nv,
+    sort_tile_split<RB, FP_KPT, NW, FULL, false>(sm, key, valid_n, 0, hist, status, tile, 0, epoch, nullptr, n_out, s.nv,
                                                  load_vals,
                                                  [&](int c) { return reinterpret_cast<uint32_t*>(s.out[c]); });
 }

@@ -209,7 +209,7 @@ __device__ __forceinline__ void radix_tile(SplitSmem<RB, KPT, NW>& sm, const Sor
                 val[i] = (uint32_t)src_load(src.v0, src.v1, src.n0, base + min(o0 + i * MQ_WAVE, valid_n - 1));
         }
     };
-    sort_tile_split<RB, KPT, NW, FULL>(sm, key, valid_n, shift, ghist, status, tile, epoch, kout, n, 1, load_vals,
+    sort_tile_split<RB, KPT, NW, FULL>(sm, key, valid_n, shift, ghist, status, tile, 0, epoch, kout, n, 1, load_vals,
                                        [&](int) { return vout; });
 }
 

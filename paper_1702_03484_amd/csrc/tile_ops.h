@@ -15,169 +15,7 @@ struct Radix {
     static constexpr int BUCKETS = 1 << RB;
     static constexpr uint32_t MASK = BUCKETS - 1;
     static constexpr int MAXP = (32 + RB - 1) / RB;
-    static constexpr int BPT = (BUCKETS + MQ_BLOCK - 1) / MQ_BLOCK;  // buckets per thread
 };
-
-// NW waves per block (a tile is NW * 64 * KPT records)
-template <int RB, int KPT, int NW = MQ_WAVES>
-struct SortSmem {
-    static constexpr int TILE = NW * MQ_WAVE * KPT;
-    uint32_t keys[TILE];
-    uint32_t vals[TILE];
-    uint32_t wcnt[NW][Radix<RB>::BUCKETS];
-    uint32_t local[Radix<RB>::BUCKETS];
-    uint32_t goff[Radix<RB>::BUCKETS];
-    uint32_t tmp[NW];
-};
-
-// Exclusive scan of the BUCKETS values in LDS `in` into LDS `out` (may
-// alias), by wave 0 alone (lane L owns buckets L*PER ... L*PER + PER - 1),
-// then one barrier: the other waves only wait once.
-template <int RB>
-__device__ __forceinline__ void scan_buckets(const uint32_t* in, uint32_t* out, uint32_t* tmp) {
-    using R = Radix<RB>;
-    constexpr int PER = (R::BUCKETS + MQ_WAVE - 1) / MQ_WAVE;
-    (void)tmp;
-    if (threadIdx.x < MQ_WAVE) {
-        uint32_t loc[PER];
-        uint32_t sum = 0;
-#pragma unroll
-        for (int k = 0; k < PER; k++) {
-            const uint32_t d = lane() * PER + k;
-            loc[k] = d < (uint32_t)R::BUCKETS ? in[d] : 0u;
-            sum += loc[k];
-        }
-        uint32_t ex = wave_incl_scan(sum) - sum;
-#pragma unroll
-        for (int k = 0; k < PER; k++) {
-            const uint32_t d = lane() * PER + k;
-            if (d < (uint32_t)R::BUCKETS) out[d] = ex;
-            ex += loc[k];
-        }
-    }
-    __syncthreads();
-}
-
-// One stable radix pass over one tile whose records are already in
-// registers (wave-striped: element i of a lane is tile position
-// (wave*KPT + i)*64 + lane; positions >= valid_n are padding).  Ranks the
-// digits, publishes the tile's digit counts, looks back over the join's
-// earlier tiles, and scatters the tile to kout/vout (join-relative).
-// `ghist` is the join's digit histogram of this pass; n_out the records of
-// the output (checked in the bounds-checked build only).  Every thread of
-// the block calls it.
-template <int RB, int KPT, int NW = MQ_WAVES>
-__device__ __forceinline__ void sort_tile(SortSmem<RB, KPT, NW>& sm, const uint32_t (&key)[KPT],
-                                          const uint32_t (&val)[KPT], uint32_t valid_n, int shift,
-                                          const uint32_t* __restrict__ ghist, uint64_t* __restrict__ status,
-                                          uint32_t tile, uint32_t first_tile, uint32_t epoch,
-                                          uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
-                                          uint32_t n_out) {
-    using R = Radix<RB>;
-    constexpr int NT = NW * MQ_WAVE;                       // threads of the block
-    constexpr int BPT = (R::BUCKETS + NT - 1) / NT;        // buckets per thread
-    const uint32_t w = threadIdx.x / MQ_WAVE;
-    const uint32_t ln = lane();
-    for (int d = threadIdx.x; d < R::BUCKETS; d += NT) {
-        sm.goff[d] = ghist[d];
-#pragma unroll
-        for (int i = 0; i < NW; i++) sm.wcnt[i][d] = 0;
-    }
-    __syncthreads();
-    scan_buckets<RB>(sm.goff, sm.goff, sm.tmp);
-
-    // stable rank within the wave, digit by digit through the wave counters
-    // (ranks are below the tile size, 2^16: two per register)
-    static_assert(NT * KPT <= 65536 && KPT % 2 == 0, "16-bit ranks");
-    uint32_t rank2[KPT / 2];
-    const uint64_t lt = lanemask_lt();
-#pragma unroll
-    for (int i = 0; i < KPT; i++) {
-        const uint32_t off = (w * KPT + i) * MQ_WAVE + ln;
-        const bool ok = off < valid_n;
-        const uint32_t dg = (key[i] >> shift) & R::MASK;
-        // lanes whose digit differs in some bit: per bit, the ballot of
-        // that bit xor this lane's bit spread over 64 bits (0 or all ones)
-        uint32_t diff_lo = 0, diff_hi = 0;
-#pragma unroll
-        for (int b = 0; b < RB; b++) {
-            const int32_t top = (int32_t)(dg << (31 - b));  // digit bit b in the sign bit
-            const uint64_t m = __ballot(top < 0);
-            const uint32_t spread = (uint32_t)(top >> 31);
-            diff_lo |= (uint32_t)m ^ spread;
-            diff_hi |= (uint32_t)(m >> 32) ^ spread;
-        }
-        const uint64_t peers = __ballot(ok) & ~((uint64_t)diff_hi << 32 | diff_lo);
-        const uint32_t below = __popcll(peers & lt);
-        const uint32_t old = ok ? sm.wcnt[w][dg] : 0u;
-        if (ok && below == 0) sm.wcnt[w][dg] = old + (uint32_t)__popcll(peers);
-        if (i % 2 == 0)
-            rank2[i / 2] = old + below;
-        else
-            rank2[i / 2] |= (old + below) << 16;
-    }
-    __syncthreads();
-
-    // per digit: exclusive prefix over waves, tile total, local digit starts
-    uint32_t tot[BPT];
-#pragma unroll
-    for (int k = 0; k < BPT; k++) {
-        const uint32_t d = threadIdx.x * BPT + k;
-        uint32_t run = 0;
-        if (d < (uint32_t)R::BUCKETS) {
-#pragma unroll
-            for (int i = 0; i < NW; i++) {
-                const uint32_t c = sm.wcnt[i][d];
-                sm.wcnt[i][d] = run;
-                run += c;
-            }
-            sm.local[d] = run;
-        }
-        tot[k] = run;
-    }
-    __syncthreads();
-    scan_buckets<RB>(sm.local, sm.local, sm.tmp);
-
-    // publish this tile's digit totals, then look back for the prefix
-    uint64_t* st = status + (uint64_t)tile * R::BUCKETS;
-#pragma unroll
-    for (int k = 0; k < BPT; k++) {
-        const uint32_t d = threadIdx.x * BPT + k;
-        if (d < (uint32_t)R::BUCKETS) st_store(st + d, st_pack(epoch, tile == first_tile ? ST_INC : ST_AGG, tot[k]));
-    }
-    if (tile > first_tile) {
-#pragma unroll
-        for (int k = 0; k < BPT; k++) {
-            const uint32_t d = threadIdx.x * BPT + k;
-            if (d < (uint32_t)R::BUCKETS) {
-                const uint64_t ex = lookback(status + d, tile, first_tile, R::BUCKETS, epoch);
-                st_store(st + d, st_pack(epoch, ST_INC, ex + tot[k]));
-                sm.goff[d] += (uint32_t)ex;
-            }
-        }
-    }
-    // local scatter into LDS in digit order
-#pragma unroll
-    for (int i = 0; i < KPT; i++) {
-        const uint32_t off = (w * KPT + i) * MQ_WAVE + ln;
-        if (off < valid_n) {
-            const uint32_t dg = (key[i] >> shift) & R::MASK;
-            const uint32_t pos = sm.local[dg] + sm.wcnt[w][dg] + ((rank2[i / 2] >> (16 * (i % 2))) & 0xffffu);
-            sm.keys[pos] = key[i];
-            sm.vals[pos] = val[i];
-        }
-    }
-    __syncthreads();
-    for (uint32_t j = threadIdx.x; j < valid_n; j += NT) {
-        const uint32_t k = sm.keys[j];
-        const uint32_t dg = (k >> shift) & R::MASK;
-        const uint32_t g = sm.goff[dg] + (j - sm.local[dg]);
-        if (MQ_IN_BOUNDS(g, n_out)) {
-            kout[g] = k;
-            vout[g] = sm.vals[j];
-        }
-    }
-}
 
 // d & ~(a ^ b): one three-input operation
 __device__ __forceinline__ uint32_t and_xnor(uint32_t d, uint32_t a, uint32_t b) {
@@ -191,11 +29,16 @@ __device__ __forceinline__ uint32_t bit_spread(uint32_t x, int b) {
     return r;
 }
 
-// The same pass with the tile's keys and payloads staged one after the other
-// in one buffer (half the LDS: two blocks share a CU and one's memory phases
-// overlap the other's ranking).  The payloads are loaded only once the keys
-// are in LDS (load_vals fills the array in key order), so a thread holds one
-// of the two at a time.  Records past valid_n are padding: keys of all ones.
+// One stable radix pass over one tile whose keys are already in registers
+// (wave-striped: element i of a lane is tile position (wave*KPT + i)*64 +
+// lane): ranks the digits, publishes the tile's digit counts, looks back over
+// the join's earlier tiles (from `first` on), and scatters the tile to
+// kout/vout (join-relative).
+// Keys and payloads are staged one after the other in one buffer (two blocks
+// share a CU and one's memory phases overlap the other's ranking).  The
+// payloads are loaded only once the keys are in LDS (load_vals fills the array
+// in key order), so a thread holds one of the two at a time.  Records past
+// valid_n are padding: keys of all ones.
 template <int RB, int KPT, int NW>
 struct SplitSmem {
     static constexpr int TILE = NW * MQ_WAVE * KPT;
@@ -219,8 +62,8 @@ __device__ __forceinline__ void opaque(uint32_t (&v)[N]) {
 template <int RB, int KPT, int NW, bool FULL, bool KEYS = true, class LoadVals, class ValsOut>
 __device__ __forceinline__ void sort_tile_split(SplitSmem<RB, KPT, NW>& sm, uint32_t (&key)[KPT], uint32_t valid_n,
                                                 int shift, const uint32_t* __restrict__ ghist,
-                                                uint64_t* __restrict__ status, uint32_t tile, uint32_t epoch,
-                                                uint32_t* __restrict__ kout, uint32_t n_out, int np,
+                                                uint64_t* __restrict__ status, uint32_t tile, uint32_t first,
+                                                uint32_t epoch, uint32_t* __restrict__ kout, uint32_t n_out, int np,
                                                 LoadVals load_vals, ValsOut vout) {
     using R = Radix<RB>;
     constexpr int NT = NW * MQ_WAVE;                 // threads of the block
@@ -294,7 +137,7 @@ __device__ __forceinline__ void sort_tile_split(SplitSmem<RB, KPT, NW>& sm, uint
                 run += c;
             }
             if (!FULL && d == pad_digit) run -= TILE - valid_n;
-            st_store(st + d, st_pack(epoch, tile == 0 ? ST_INC : ST_AGG, run));
+            st_store(st + d, st_pack(epoch, tile == first ? ST_INC : ST_AGG, run));
         }
         tot[k] = run;
         sum_t += run;
@@ -344,8 +187,8 @@ __device__ __forceinline__ void sort_tile_split(SplitSmem<RB, KPT, NW>& sm, uint
         const uint32_t d = threadIdx.x * BPT + k;
         if (d < (uint32_t)R::BUCKETS) {
             uint32_t ex = 0;
-            if (tile > 0) {
-                ex = (uint32_t)lookback(status + d, tile, 0, R::BUCKETS, epoch);
+            if (tile > first) {
+                ex = (uint32_t)lookback(status + d, tile, first, R::BUCKETS, epoch);
                 st_store(st + d, st_pack(epoch, ST_INC, ex + tot[k]));
             }
             sm.goff[d] = off[k] + ex;

@@ -60,6 +60,7 @@ __device__ __forceinline__ T wave_sum(T v) {
 }
 
 // lane - 1's value; lane 0 gets `first` (DPP: the wave shifted right by one)
+// every lane must be active: a lane whose neighbour is not gets `first` as well
 __device__ __forceinline__ uint32_t wave_prev(uint32_t v, uint32_t first) {
     return (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)v, 0x138, 0xf, 0xf, false);
 }

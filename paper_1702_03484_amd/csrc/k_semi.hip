@@ -45,7 +45,7 @@ __global__ __launch_bounds__(BS_THREADS) void bitmap_set_kernel(const int32_t* _
             if (fresh) fresh = atomicExch(mark, k) != k;  // of several lanes with k, one
             if (__ballot(fresh) == 0ull) continue;
             uint32_t bits = fresh ? 1u << (k & 31u) : 0u;
-            const bool follows = lane() > 0 && wave_prev(word, 0u) == word;
+            const bool follows = wave_prev(word, ~word) == word;
             if (__popcll(__ballot(follows)) >= MQ_WAVE / 2) {
                 // neighbours with one word: the run's bits meet in its first lane
 #pragma unroll

@@ -45,3 +45,21 @@ def test_rows(sess, n, kind):
         sess._keep.clear()
     for got, want in ((out[0], out[2]), (out[1], out[3])):
         assert got[0].numel() >= 1 and all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+@pytest.mark.parametrize("at", [1, 2, 63, 64, 65])
+def test_a_lone_key_among_neighbours(sess, at):
+    """a wave whose keys share one bitmap word but for one, in the lowest word"""
+    announce(f"semi filter lone key at {at}")
+    small = torch.full((128,), 5000, dtype=torch.int32, device="cuda")
+    small[at] = 0
+    big = torch.tensor([0, 5000, 4999, 1, 31, 0], dtype=torch.int32, device="cuda").repeat(100)
+    try:
+        sess.set_join_options(semijoin=2, merge=1, precount=1)
+        t = sess.join(sess.table([0], [big]), sess.table([0], [small]), 0)
+        assert sess.stats().path == B.MAPSQ_PATH_SEMIJOIN
+        assert t.nrows == 200 + 100 * 127
+        sess.free(t)
+    finally:
+        sess.set_join_options()
+        sess._keep.clear()

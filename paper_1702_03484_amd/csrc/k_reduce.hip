@@ -1014,21 +1014,34 @@ __global__ __launch_bounds__(MQ_BLOCK) void mat_seg_kernel(MatArgs a) {
 // One pass over the sorted records: every record's value columns move into
 // sorted order, so that materialisation reads contiguous ranges instead of
 // gathering each output row's values through its record id.
+constexpr int GV_UNROLL = 8;
+
 __global__ __launch_bounds__(MQ_BLOCK) void gather_values_kernel(GatherArgs g) {
-    const uint32_t stride = gridDim.x * MQ_BLOCK;
-    for (uint32_t i = blockIdx.x * MQ_BLOCK + threadIdx.x; i < g.n; i += stride) {
-        const uint32_t r = g.vals[i];
-        if (r < g.n_left) {
-            for (int c = 0; c < g.nl; c++) g.out[c][i] = g.lcol[c][r];
-        } else {
-            for (int c = 0; c < g.nr; c++) g.out[c][i] = g.rcol[c][r - g.n_left];
+    const int nv = g.nl > g.nr ? g.nl : g.nr;
+    const uint64_t i0 = (uint64_t)blockIdx.x * (MQ_BLOCK * GV_UNROLL) + threadIdx.x;
+    uint32_t r[GV_UNROLL];
+#pragma unroll
+    for (int u = 0; u < GV_UNROLL; u++) r[u] = g.vals[min(i0 + u * MQ_BLOCK, (uint64_t)g.n - 1)];
+    for (int c = 0; c < nv; c++) {
+        // a side without this column reads its last one instead, or nothing
+        const int32_t* lc = g.nl ? g.lcol[c < g.nl ? c : g.nl - 1] : nullptr;
+        const int32_t* rc = g.nr ? g.rcol[c < g.nr ? c : g.nr - 1] : nullptr;
+        int32_t x[GV_UNROLL];
+#pragma unroll
+        for (int u = 0; u < GV_UNROLL; u++) {
+            const bool left = r[u] < g.n_left;
+            const int32_t* col = left ? lc : rc;
+            x[u] = col ? col[left ? r[u] : r[u] - g.n_left] : 0;
         }
+#pragma unroll
+        for (int u = 0; u < GV_UNROLL; u++)
+            if (i0 + u * MQ_BLOCK < g.n) g.out[c][i0 + u * MQ_BLOCK] = x[u];
     }
 }
 
 hipError_t launch_gather_values(const GatherArgs& g, hipStream_t stream) {
     if (g.n == 0 || (g.nl == 0 && g.nr == 0)) return hipSuccess;
-    const uint32_t blocks = std::min((g.n + MQ_BLOCK * 4 - 1) / (MQ_BLOCK * 4), 8192u);
+    const uint32_t blocks = (g.n - 1) / (MQ_BLOCK * GV_UNROLL) + 1;
     gather_values_kernel<<<blocks, MQ_BLOCK, 0, stream>>>(g);
     return hipGetLastError();
 }

@@ -17,13 +17,24 @@ namespace mq {
 // the kernels of up to 128 VGPRs, 5 for those of up to 96, 8 for the
 // histogram's 48 (measured on the 512-join batch: 6% off the launch).
 constexpr uint32_t BATCH_BLOCKS = 1024;
-constexpr uint32_t BATCH_BLOCKS_5 = 1280;
 constexpr uint32_t BATCH_BLOCKS_8 = 2048;
 constexpr uint32_t BMAT_BLOCKS = 2048;
 constexpr int BMAT_RPT = 8;
 constexpr uint32_t BMAT_WROWS = MQ_WAVE * BMAT_RPT;
 
 uint32_t batch_chunk_rows() { return BMAT_WROWS; }
+
+// A tile of 256 x KPT records is worked on by KPT / 2 waves, 8 records per
+// thread (within 64 VGPRs): 16-wave blocks, two to a CU, for the default tiles.
+// A tile costs two atomics and a look-back whatever its size, so tiles are
+// large, and it is a chain of steps, so many waves share it.  16 joins of 8M
+// records: four radix passes 96 us, 155 in 4-wave blocks of 32 records per
+// thread with both halves of a record in LDS at once; heads, counts and
+// compaction 64 us, 141.
+constexpr int TILE_KPT = 8;
+constexpr int tile_waves(int kpt) { return kpt * (int)MQ_BLOCK / (int)MQ_WAVE / TILE_KPT; }
+// one resident round of blocks
+constexpr uint32_t tile_blocks(int kpt) { return 256u * 32u / (uint32_t)tile_waves(kpt); }
 
 // Relative key of record idx (< nl + nr) of a join: the column is selected
 // per lane before one load, and callers clamp idx into range instead of
@@ -74,6 +85,8 @@ __global__ void bclear_kernel(const BatchHdr* __restrict__ h) {
 
 // Filters of the joins that have one: every record of the build side sets
 // its key's bits (a word already holding them is left alone).
+constexpr int BFILT_UNROLL = 8;
+
 template <int KPT>
 __global__ __launch_bounds__(MQ_BLOCK) void bfilt_kernel(const BatchHdr* __restrict__ h) {
     constexpr uint32_t TILE = MQ_BLOCK * KPT;
@@ -85,12 +98,25 @@ __global__ __launch_bounds__(MQ_BLOCK) void bfilt_kernel(const BatchHdr* __restr
         const uint32_t b0 = J.probe_right ? 0u : J.nl;
         const uint32_t b1 = J.probe_right ? J.nl : J.nl + J.nr;
         const uint32_t i0 = max(base, b0), i1 = min(base + TILE, b1);
-        for (uint32_t i = i0 + threadIdx.x; i < i1; i += MQ_BLOCK) {
-            const uint64_t x = bloom_hash(bsrc_key(J, i));
-            const uint64_t m = bloom_bits(x);
-            unsigned long long* wp = reinterpret_cast<unsigned long long*>(J.filt + bloom_word(x, J.fmask));
-            if ((__hip_atomic_load(wp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & m) != m)
-                atomicOr(wp, (unsigned long long)m);
+        // BFILT_UNROLL keys of a thread at a time, their words looked at together
+        for (uint32_t i = i0; i < i1; i += MQ_BLOCK * BFILT_UNROLL) {
+            uint32_t k[BFILT_UNROLL];
+#pragma unroll
+            for (int u = 0; u < BFILT_UNROLL; u++) k[u] = bsrc_key(J, min(i + u * MQ_BLOCK + threadIdx.x, i1 - 1));
+            uint64_t m[BFILT_UNROLL], was[BFILT_UNROLL];
+            unsigned long long* wp[BFILT_UNROLL];
+#pragma unroll
+            for (int u = 0; u < BFILT_UNROLL; u++) {
+                const uint64_t x = bloom_hash(k[u]);
+                m[u] = bloom_bits(x);
+                wp[u] = reinterpret_cast<unsigned long long*>(J.filt + bloom_word(x, J.fmask));
+                // of neighbours with one key (a side in key order) the first asks
+                if (wave_prev(k[u], ~k[u]) == k[u]) m[u] = 0;
+                was[u] = m[u] ? __hip_atomic_load(wp[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+            }
+#pragma unroll
+            for (int u = 0; u < BFILT_UNROLL; u++)
+                if ((was[u] & m[u]) != m[u]) atomicOr(wp[u], (unsigned long long)m[u]);
         }
     }
 }
@@ -105,9 +131,10 @@ __global__ __launch_bounds__(MQ_BLOCK) void bfilt_kernel(const BatchHdr* __restr
 // straight from sparse tiles, each tile would put only a few records in
 // each digit bucket and the pass's writes would break into partial lines.)
 template <int KPT>
-__global__ __launch_bounds__(MQ_BLOCK) void bcompact_kernel(const BatchHdr* __restrict__ h) {
+__global__ __launch_bounds__(tile_waves(KPT) * MQ_WAVE, 8) void bcompact_kernel(const BatchHdr* __restrict__ h) {
     constexpr uint32_t TILE = MQ_BLOCK * KPT;
-    __shared__ uint32_t s_wtot[MQ_WAVES];
+    constexpr int NW = tile_waves(KPT), IPT = TILE_KPT;
+    __shared__ uint32_t s_wtot[NW];
     __shared__ uint64_t s_excl;
     __shared__ uint32_t s_tile;
     const uint32_t T = h->total_tiles, passes = h->passes;
@@ -121,14 +148,14 @@ __global__ __launch_bounds__(MQ_BLOCK) void bcompact_kernel(const BatchHdr* __re
         if (!J.filt) continue;  // block-uniform
         const uint32_t n = J.nl + J.nr;
         const uint32_t base = (t - J.tile_off) * TILE;
-        uint32_t k[KPT];
+        uint32_t k[IPT];
 #pragma unroll
-        for (int i = 0; i < KPT; i++) k[i] = bsrc_key(J, min(base + (w * KPT + i) * MQ_WAVE + lane(), n - 1));
-        uint64_t km[KPT];
+        for (int i = 0; i < IPT; i++) k[i] = bsrc_key(J, min(base + (w * IPT + i) * MQ_WAVE + lane(), n - 1));
+        uint64_t km[IPT];
         uint32_t run = 0;
 #pragma unroll
-        for (int i = 0; i < KPT; i++) {
-            const uint32_t idx = base + (w * KPT + i) * MQ_WAVE + lane();
+        for (int i = 0; i < IPT; i++) {
+            const uint32_t idx = base + (w * IPT + i) * MQ_WAVE + lane();
             km[i] = __ballot(idx < n && bkeep(J, idx, k[i]));
             run += (uint32_t)__popcll(km[i]);
         }
@@ -136,7 +163,7 @@ __global__ __launch_bounds__(MQ_BLOCK) void bcompact_kernel(const BatchHdr* __re
         __syncthreads();
         uint32_t wex = 0, ttot = 0;
 #pragma unroll
-        for (int i = 0; i < MQ_WAVES; i++) {
+        for (int i = 0; i < NW; i++) {
             if ((uint32_t)i < w) wex += s_wtot[i];
             ttot += s_wtot[i];
         }
@@ -152,12 +179,12 @@ __global__ __launch_bounds__(MQ_BLOCK) void bcompact_kernel(const BatchHdr* __re
         uint32_t* ko = h->keys[1] + J.rec_off;
         uint32_t* vo = h->vals[1] + J.rec_off;
 #pragma unroll
-        for (int i = 0; i < KPT; i++) {
+        for (int i = 0; i < IPT; i++) {
             if ((km[i] >> lane()) & 1ull) {
                 const uint32_t at = pos + (uint32_t)__popcll(km[i] & lt);
                 if (MQ_IN_BOUNDS(at, n)) {
                     ko[at] = k[i];
-                    vo[at] = base + (w * KPT + i) * MQ_WAVE + lane();
+                    vo[at] = base + (w * IPT + i) * MQ_WAVE + lane();
                 }
             }
             pos += (uint32_t)__popcll(km[i]);
@@ -221,17 +248,8 @@ __global__ __launch_bounds__(MQ_BLOCK) void bhist_kernel(const BatchHdr* __restr
         }
 }
 
-// A tile of 256 x KPT records is sorted by KPT / 2 waves, 8 keys per thread
-// (64 VGPRs, no spills): 16-wave blocks, two to a CU, for the default tiles.
-// 16 joins of 8M records, four passes: 96 us, 155 in 4-wave blocks of 32
-// keys per thread with both halves of a record in LDS at once.
-constexpr int BPASS_KPT = 8;
-constexpr int bpass_waves(int kpt) { return kpt * (int)MQ_BLOCK / (int)MQ_WAVE / BPASS_KPT; }
-// one resident round of blocks
-constexpr uint32_t bpass_blocks(int kpt) { return 256u * 32u / (uint32_t)bpass_waves(kpt); }
-
 template <int RB, int NW, bool GEN, bool FULL>
-__device__ __forceinline__ void bpass_tile(SplitSmem<RB, BPASS_KPT, NW>& sm, const BatchHdr* __restrict__ h,
+__device__ __forceinline__ void bpass_tile(SplitSmem<RB, TILE_KPT, NW>& sm, const BatchHdr* __restrict__ h,
                                            const BatchJoin& J, const uint32_t* __restrict__ hist, uint32_t base,
                                            uint32_t valid_n, int pass, uint32_t t, uint32_t epoch) {
     // the first pass of an unfiltered join reads its records from the tables;
@@ -239,39 +257,39 @@ __device__ __forceinline__ void bpass_tile(SplitSmem<RB, BPASS_KPT, NW>& sm, con
     // records of the previous one (the compacted kept records)
     const bool gen = GEN && !J.filt;
     const int src = (pass - 1) & 1, dst = pass & 1;  // the first pass writes buffer 0
-    const uint32_t o0 = threadIdx.x / MQ_WAVE * BPASS_KPT * MQ_WAVE + lane();
+    const uint32_t o0 = threadIdx.x / MQ_WAVE * TILE_KPT * MQ_WAVE + lane();
     auto at = [&](int i) { return FULL ? o0 + i * MQ_WAVE : min(o0 + i * MQ_WAVE, valid_n - 1); };
-    uint32_t key[BPASS_KPT];
+    uint32_t key[TILE_KPT];
     if (gen) {
 #pragma unroll
-        for (int i = 0; i < BPASS_KPT; i++) key[i] = bsrc_key(J, base + at(i));
+        for (int i = 0; i < TILE_KPT; i++) key[i] = bsrc_key(J, base + at(i));
     } else {
         const uint32_t* kin = h->keys[src] + J.rec_off + base;
 #pragma unroll
-        for (int i = 0; i < BPASS_KPT; i++) key[i] = kin[at(i)];
+        for (int i = 0; i < TILE_KPT; i++) key[i] = kin[at(i)];
     }
     if (!FULL) {
 #pragma unroll
-        for (int i = 0; i < BPASS_KPT; i++)
+        for (int i = 0; i < TILE_KPT; i++)
             if (o0 + i * MQ_WAVE >= valid_n) key[i] = 0xffffffffu;
     }
     const uint32_t* vin = h->vals[src] + J.rec_off + base;
     uint32_t* vout = h->vals[dst] + J.rec_off;
-    sort_tile_split<RB, BPASS_KPT, NW, FULL>(
+    sort_tile_split<RB, TILE_KPT, NW, FULL>(
         sm, key, valid_n, pass * RB, hist, h->status, t, J.tile_off, epoch, h->keys[dst] + J.rec_off, J.nrec, 1,
-        [&](int, uint32_t(&val)[BPASS_KPT]) {
+        [&](int, uint32_t(&val)[TILE_KPT]) {
 #pragma unroll
-            for (int i = 0; i < BPASS_KPT; i++) val[i] = gen ? base + at(i) : vin[at(i)];
+            for (int i = 0; i < TILE_KPT; i++) val[i] = gen ? base + at(i) : vin[at(i)];
         },
         [&](int) { return vout; });
 }
 
 template <int RB, int KPT, bool GEN>
-__global__ __launch_bounds__(bpass_waves(KPT) * MQ_WAVE, 8) void bpass_kernel(const BatchHdr* __restrict__ h, int pass) {
-    constexpr int NW = bpass_waves(KPT);
+__global__ __launch_bounds__(tile_waves(KPT) * MQ_WAVE, 8) void bpass_kernel(const BatchHdr* __restrict__ h, int pass) {
+    constexpr int NW = tile_waves(KPT);
     constexpr uint32_t TILE = MQ_BLOCK * KPT;
-    static_assert(TILE == NW * MQ_WAVE * BPASS_KPT, "the waves cover the tile");
-    __shared__ SplitSmem<RB, BPASS_KPT, NW> sm;
+    static_assert(TILE == NW * MQ_WAVE * TILE_KPT, "the waves cover the tile");
+    __shared__ SplitSmem<RB, TILE_KPT, NW> sm;
     __shared__ uint32_t s_tile;
     const uint32_t T = h->total_tiles, passes = h->passes;
     const uint32_t epoch = h->epoch0 + pass;
@@ -293,9 +311,10 @@ __global__ __launch_bounds__(bpass_waves(KPT) * MQ_WAVE, 8) void bpass_kernel(co
 }
 
 template <int KPT>
-__global__ __launch_bounds__(MQ_BLOCK) void bheads_kernel(BatchHdr* __restrict__ h) {
+__global__ __launch_bounds__(tile_waves(KPT) * MQ_WAVE, 8) void bheads_kernel(BatchHdr* __restrict__ h) {
     constexpr uint32_t TILE = MQ_BLOCK * KPT;
-    __shared__ HeadsSmem sm;
+    constexpr int NW = tile_waves(KPT);
+    __shared__ HeadsSmem<NW> sm;
     __shared__ uint32_t s_tile;
     const uint32_t T = h->total_tiles, passes = h->passes;
     const int fin = (passes - 1) & 1;
@@ -308,16 +327,18 @@ __global__ __launch_bounds__(MQ_BLOCK) void bheads_kernel(BatchHdr* __restrict__
         const uint32_t lt = t - J.tile_off;
         const uint32_t n = J.nrec;
         if (lt * TILE >= n) continue;  // beyond the kept records (block-uniform)
-        heads_tile<KPT>(sm, h->keys[fin] + J.rec_off, h->vals[fin] + J.rec_off, n, J.nl, lt * TILE, t, J.tile_off,
+        heads_tile<TILE_KPT, NW>(sm, h->keys[fin] + J.rec_off, h->vals[fin] + J.rec_off, n, J.nl, lt * TILE, t, J.tile_off,
                         (lt + 1) * TILE >= n, h->keys[1 - fin] + J.rec_off, h->vals[1 - fin] + J.rec_off, &J.nseg,
                         h->status, epoch);
     }
 }
 
+// the products of a thread's 8 segments take up to 128 VGPRs
 template <int KPT>
-__global__ __launch_bounds__(MQ_BLOCK) void bcount_kernel(BatchHdr* __restrict__ h) {
+__global__ __launch_bounds__(tile_waves(KPT) * MQ_WAVE, 4) void bcount_kernel(BatchHdr* __restrict__ h) {
     constexpr uint32_t TILE = MQ_BLOCK * KPT;
-    __shared__ CountSmem sm;
+    constexpr int NW = tile_waves(KPT);
+    __shared__ CountSmem<NW> sm;
     __shared__ uint32_t s_tile;
     const uint32_t T = h->total_tiles, passes = h->passes;
     const int fin = (passes - 1) & 1;
@@ -331,7 +352,7 @@ __global__ __launch_bounds__(MQ_BLOCK) void bcount_kernel(BatchHdr* __restrict__
         const uint32_t ns = J.nseg;
         if (lt * TILE >= ns) continue;  // beyond the join's segments (block-uniform)
         const uint32_t last = (ns + TILE - 1) / TILE - 1;
-        count_tile<KPT>(sm, J.nrec, ns, lt * TILE, t, J.tile_off, lt == last, h->keys[1 - fin] + J.rec_off,
+        count_tile<TILE_KPT, NW>(sm, J.nrec, ns, lt * TILE, t, J.tile_off, lt == last, h->keys[1 - fin] + J.rec_off,
                         h->vals[1 - fin] + J.rec_off, h->seg_off + J.rec_off, &J.total, h->status, epoch,
                         &J.max_pairs);
     }
@@ -413,6 +434,8 @@ __device__ __forceinline__ bool bjoin_uses_sval(const BatchHdr* h, const BatchJo
     return J.status == 0 && nv > 0 && nv <= h->nsval && J.total >= (uint64_t)J.nrec;
 }
 
+constexpr int GATHER_UNROLL = 8;
+
 template <int KPT>
 __global__ __launch_bounds__(MQ_BLOCK) void bgather_kernel(const BatchHdr* __restrict__ h) {
     constexpr uint32_t TILE = MQ_BLOCK * KPT;
@@ -431,13 +454,30 @@ __global__ __launch_bounds__(MQ_BLOCK) void bgather_kernel(const BatchHdr* __res
         if (i0 >= n) continue;
         const uint32_t i1 = min(i0 + UNIT, n);
         const uint32_t* vals = h->vals[fin] + J.rec_off;
-        for (uint32_t i = i0 + threadIdx.x; i < i1; i += MQ_BLOCK) {
-            const uint32_t r = vals[i];
-            if (!MQ_IN_BOUNDS(r, J.nl + J.nr)) continue;
-            if (r < J.nl) {
-                for (int c = 0; c < J.nvl; c++) h->sval[c][J.rec_off + i] = J.lcol[c][r];
-            } else {
-                for (int c = 0; c < J.nvr; c++) h->sval[c][J.rec_off + i] = J.rcol[c][r - J.nl];
+        // GATHER_UNROLL records of a thread at a time: their cells are cache
+        // lines of their own, fetched side by side
+        for (uint32_t i = i0 + threadIdx.x; i < i1; i += MQ_BLOCK * GATHER_UNROLL) {
+            uint32_t r[GATHER_UNROLL];
+#pragma unroll
+            for (int g = 0; g < GATHER_UNROLL; g++) {
+                r[g] = vals[min(i + g * MQ_BLOCK, i1 - 1)];
+                if (!MQ_IN_BOUNDS(r[g], J.nl + J.nr)) r[g] = 0;
+            }
+            const int nv = max(J.nvl, J.nvr);
+            for (int c = 0; c < nv; c++) {
+                int32_t x[GATHER_UNROLL];
+#pragma unroll
+                for (int g = 0; g < GATHER_UNROLL; g++) {
+                    const bool left = r[g] < J.nl;
+                    // a side without this column reads its key column instead
+                    const int32_t* col = left ? (c < J.nvl ? J.lcol[c] : J.lkey) : (c < J.nvr ? J.rcol[c] : J.rkey);
+                    x[g] = col[left ? r[g] : r[g] - J.nl];
+                }
+#pragma unroll
+                for (int g = 0; g < GATHER_UNROLL; g++) {
+                    const uint32_t at = i + g * MQ_BLOCK;
+                    if (at < i1) h->sval[c][J.rec_off + at] = x[g];
+                }
             }
         }
     }
@@ -499,15 +539,15 @@ static hipError_t launch_batch_t(const BatchHdr* hdr, int passes, hipStream_t st
     BatchHdr* h = const_cast<BatchHdr*>(hdr);
     bclear_kernel<RB><<<256, MQ_BLOCK, 0, stream>>>(hdr);
     bfilt_kernel<KPT><<<BATCH_BLOCKS, MQ_BLOCK, 0, stream>>>(hdr);
-    bcompact_kernel<KPT><<<BATCH_BLOCKS_5, MQ_BLOCK, 0, stream>>>(hdr);
+    constexpr uint32_t blocks = tile_blocks(KPT), threads = tile_waves(KPT) * MQ_WAVE;
+    bcompact_kernel<KPT><<<blocks, threads, 0, stream>>>(hdr);
     bhist_kernel<RB, KPT><<<BATCH_BLOCKS_8, MQ_BLOCK, 0, stream>>>(hdr);
     for (int p = 0; p < passes; p++) {
-        constexpr uint32_t threads = bpass_waves(KPT) * MQ_WAVE;
-        if (p == 0) bpass_kernel<RB, KPT, true><<<bpass_blocks(KPT), threads, 0, stream>>>(hdr, p);
-        else bpass_kernel<RB, KPT, false><<<bpass_blocks(KPT), threads, 0, stream>>>(hdr, p);
+        if (p == 0) bpass_kernel<RB, KPT, true><<<blocks, threads, 0, stream>>>(hdr, p);
+        else bpass_kernel<RB, KPT, false><<<blocks, threads, 0, stream>>>(hdr, p);
     }
-    bheads_kernel<KPT><<<BATCH_BLOCKS_5, MQ_BLOCK, 0, stream>>>(h);
-    bcount_kernel<KPT><<<BATCH_BLOCKS, MQ_BLOCK, 0, stream>>>(h);
+    bheads_kernel<KPT><<<blocks, threads, 0, stream>>>(h);
+    bcount_kernel<KPT><<<blocks, threads, 0, stream>>>(h);
     bplace_kernel<<<1, MQ_BLOCK, 0, stream>>>(h);
     bgather_kernel<KPT><<<BATCH_BLOCKS, MQ_BLOCK, 0, stream>>>(hdr);
     bmat_kernel<<<BMAT_BLOCKS, MQ_BLOCK, 0, stream>>>(hdr);

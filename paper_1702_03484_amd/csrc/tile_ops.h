@@ -230,16 +230,17 @@ __device__ __forceinline__ void sort_tile_split(SplitSmem<RB, KPT, NW>& sm, uint
 // RIGHT record (split = its position), or, in a segment without RIGHT
 // records, the last record (split = its position + 1).
 
+template <int NW>
 struct HeadsSmem {
-    uint32_t wtot[MQ_WAVES];
+    uint32_t wtot[NW];
     uint64_t excl;
 };
 
-// One tile of IPT*256 records at join-relative positions base..; returns
+// One tile of NW*64*IPT records at join-relative positions base..; returns
 // (in every thread) nothing; the tile's last-segment count goes to *nseg
 // when `last_tile`.
-template <int IPT>
-__device__ __forceinline__ void heads_tile(HeadsSmem& sm, const uint32_t* __restrict__ keys,
+template <int IPT, int NW>
+__device__ __forceinline__ void heads_tile(HeadsSmem<NW>& sm, const uint32_t* __restrict__ keys,
                                            const uint32_t* __restrict__ vals, uint32_t n, uint32_t n_left,
                                            uint32_t base, uint32_t tile, uint32_t first_tile, bool last_tile,
                                            uint32_t* __restrict__ seg_start, uint32_t* __restrict__ seg_split,
@@ -247,30 +248,55 @@ __device__ __forceinline__ void heads_tile(HeadsSmem& sm, const uint32_t* __rest
                                            uint32_t epoch) {
     const uint32_t w = threadIdx.x / MQ_WAVE;
     const uint64_t lt = lanemask_lt();
+    // every key and payload is read once, all loads clamped into range and in
+    // flight together; neighbours come from the next lane or the next item
+    const uint32_t w0 = base + w * IPT * MQ_WAVE;
+    const uint32_t kbefore = keys[w0 > 0 ? min(w0, n) - 1 : 0u];
+    const uint32_t vbefore = vals[w0 > 0 ? min(w0, n) - 1 : 0u];
+    const uint32_t kafter = keys[min(w0 + IPT * MQ_WAVE, n - 1)];
     uint64_t hm[IPT];
+    uint32_t rbits = 0, run = 0, klast = kbefore;
+    constexpr int PART = IPT < 16 ? IPT : 16;
+#pragma unroll
+    for (int p = 0; p < IPT; p += PART) {
+        uint32_t k[PART], v[PART];
+#pragma unroll
+        for (int i = 0; i < PART; i++) {
+            const uint32_t idx = min(w0 + (p + i) * MQ_WAVE + lane(), n - 1);
+            k[i] = keys[idx];
+            v[i] = vals[idx];
+        }
+#pragma unroll
+        for (int i = 0; i < PART; i++) {
+            const uint32_t idx = w0 + (p + i) * MQ_WAVE + lane();
+            const uint32_t prev = wave_prev(k[i], klast);
+            hm[p + i] = __ballot(idx < n && (idx == 0 || prev != k[i]));
+            klast = (uint32_t)__builtin_amdgcn_readlane((int)k[i], MQ_WAVE - 1);
+            run += (uint32_t)__popcll(hm[p + i]);
+            rbits |= (idx < n && v[i] >= n_left ? 1u : 0u) << (p + i);
+        }
+    }
+    // klast: the wave's last record (n - 1's past the end)
+    const bool next_head = w0 + IPT * MQ_WAVE >= n || kafter != klast;
     uint32_t wbits = 0, sbits = 0;  // per item: writes a split; is a first RIGHT record
-    uint32_t run = 0;
+    uint64_t rprev = vbefore >= n_left ? 1ull << 63 : 0ull;
 #pragma unroll
     for (int i = 0; i < IPT; i++) {
-        const uint32_t idx = base + (w * IPT + i) * MQ_WAVE + lane();
-        bool h = false;
-        if (idx < n) {
-            const uint32_t k = keys[idx];
-            const bool is_r = vals[idx] >= n_left;
-            h = idx == 0 || keys[idx - 1] != k;
-            const bool last = idx + 1 == n || keys[idx + 1] != k;
-            const bool first_r = is_r && (h || vals[idx - 1] < n_left);
-            if (first_r || (last && !is_r)) wbits |= 1u << i;
-            if (first_r) sbits |= 1u << i;
-        }
-        hm[i] = __ballot(h);
-        run += (uint32_t)__popcll(hm[i]);
+        const uint32_t idx = w0 + i * MQ_WAVE + lane();
+        const bool is_r = (rbits >> i) & 1u, h = (hm[i] >> lane()) & 1ull;
+        const uint64_t r = __ballot(is_r);
+        const uint64_t after = hm[i] >> 1 | (uint64_t)(i + 1 < IPT ? hm[i + 1] & 1ull : (next_head ? 1ull : 0ull)) << 63;
+        const bool last = idx + 1 == n || ((after >> lane()) & 1ull);
+        const bool first_r = is_r && (h || !(((r << 1 | rprev >> 63) >> lane()) & 1ull));
+        rprev = r;
+        if (first_r || (idx < n && last && !is_r)) wbits |= 1u << i;
+        if (first_r) sbits |= 1u << i;
     }
     if (lane() == 0) sm.wtot[w] = run;
     __syncthreads();
     uint32_t wex = 0, ttot = 0;
 #pragma unroll
-    for (int i = 0; i < MQ_WAVES; i++) {
+    for (int i = 0; i < NW; i++) {
         if ((uint32_t)i < w) wex += sm.wtot[i];
         ttot += sm.wtot[i];
     }
@@ -299,37 +325,48 @@ __device__ __forceinline__ void heads_tile(HeadsSmem& sm, const uint32_t* __rest
 
 // ------------------------------------------------------ count and scan ---
 
+template <int NW>
 struct CountSmem {
-    uint64_t tmp[MQ_WAVES];
-    uint64_t mx[MQ_WAVES];
+    uint64_t tmp[NW];
+    uint64_t mx[NW];
     uint64_t excl;
 };
 
-// Segments base + t*IPT ... (blocked) of one join: count cL*cR, scan into
-// exact offsets (saturating at 2^40-1); the join's last tile writes *total.
-template <int IPT>
-__device__ __forceinline__ void count_tile(CountSmem& sm, uint32_t n, uint32_t ns, uint32_t base, uint32_t tile,
+// Segments from base on of one join, wave-striped (item i of a lane is
+// (wave*IPT + i)*64 + lane, so every load and store is a whole line): count
+// cL*cR, scan into exact offsets (saturating at 2^40-1); the join's last tile
+// writes *total.
+template <int IPT, int NW>
+__device__ __forceinline__ void count_tile(CountSmem<NW>& sm, uint32_t n, uint32_t ns, uint32_t base, uint32_t tile,
                                            uint32_t first_tile, bool last_tile,
                                            const uint32_t* __restrict__ seg_start,
                                            const uint32_t* __restrict__ seg_split, uint64_t* __restrict__ seg_off,
                                            uint64_t* __restrict__ total, uint64_t* __restrict__ status,
                                            uint32_t epoch, uint64_t* __restrict__ max_pairs) {
-    const uint32_t first = base + threadIdx.x * IPT;
+    const uint32_t w = threadIdx.x / MQ_WAVE;
+    const uint32_t first = base + w * IPT * MQ_WAVE + lane();
     uint64_t cnt[IPT];
     uint64_t sum = 0, mx = 0;
+    constexpr int PART = IPT < 8 ? IPT : 8;
 #pragma unroll
-    for (int i = 0; i < IPT; i++) {
-        const uint32_t s = first + i;
-        cnt[i] = 0;
-        if (s < ns) {
-            const uint32_t st = seg_start[s];
-            const uint32_t en = s + 1 < ns ? seg_start[s + 1] : n;
-            const uint32_t sp = seg_split[s];
-            const uint64_t c = (uint64_t)(sp - st) * (uint64_t)(en - sp);
-            cnt[i] = c > SAT40 ? SAT40 : c;
+    for (int p = 0; p < IPT; p += PART) {
+        uint32_t st[PART], en[PART], sp[PART];
+#pragma unroll
+        for (int i = 0; i < PART; i++) {
+            const uint32_t s = min(first + (p + i) * MQ_WAVE, ns - 1);
+            st[i] = seg_start[s];
+            en[i] = seg_start[min(s + 1, ns - 1)];
+            sp[i] = seg_split[s];
         }
-        sum += cnt[i];
-        mx = cnt[i] > mx ? cnt[i] : mx;
+#pragma unroll
+        for (int i = 0; i < PART; i++) {
+            const uint32_t s = first + (p + i) * MQ_WAVE;
+            const uint32_t end = s + 1 < ns ? en[i] : n;
+            const uint64_t c = s < ns ? (uint64_t)(sp[i] - st[i]) * (uint64_t)(end - sp[i]) : 0ull;
+            cnt[p + i] = c > SAT40 ? SAT40 : c;
+            sum += cnt[p + i];
+            mx = cnt[p + i] > mx ? cnt[p + i] : mx;
+        }
     }
     // the tile's largest count raises the join's maximum (one atomic per tile)
 #pragma unroll
@@ -337,10 +374,19 @@ __device__ __forceinline__ void count_tile(CountSmem& sm, uint32_t n, uint32_t n
         const uint64_t y = __shfl_xor(mx, o);
         mx = y > mx ? y : mx;
     }
-    if (lane() == 0) sm.mx[threadIdx.x / MQ_WAVE] = mx;
-    uint64_t ttot;
-    const uint64_t ex_in = block_excl_scan<uint64_t>(sum, sm.tmp, &ttot);
-    if (threadIdx.x < MQ_WAVE) {
+    sum = wave_sum(sum);
+    if (lane() == 0) {
+        sm.mx[w] = mx;
+        sm.tmp[w] = sum;
+    }
+    __syncthreads();
+    uint64_t before = 0, ttot = 0;
+#pragma unroll
+    for (int i = 0; i < NW; i++) {
+        if ((uint32_t)i < w) before += sm.tmp[i];
+        ttot += sm.tmp[i];
+    }
+    if (w == 0) {
         const uint64_t ex = tile_prefix_wave(status, tile, first_tile, epoch, ttot);
         if (lane() == 0) {
             sm.excl = ex;
@@ -351,15 +397,19 @@ __device__ __forceinline__ void count_tile(CountSmem& sm, uint32_t n, uint32_t n
     if (threadIdx.x == 0 && max_pairs) {
         uint64_t m = 0;
 #pragma unroll
-        for (int w = 0; w < MQ_WAVES; w++) m = sm.mx[w] > m ? sm.mx[w] : m;
+        for (int i = 0; i < NW; i++) m = sm.mx[i] > m ? sm.mx[i] : m;
         atomicMax(reinterpret_cast<unsigned long long*>(max_pairs), (unsigned long long)m);
     }
-    uint64_t off = sm.excl + ex_in;
+    uint64_t off = sm.excl + before;
+    // products below 2^20 scan as 32-bit words (64 of them stay below 2^26)
+    const bool small = __ballot(mx >= 1ull << 20) == 0ull;
 #pragma unroll
     for (int i = 0; i < IPT; i++) {
-        const uint32_t s = first + i;
-        if (s < ns) seg_off[s] = off > SAT40 ? SAT40 : off;
-        off += cnt[i];
+        const uint32_t s = first + i * MQ_WAVE;
+        const uint64_t inc = small ? (uint64_t)wave_incl_u32((uint32_t)cnt[i]) : wave_incl_scan(cnt[i]);
+        const uint64_t at = off + inc - cnt[i];
+        if (s < ns) seg_off[s] = at > SAT40 ? SAT40 : at;
+        off += __shfl(inc, MQ_WAVE - 1, MQ_WAVE);
     }
 }
 

@@ -21,7 +21,7 @@ LIB = os.path.join(HERE, "libmapsq.so")
 BUILD_DEBUG = os.path.join(HERE, "_build_debug")
 LIB_DEBUG = os.path.join(HERE, "libmapsq_debug.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-SOURCES = ["k_sort.hip", "k_index.hip", "k_few.hip", "k_reduce.hip", "k_map.hip", "k_util.hip", "k_batch.hip", "k_semi.hip", "k_merge.hip", "noalloc.hip", "k_dict.hip", "dict.cpp", "runtime.cpp", "arena.cpp", "planner.cpp",
+SOURCES = ["k_sort.hip", "k_index.hip", "k_few.hip", "k_small.hip", "k_reduce.hip", "k_map.hip", "k_util.hip", "k_batch.hip", "k_semi.hip", "k_merge.hip", "noalloc.hip", "k_dict.hip", "dict.cpp", "runtime.cpp", "arena.cpp", "planner.cpp",
            "batch.cpp", "serve.cpp", "capi.cpp"]
 FLAGS = [
     "-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",

@@ -97,6 +97,32 @@ hipError_t launch_key_sample(const int32_t* a, uint32_t na, const int32_t* b, ui
 hipError_t launch_side_records(const int32_t* keys, uint32_t n, int32_t base, uint32_t id_base,
                                const uint32_t* at_dev, uint32_t* kout, uint32_t* vout, hipStream_t stream);
 
+// Sort and segments of a small join in one launch (k_small.hip): the records
+// of `src` (kin null) or at kin/vin, sorted on the key_bits bits from lo_bit on
+// into kout/vout (may be kin/vin), segments and *nseg as launch_seg_write writes
+// them, mail as launch_seg_sum's.
+constexpr uint32_t SMALL_JOIN = 4096;
+struct SmallJoin {
+    SortSrc src;
+    const uint32_t* kin;
+    const uint32_t* vin;
+    uint32_t n, n_left;
+    int32_t lo_bit, key_bits, side_bit;
+    int32_t width;  // digit width, set by the launch
+    uint32_t* kout;
+    uint32_t* vout;
+    uint32_t* seg_start;
+    uint32_t* seg_split;
+    uint64_t* seg_off;
+    uint32_t* nseg;
+};
+// digits of at most 8 bits, spread evenly
+inline int small_join_width(int key_bits) {
+    const int passes = key_bits > 8 ? (key_bits + 7) / 8 : 1;
+    return key_bits > 0 ? (key_bits + passes - 1) / passes : 1;
+}
+hipError_t launch_small_join(SmallJoin a, Mail mail, hipStream_t stream);
+
 // Counting shuffle of a join with few distinct keys (k_few.hip).  Every word
 // of a bitmap of range bits becomes an entry (bits, bits set in the words
 // before); the first FEW_KEYS set bits' positions go to keys (base added) and

@@ -42,36 +42,60 @@ __device__ __forceinline__ uint32_t src_key_of(const SortSrc& s, int32_t raw, ui
 // No device-wide atomics: they serialise on the few hundred counters.
 constexpr int HIST_IPT = 16;
 constexpr uint32_t HIST_BLOCKS = 512;
+// from here on blocks of 1,024 threads, two to a CU: 32M keys of two columns
+// 34 us, with 256 46, and 67 with a key a load; fewer keys need the blocks
+constexpr uint32_t HIST_BIG = 1u << 22;
 
-template <int RB, bool GEN>
-__global__ __launch_bounds__(MQ_BLOCK) void radix_hist_kernel(SortSrc src, const uint32_t* __restrict__ keys,
+template <int RB, bool GEN, uint32_t NT>
+__global__ __launch_bounds__(NT) void radix_hist_kernel(SortSrc src, const uint32_t* __restrict__ keys,
                                                               uint32_t n, int shift0, int passes,
                                                               uint32_t* __restrict__ part) {
     using R = Radix<RB>;
     __shared__ uint32_t sh[R::MAXP * R::BUCKETS];
-    for (int i = threadIdx.x; i < R::MAXP * R::BUCKETS; i += MQ_BLOCK) sh[i] = 0;
+    for (int i = threadIdx.x; i < R::MAXP * R::BUCKETS; i += NT) sh[i] = 0;
     __syncthreads();
-    constexpr uint32_t TILE = MQ_BLOCK * HIST_IPT;
+    constexpr uint32_t TILE = NT * HIST_IPT;
     const uint32_t ntiles = (n + TILE - 1) / TILE;
     for (uint32_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        // each thread takes HIST_IPT consecutive keys: runs of one digit
-        // (index-ordered keys have long ones) cost one LDS atomic per run
-        // instead of one per key
-        const uint32_t first = t * TILE + threadIdx.x * HIST_IPT;
+        // a whole tile of one side on a 16-byte boundary: four keys a load,
+        // neighbouring lanes on neighbouring addresses; else a thread's 16
+        // consecutive keys one by one (4 bytes of every line per load).  Runs of
+        // one digit (index-ordered keys have long ones) cost one LDS atomic.
+        const uint32_t base = t * TILE;
+        const bool right = GEN && base >= src.n0;
+        const uint32_t* from = GEN ? reinterpret_cast<const uint32_t*>(right ? src.k1 + (base - src.n0) : src.k0 + base)
+                                   : keys + base;
+        const bool vec = base + TILE <= (GEN && !right ? min(n, src.n0) : n) &&
+                         reinterpret_cast<uintptr_t>(from) % 16 == 0;
         uint32_t k[HIST_IPT];
+        if (vec) {
+            const uint4* f4 = reinterpret_cast<const uint4*>(from);
 #pragma unroll
-        for (int i = 0; i < HIST_IPT; i++) {
-            const uint32_t idx = first + i;
-            if (GEN)
-                k[i] = (uint32_t)src_load(src.k0, src.k1, src.n0, min(idx, n - 1));
-            else
-                k[i] = idx < n ? keys[idx] : 0u;
-        }
-        if (GEN) {
+            for (int i = 0; i < HIST_IPT; i += 4) {
+                const uint4 q = f4[i / 4 * NT + threadIdx.x];
+                k[i] = q.x;
+                k[i + 1] = q.y;
+                k[i + 2] = q.z;
+                k[i + 3] = q.w;
+            }
+            if (GEN) {
 #pragma unroll
-            for (int i = 0; i < HIST_IPT; i++) k[i] = src_key_of(src, (int32_t)k[i], first + i);
+                for (int i = 0; i < HIST_IPT; i++) k[i] = src_key_of(src, (int32_t)k[i], base);  // one side
+            }
         }
-        const int cnt = first >= n ? 0 : (int)min((uint32_t)HIST_IPT, n - first);
+        const uint32_t first = base + threadIdx.x * HIST_IPT;
+        if (!vec) {
+#pragma unroll
+            for (int i = 0; i < HIST_IPT; i++) {
+                const uint32_t idx = min(first + i, n - 1);
+                k[i] = GEN ? (uint32_t)src_load(src.k0, src.k1, src.n0, idx) : keys[idx];
+            }
+            if (GEN) {
+#pragma unroll
+                for (int i = 0; i < HIST_IPT; i++) k[i] = src_key_of(src, (int32_t)k[i], first + i);
+            }
+        }
+        const int cnt = vec ? HIST_IPT : first >= n ? 0 : (int)min((uint32_t)HIST_IPT, n - first);
         for (int p = 0; p < passes; p++) {
             const int sh_p = shift0 + p * RB;
             uint32_t cur = (k[0] >> sh_p) & R::MASK, run = 0;
@@ -92,7 +116,7 @@ __global__ __launch_bounds__(MQ_BLOCK) void radix_hist_kernel(SortSrc src, const
     }
     __syncthreads();
     uint32_t* row = part + (uint64_t)blockIdx.x * passes * R::BUCKETS;
-    for (int i = threadIdx.x; i < passes * R::BUCKETS; i += MQ_BLOCK) row[i] = sh[i];
+    for (int i = threadIdx.x; i < passes * R::BUCKETS; i += NT) row[i] = sh[i];
 }
 
 // hist[c] = sum over the partial rows.  A block of 16 waves owns 64
@@ -238,19 +262,27 @@ hipError_t launch_radix_hist(const SortSrc& src, const uint32_t* keys, uint32_t 
                              uint32_t* part, uint32_t* hist, hipStream_t stream) {
     if (n == 0) return hipSuccess;
     if (shift0 < 0 || passes < 1 || shift0 + (passes - 1) * rb > 31) return hipErrorInvalidValue;
-    const uint32_t blocks = std::min((n + MQ_BLOCK * HIST_IPT - 1) / (MQ_BLOCK * HIST_IPT), HIST_BLOCKS);
+    const uint32_t nt = n >= HIST_BIG ? 1024u : (uint32_t)MQ_BLOCK;
+    const uint32_t blocks = std::min((n - 1) / (nt * HIST_IPT) + 1, HIST_BLOCKS);
     bool gen = keys == nullptr;
-#define MQ_H(B)                                                                                         \
-    case B:                                                                                             \
-        if (gen)                                                                                        \
-            radix_hist_kernel<B, true><<<blocks, MQ_BLOCK, 0, stream>>>(src, keys, n, shift0, passes, part);    \
-        else                                                                                            \
-            radix_hist_kernel<B, false><<<blocks, MQ_BLOCK, 0, stream>>>(src, keys, n, shift0, passes, part);   \
+#define MQ_HG(B, G)                                                                                     \
+    if (nt == 1024)                                                                                     \
+        radix_hist_kernel<B, G, 1024><<<blocks, nt, 0, stream>>>(src, keys, n, shift0, passes, part);   \
+    else                                                                                                \
+        radix_hist_kernel<B, G, MQ_BLOCK><<<blocks, nt, 0, stream>>>(src, keys, n, shift0, passes, part)
+#define MQ_H(B)            \
+    case B:                \
+        if (gen) {         \
+            MQ_HG(B, true);  \
+        } else {           \
+            MQ_HG(B, false); \
+        }                  \
         break;
     switch (rb) {
         MQ_RB_LIST(MQ_H)
         default: return hipErrorInvalidValue;
     }
+#undef MQ_HG
 #undef MQ_H
     const uint32_t width = (uint32_t)passes << rb;
     return launch_hist_reduce(part, blocks, width, hist, stream);

@@ -272,12 +272,16 @@ hipError_t launch_unpack_pos(const uint32_t* w0, const uint32_t* w1, uint64_t n,
 // ---- distinct values per predicate -----------------------------------------
 // cnt[q] = runs of equal values in col over the rows of predicate q (its rows
 // are [off[q], off[q + 1])), for the PSO subject column (blockIdx.y 0) and the
-// POS object column (1).  A block owns DIST_ROWS rows of a column: while few
-// predicates meet in them it counts each one's heads with a block reduction
-// and one atomic, else every head finds its predicate by itself.  One launch
-// for all: 20M triples, 15 predicates 98 us, against 627 us as two launches
-// per predicate whose waves all added to one word.
-constexpr uint32_t DIST_ROWS = 8192;
+// POS object column (1).  A wave owns DIST_IPT * 64 consecutive rows: each row
+// is read once (its neighbour comes from the next lane), the heads are kept as
+// bit words and counted per predicate under a mask, and the block's counts meet
+// in LDS before one add per predicate; where many predicates meet in a block,
+// every head finds its predicate by itself.  20M triples, 15 predicates: 50
+// us; 100 with the row before fetched again and every head tested against the
+// predicate's bounds, 627 as two launches per predicate.
+constexpr int DIST_IPT = 32;
+constexpr uint32_t DIST_THREADS = 1024;
+constexpr uint32_t DIST_ROWS = DIST_THREADS * DIST_IPT;
 constexpr uint32_t DIST_FEW = 4;
 
 // last q with off[q] <= row
@@ -291,62 +295,72 @@ __device__ __forceinline__ uint32_t pred_at(const int64_t* __restrict__ off, uin
     return lo;
 }
 
-__global__ __launch_bounds__(IX_THREADS) void distinct_kernel(const int32_t* __restrict__ a,
-                                                              const int32_t* __restrict__ b, int64_t n,
-                                                              const int64_t* __restrict__ off, uint32_t np,
-                                                              unsigned long long* __restrict__ cnt) {
-    constexpr int IPT = DIST_ROWS / IX_THREADS;
-    __shared__ uint32_t sh[IX_THREADS / MQ_WAVE];
+__global__ __launch_bounds__(DIST_THREADS) void distinct_kernel(const int32_t* __restrict__ a,
+                                                                const int32_t* __restrict__ b, int64_t n,
+                                                                const int64_t* __restrict__ off, uint32_t np,
+                                                                unsigned long long* __restrict__ cnt) {
+    static_assert(DIST_IPT <= MQ_WAVE && DIST_FEW <= DIST_THREADS, "a lane per head word");
+    __shared__ uint32_t sh[DIST_FEW];
     const int32_t* __restrict__ x = blockIdx.y ? b : a;
     unsigned long long* out = cnt + (blockIdx.y ? np : 0u);
     const int64_t r0 = (int64_t)blockIdx.x * DIST_ROWS;
     const int64_t r1 = min(r0 + (int64_t)DIST_ROWS, n);
     const uint32_t q0 = pred_at(off, np, r0), q1 = pred_at(off, np, r1 - 1);
-    // row k of this thread: r0 + k * IX_THREADS + threadIdx.x
-    uint32_t heads = 0;  // bit k: row k differs from the row before it
-    static_assert(IPT == 32, "one head bit per row of a thread");
-#pragma unroll 8
-    for (int k = 0; k < IPT; k++) {
-        const int64_t i = r0 + (int64_t)k * IX_THREADS + threadIdx.x;
-        const int32_t v = i < r1 ? x[i] : 0;
-        int32_t u = __shfl_up(v, 1);
-        if (lane() == 0 && i > 0 && i < r1) u = x[i - 1];
-        if (i < r1 && (i == 0 || u != v)) heads |= 1u << k;
-    }
-    if (q1 - q0 < DIST_FEW) {
-        for (uint32_t q = q0; q <= q1; q++) {
-            const int64_t lo = max(off[q], r0), hi = min(off[q + 1], r1);
-            uint32_t c = 0;
-#pragma unroll 8
-            for (int k = 0; k < IPT; k++) {
-                const int64_t i = r0 + (int64_t)k * IX_THREADS + threadIdx.x;
-                // a predicate's first row starts a run whatever came before it
-                if (i >= lo && i < hi && (((heads >> k) & 1u) || i == off[q])) c++;
+    if (threadIdx.x < DIST_FEW) sh[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t w0 = r0 + (int64_t)(threadIdx.x / MQ_WAVE) * (DIST_IPT * MQ_WAVE);
+    if (w0 < r1) {  // wave-uniform
+        const uint32_t rows = (uint32_t)min((int64_t)(DIST_IPT * MQ_WAVE), r1 - w0);
+        uint32_t before = w0 > 0 ? (uint32_t)x[w0 - 1] : ~(uint32_t)x[0];
+        uint64_t word = 0;  // lane k: heads of rows [64 k, 64 k + 64) of the wave
+        constexpr int PART = 16;
+#pragma unroll
+        for (int p = 0; p < DIST_IPT; p += PART) {
+            uint32_t v[PART];
+#pragma unroll
+            for (int i = 0; i < PART; i++) v[i] = (uint32_t)x[w0 + min((p + i) * MQ_WAVE + lane(), rows - 1)];
+#pragma unroll
+            for (int i = 0; i < PART; i++) {
+                const uint32_t prev = wave_prev(v[i], before);
+                const uint64_t m = __ballot(prev != v[i] && (p + i) * MQ_WAVE + lane() < rows);
+                before = last_lane(v[i]);
+                if (lane() == (uint32_t)(p + i)) word = m;
             }
-            c = wave_sum(c);
-            if (lane() == 0) sh[threadIdx.x / MQ_WAVE] = c;
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                for (uint32_t w = 1; w < IX_THREADS / MQ_WAVE; w++) c += sh[w];
-                if (c) atomicAdd(out + q, (unsigned long long)c);
-            }
-            __syncthreads();
         }
-        return;
+        if (q1 - q0 < DIST_FEW) {
+            for (uint32_t q = q0; q <= q1; q++) {
+                const int64_t lo = off[q] - w0, hi = off[q + 1] - w0;  // the predicate's rows, wave-relative
+                if (lo >= (int64_t)rows || hi <= 0) continue;
+                const int64_t f = (int64_t)lane() * MQ_WAVE;  // the lane's first row
+                uint64_t mask = ~0ull;
+                if (lo > f) mask = lo - f >= MQ_WAVE ? 0ull : ~0ull << (lo - f);
+                if (hi < f + MQ_WAVE) mask = hi <= f ? 0ull : mask & (~0ull >> (f + MQ_WAVE - hi));
+                uint64_t heads = word;
+                // a predicate's first row starts a run whatever came before it
+                if (lo >= f && lo < f + MQ_WAVE) heads |= 1ull << (lo - f);
+                const uint32_t c = last_lane(wave_incl_u32((uint32_t)__popcll(heads & mask)));
+                if (lane() == 0 && c) atomicAdd(&sh[q - q0], c);
+            }
+        } else {
+            for (uint32_t k = 0; k < DIST_IPT; k++) {
+                const uint64_t m = __shfl(word, (int)k);
+                const uint32_t at = k * MQ_WAVE + lane();
+                if (at >= rows) continue;
+                const uint32_t q = pred_at(off, np, w0 + at);
+                if (((m >> lane()) & 1ull) || w0 + at == off[q]) atomicAdd(out + q, 1ull);
+            }
+        }
     }
-    for (int k = 0; k < IPT; k++) {
-        const int64_t i = r0 + (int64_t)k * IX_THREADS + threadIdx.x;
-        if (i >= r1) break;
-        const uint32_t q = pred_at(off, np, i);
-        if (((heads >> k) & 1u) || i == off[q]) atomicAdd(out + q, 1ull);
-    }
+    __syncthreads();
+    if (q1 - q0 < DIST_FEW && threadIdx.x <= q1 - q0 && sh[threadIdx.x])
+        atomicAdd(out + q0 + threadIdx.x, (unsigned long long)sh[threadIdx.x]);
 }
 
 hipError_t launch_distinct(const int32_t* pso_s, const int32_t* pos_o, int64_t n, const int64_t* off, uint32_t np,
                            unsigned long long* cnt, hipStream_t stream) {
     if (n == 0 || np == 0) return hipSuccess;
-    const dim3 grid((uint32_t)((n + DIST_ROWS - 1) / DIST_ROWS), 2);
-    distinct_kernel<<<grid, IX_THREADS, 0, stream>>>(pso_s, pos_o, n, off, np, cnt);
+    const dim3 grid((uint32_t)((n - 1) / DIST_ROWS + 1), 2);
+    distinct_kernel<<<grid, DIST_THREADS, 0, stream>>>(pso_s, pos_o, n, off, np, cnt);
     return hipGetLastError();
 }
 

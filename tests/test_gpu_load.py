@@ -19,6 +19,8 @@ CASES = [
     (3, 5, 2, 5, 1),
     (4095, 100, 1, 7, 1),                     # one predicate
     (8193, 1 << 16, 5, 1 << 16, 1),           # 2 * 16 + 3 bits: the high half has three
+    (2_049, 40, 3, 40, 1),                    # one row past a wave's share
+    (65_537, 900, 3, 900, 1),                 # one row past two counting blocks
     (16_385, 50, 700, 50, 1),                 # many predicates in one counting block
     (40_003, 90, 4097, 90, 1),                # more predicates than have statistics
     (20_011, (1 << 29) - 3, 64, 1 << 29, 1),  # 64 bits: the whole word

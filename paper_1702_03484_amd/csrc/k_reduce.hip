@@ -1,19 +1,20 @@
 // ReduceDuplicate of Algorithm 1 on gfx950: after the shuffle, records with
 // equal keys are contiguous, LEFT records (payload < n_left) ahead of RIGHT
 // records within each key.  Three phases:
-//   heads        compacts the first position of every distinct key and its
-//                LEFT/RIGHT split,
-//   count        counts cL*cR pairs per key and scans the counts into exact
-//                output offsets,
+//   segments     finds the first record of every distinct key, its LEFT/RIGHT
+//                split, the pairs cL*cR and their exact output offsets,
 //   materialize  writes the per-key cross products, with the output rows
 //                split evenly over the grid (a key with a huge product is
 //                spread over many blocks).
-// Heads and count each run as two kernels with no ordering between blocks
-// (no tile counter, no look-back): a sum pass in which block b owns a
-// contiguous run of tiles and stores each tile's offset within the run and
-// the run's total, one block that turns the run totals into prefix sums,
-// then a write pass with one tile per block whose offset is its run's
-// prefix plus its in-run offset.
+// Segments are read off bit maps (one bit per record: head, RIGHT) in two
+// kernels with no ordering between blocks (no tile counter, no look-back): a
+// sum pass in which block b owns a contiguous run of tiles and stores each
+// tile's offset within the run and the run's total, one block that turns the
+// run totals into prefix sums, then a pass with one tile per block whose offset
+// is its run's prefix plus its in-run offset.  That last pass writes the
+// segment arrays for the row-chunk kernel, or, where few rows meet per key,
+// the output rows themselves.  Composite keys sorted word by word carry their
+// segment starts as flags and go through the heads and count passes.
 #include "device_common.h"
 #include "kernels.h"
 #include "tile_ops.h"

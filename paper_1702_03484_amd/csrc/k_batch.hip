@@ -468,10 +468,10 @@ __global__ __launch_bounds__(MQ_BLOCK) void bgather_kernel(const BatchHdr* __res
                 int32_t x[GATHER_UNROLL];
 #pragma unroll
                 for (int g = 0; g < GATHER_UNROLL; g++) {
-                    const bool left = r[g] < J.nl;
-                    // a side without this column reads its key column instead
-                    const int32_t* col = left ? (c < J.nvl ? J.lcol[c] : J.lkey) : (c < J.nvr ? J.rcol[c] : J.rkey);
-                    x[g] = col[left ? r[g] : r[g] - J.nl];
+                    // a side without this column reads one word for all its records
+                    const bool left = r[g] < J.nl, has = c < (left ? J.nvl : J.nvr);
+                    const int32_t* col = !has ? J.lkey : left ? J.lcol[c] : J.rcol[c];
+                    x[g] = col[!has ? 0u : left ? r[g] : r[g] - J.nl];
                 }
 #pragma unroll
                 for (int g = 0; g < GATHER_UNROLL; g++) {

@@ -1024,15 +1024,16 @@ __global__ __launch_bounds__(MQ_BLOCK) void gather_values_kernel(GatherArgs g) {
 #pragma unroll
     for (int u = 0; u < GV_UNROLL; u++) r[u] = g.vals[min(i0 + u * MQ_BLOCK, (uint64_t)g.n - 1)];
     for (int c = 0; c < nv; c++) {
-        // a side without this column reads its last one instead, or nothing
-        const int32_t* lc = g.nl ? g.lcol[c < g.nl ? c : g.nl - 1] : nullptr;
-        const int32_t* rc = g.nr ? g.rcol[c < g.nr ? c : g.nr - 1] : nullptr;
+        // a side without this column reads one word for all its records
+        const bool has_l = c < g.nl, has_r = c < g.nr;
+        const int32_t* lc = has_l ? g.lcol[c] : g.rcol[0];
+        const int32_t* rc = has_r ? g.rcol[c] : g.lcol[0];
         int32_t x[GV_UNROLL];
 #pragma unroll
         for (int u = 0; u < GV_UNROLL; u++) {
             const bool left = r[u] < g.n_left;
-            const int32_t* col = left ? lc : rc;
-            x[u] = col ? col[left ? r[u] : r[u] - g.n_left] : 0;
+            const uint32_t at = left ? (has_l ? r[u] : 0u) : (has_r ? r[u] - g.n_left : 0u);
+            x[u] = (left ? lc : rc)[at];
         }
 #pragma unroll
         for (int u = 0; u < GV_UNROLL; u++)

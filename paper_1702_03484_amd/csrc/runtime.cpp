@@ -877,6 +877,7 @@ static mapsq_status few_join(Ctx* ctx, const mapsq_table* L, const mapsq_table* 
         out->nrows = (int64_t)total;
         return MAPSQ_OK;
     }
+    part.reset();  // the result has at least the room the sort would leave it
     mapsq_table m{};
     if ((st = result_room(ctx, total, nc))) return st;
     if (alloc_table(ctx, (int64_t)total, nc, &m))
@@ -1217,7 +1218,7 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
         nL >= FEW_MIN_RECORDS && lv.size() <= FEW_COLS && rv.size() <= FEW_COLS && key_bits > 8 && key_range / 16 <= nL) {
         bool done = false;
         st = few_join(ctx, L, R, lk, rk, lv, rv, kmin, key_range, key_bits, js, set_meta, finish, out, &done);
-        if (done) return st;
+        if (done || st) return st;
     }
 
     // A large shuffle first gets the exact |RS| from two passes over the

@@ -161,7 +161,8 @@ mapsq_status mapsq_predicate_stats(mapsq_ctx* ctx, int32_t predicate, int64_t* t
  * constants form a prefix of one index order and that has no repeated
  * variable returns a view of the store (owned = 0); any other pattern is
  * scanned and compacted into an owned table.  UNSUPPORTED for a pattern
- * without variables; STATE without a store.  Synchronises once. */
+ * without variables; STATE without a store.  Synchronises once: an owned
+ * table's rows are complete on return and can be read on any stream. */
 mapsq_status mapsq_map_pattern(mapsq_ctx* ctx, const mapsq_pattern* pattern, int32_t key_var, mapsq_table* out);
 
 /* Join (Algorithm 1): RS = left JOIN right on variable `key_var`, which both

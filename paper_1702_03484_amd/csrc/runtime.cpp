@@ -694,9 +694,15 @@ mapsq_status map_pattern(Ctx* ctx, const mapsq_pattern* pat, int32_t key_var, ma
         zero_table(out);
         return ctx->fail(MAPSQ_ERR_HIP, std::string("map scan: ") + hipGetErrorString(e));
     }
+    // The count is posted while rows are still being written, and the caller
+    // may read them on any stream: the stream is waited for (50M rows: 79 us
+    // a scan, 72 when the call returned on the count).
     uint64_t kept = 0;
     if (mp.rows > 0) {
-        if (mapsq_status st = wait_mail(ctx, mail)) {
+        e = hipStreamSynchronize(ctx->stream);
+        mapsq_status st = e == hipSuccess ? wait_mail(ctx, mail)
+                                          : ctx->fail(MAPSQ_ERR_HIP, std::string("map scan: ") + hipGetErrorString(e));
+        if (st) {
             free_table(ctx, &t);
             zero_table(out);
             return st;

@@ -162,7 +162,9 @@ class MapSQ:
         return B.make_table(vars, [t.data_ptr() for t in ts], n, key_max, sorted_col)
 
     def column(self, t: B.mapsq_table, c: int) -> torch.Tensor:
-        """Column c of a table as an int32 tensor view (no copy)."""
+        """Column c of a table as an int32 tensor view (no copy).  The rows of a
+        join or query may still be under way on the session's stream: another
+        stream waits for that one before it reads them."""
         n = int(t.nrows)
         if n == 0:
             return torch.empty(0, dtype=torch.int32, device=self.arena.device)
@@ -177,5 +179,5 @@ class MapSQ:
         raise ValueError("column is outside the arena and the wrapped tensors")
 
     def to_numpy(self, t: B.mapsq_table):
-        torch.cuda.current_stream(self.device).synchronize()
+        self.stream.synchronize()  # the rows are written on the session's stream
         return [self.column(t, c).cpu().numpy() for c in range(t.ncols)]

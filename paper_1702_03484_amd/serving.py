@@ -10,7 +10,6 @@ from __future__ import annotations
 import time
 
 import numpy as np
-import torch
 
 from . import binding as B
 
@@ -72,7 +71,7 @@ def run_continuous(sess, queries, arrivals, budget_bytes=0, max_active=0, collec
             continue
         B.mapsq_serve_step(sess.ctx)
         rounds += 1
-        torch.cuda.current_stream(sess.device).synchronize()
+        sess.stream.synchronize()
         now = time.perf_counter() - t0
         idle += 1
         while True:  # the queries that ended this round, one call each
@@ -112,7 +111,7 @@ def run_plain(sess, queries, arrivals, collect=None):
             status[j] = e.code
             lat[j] = time.perf_counter() - t0 - arrivals[j]
             continue
-        torch.cuda.current_stream(sess.device).synchronize()
+        sess.stream.synchronize()
         lat[j] = time.perf_counter() - t0 - arrivals[j]
         if collect is not None:
             collect[j] = (list(t.vars), sess.to_numpy(t))

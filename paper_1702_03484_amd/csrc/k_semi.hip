@@ -156,13 +156,13 @@ __global__ __launch_bounds__(SEMI_THREADS) void semi_write_kernel(SemiArgs a, ui
 
 // Every record of one side, written from position (*at_dev if given) + i.
 __global__ __launch_bounds__(MQ_BLOCK) void side_records_kernel(const int32_t* __restrict__ keys, uint32_t n,
-                                                                int32_t base, uint32_t id_base,
+                                                                int32_t base, uint32_t mask, uint32_t id_base,
                                                                 const uint32_t* __restrict__ at_dev,
                                                                 uint32_t* __restrict__ kout,
                                                                 uint32_t* __restrict__ vout) {
     const uint32_t at = at_dev ? *at_dev : 0u;
     for (uint32_t i = blockIdx.x * MQ_BLOCK + threadIdx.x; i < n; i += gridDim.x * MQ_BLOCK) {
-        kout[at + i] = (uint32_t)keys[i] - (uint32_t)base;
+        kout[at + i] = ((uint32_t)keys[i] - (uint32_t)base) & mask;
         vout[at + i] = id_base + i;
     }
 }
@@ -196,11 +196,11 @@ size_t semi_scratch_bytes(uint32_t n) {
     return n == 0 ? 0 : (((size_t)n - 1) / MQ_WAVE + 1) * 8 + (size_t)std::min(semi_tiles(n), SEMI_BLOCKS) * 4;
 }
 
-hipError_t launch_side_records(const int32_t* keys, uint32_t n, int32_t base, uint32_t id_base,
+hipError_t launch_side_records(const int32_t* keys, uint32_t n, int32_t base, uint32_t mask, uint32_t id_base,
                                const uint32_t* at_dev, uint32_t* kout, uint32_t* vout, hipStream_t stream) {
     if (n == 0) return hipSuccess;
     const uint32_t blocks = std::min<uint32_t>((n + MQ_BLOCK - 1) / MQ_BLOCK, 2048u);
-    side_records_kernel<<<blocks, MQ_BLOCK, 0, stream>>>(keys, n, base, id_base, at_dev, kout, vout);
+    side_records_kernel<<<blocks, MQ_BLOCK, 0, stream>>>(keys, n, base, mask, id_base, at_dev, kout, vout);
     return hipGetLastError();
 }
 

@@ -57,7 +57,7 @@ __global__ __launch_bounds__(SJ_THREADS) void small_join_kernel(SmallJoin a, Mai
         } else {
             const bool right = idx >= a.src.n0;
             const uint32_t r = right ? idx - a.src.n0 : idx;
-            const uint32_t rel = (uint32_t)(right ? a.src.k1 : a.src.k0)[r] - (uint32_t)a.src.base;
+            const uint32_t rel = ((uint32_t)(right ? a.src.k1 : a.src.k0)[r] - (uint32_t)a.src.base) & a.src.mask;
             key[i] = a.src.carry ? rel << 1 | (right ? 1u : 0u) : rel;
             val[i] = a.src.carry ? (uint32_t)(right ? a.src.v1 : a.src.v0)[r] : idx;
         }

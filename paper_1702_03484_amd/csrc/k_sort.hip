@@ -31,7 +31,7 @@ __device__ __forceinline__ int32_t src_load(const int32_t* c0, const int32_t* c1
 }
 
 __device__ __forceinline__ uint32_t src_key_of(const SortSrc& s, int32_t raw, uint32_t idx) {
-    const uint32_t rel = (uint32_t)raw - (uint32_t)s.base;
+    const uint32_t rel = ((uint32_t)raw - (uint32_t)s.base) & s.mask;
     return s.carry ? rel << 1 | (idx >= s.n0 ? 1u : 0u) : rel;
 }
 

@@ -22,6 +22,10 @@ constexpr uint32_t BLOCK_THREADS = 256;  // threads per block of every tiled ker
 // a side without a value column points at any column of its rows and its
 // payloads go unused) and the key is (relative key << 1) | side, so LEFT
 // records still sort ahead of RIGHT ones within a key.
+// Relative keys are cut to `mask`, the bits the sort orders: the segment
+// kernels search for a run's end in sorted keys, and a caller's key bound that
+// does not hold must leave them keys that are in order (such records then meet
+// under the wrong keys).
 struct SortSrc {
     const int32_t* k0;
     uint32_t n0;
@@ -31,6 +35,7 @@ struct SortSrc {
     const int32_t* v0;
     const int32_t* v1;
     int32_t carry;
+    uint32_t mask = ~0u;
 };
 
 // Merge join of two tables already sorted on the key (k_merge.hip).  One
@@ -93,8 +98,8 @@ hipError_t launch_key_dot(const int32_t* keys, uint32_t n, int32_t base, uint64_
 inline uint64_t key_sample_words(uint64_t range) { return (range + 63) / 64; }
 hipError_t launch_key_sample(const int32_t* a, uint32_t na, const int32_t* b, uint32_t nb, int32_t base,
                              uint64_t range, uint32_t* cnt, uint32_t* acc, Mail mail, hipStream_t stream);
-// all n records of one side at kout/vout[(*at_dev or 0) + i]
-hipError_t launch_side_records(const int32_t* keys, uint32_t n, int32_t base, uint32_t id_base,
+// all n records of one side at kout/vout[(*at_dev or 0) + i], relative keys cut to mask
+hipError_t launch_side_records(const int32_t* keys, uint32_t n, int32_t base, uint32_t mask, uint32_t id_base,
                                const uint32_t* at_dev, uint32_t* kout, uint32_t* vout, hipStream_t stream);
 
 // Sort and segments of a small join in one launch (k_small.hip): the records

@@ -1308,6 +1308,8 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
                {reinterpret_cast<uint32_t*>(sb + 2 * nb4), reinterpret_cast<uint32_t*>(sb + 3 * nb4)}};
     uint64_t* seg_off = reinterpret_cast<uint64_t*>(sb + 4 * nb4);
 
+    const uint32_t key_mask = key_bits < 32 ? (1u << key_bits) - 1u : ~0u;  // of a single key: the bits sorted
+
     // Semi-join reduction: when one side is much larger, only its records
     // whose key the other side has are sorted (same rows, same order).
     uint32_t Ns = N;  // records that go through the shuffle
@@ -1338,9 +1340,10 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
             const Mail mail = ctx->next_mail();
             HIPCHK(launch_semi_filter(sa, seg_off, mail, ctx->stream));  // its scratch fits the later offsets' room
             if (left_big)  // the RIGHT records follow the kept LEFT ones
-                HIPCHK(launch_side_records(rkey, nR, kmin, nL, scalar32(ctx, SC_SEMI), b.k[0], b.v[0], ctx->stream));
+                HIPCHK(launch_side_records(rkey, nR, kmin, key_mask, nL, scalar32(ctx, SC_SEMI), b.k[0], b.v[0],
+                                           ctx->stream));
             else
-                HIPCHK(launch_side_records(lkey, nL, kmin, 0u, nullptr, b.k[0], b.v[0], ctx->stream));
+                HIPCHK(launch_side_records(lkey, nL, kmin, key_mask, 0u, nullptr, b.k[0], b.v[0], ctx->stream));
             // bitmap cleared, set and read once; the small side's keys read
             // twice and its records written; the big side's keys read
             ctx->prof_end(ph, 8.0 * words + 16.0 * nsm + 4.0 * nb);
@@ -1373,7 +1376,7 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
     // the side bit below a carried key rides along unsorted: every LEFT record
     // enters ahead of every RIGHT one and the passes are stable
     const int lo_bit = carry ? 1 : 0;
-    SortSrc src{lkey, nL, rkey, nR, kmin, nullptr, nullptr, carry ? 1 : 0};
+    SortSrc src{lkey, nL, rkey, nR, kmin, nullptr, nullptr, carry ? 1 : 0, key_mask};
     if (carry) {
         src.v0 = lv.empty() ? lkey : L->col[lv[0]];  // payloads of a side without values go unused
         src.v1 = rv.empty() ? rkey : R->col[rv[0]];

@@ -255,7 +255,7 @@ __global__ __launch_bounds__(MQ_BLOCK) void seg_sum_kernel(SegIn a, RunGrid g, u
     seg_load<FS, IPT>(a, t0 * TILE, rec);
     for (uint32_t tile = t0; tile < t1; tile++) {
         const uint32_t base = tile * TILE, lim = min(TILE, a.n - base);
-        const bool past = base + TILE < a.n;
+        const bool past = a.n - base > TILE;
         uint32_t ek = 0, ev = 0, lk = 0;
         if (w == 0 && past) {
             const uint32_t e = min(base + TILE + lane(), a.n - 1);
@@ -396,7 +396,7 @@ __global__ __launch_bounds__(MQ_BLOCK) void seg_write_kernel(SegIn a, RunGrid g,
     __shared__ uint32_t s_a[MQ_WAVES], s_b[MQ_WAVES];
     const uint32_t w = threadIdx.x / MQ_WAVE;
     const uint32_t tile = blockIdx.x, base = tile * TILE, lim = min(TILE, a.n - base);
-    const bool past = base + TILE < a.n;
+    const bool past = a.n - base > TILE;
     SegRecs<IPT> rec;
     uint32_t cl[IPT], cr[IPT];
     uint64_t hm[IPT], rm[IPT];
@@ -447,7 +447,7 @@ struct SegScratch {
 static bool seg_few(uint32_t n) { return n < ST_FEW; }
 static RunGrid seg_grid(uint32_t n) {
     const uint32_t tile = st_tile(seg_few(n) ? ST_IPT_FEW : ST_IPT);
-    return run_grid((n + tile - 1) / tile);
+    return run_grid(n ? (n - 1) / tile + 1 : 0u);
 }
 static SegScratch seg_tiles(void* p, uint32_t n) {
     const RunGrid g = seg_grid(n);
@@ -628,8 +628,8 @@ struct BrkScratch {
     uint32_t* h_tloc;
 };
 
-static RunGrid heads_grid(uint32_t n) { return run_grid((n + HEADS_TILE - 1) / HEADS_TILE); }
-static RunGrid count_grid(uint32_t max_seg) { return run_grid(std::max(1u, (max_seg + COUNT_TILE - 1) / COUNT_TILE)); }
+static RunGrid heads_grid(uint32_t n) { return run_grid(n ? (n - 1) / HEADS_TILE + 1 : 0u); }
+static RunGrid count_grid(uint32_t max_seg) { return run_grid(max_seg ? (max_seg - 1) / COUNT_TILE + 1 : 1u); }
 
 static BrkScratch brk_scratch(void* p, uint32_t n) {
     const RunGrid gh = heads_grid(n), gc = count_grid(n);
@@ -747,7 +747,7 @@ __global__ __launch_bounds__(MQ_BLOCK) void count_write_kernel(uint32_t n, const
     __shared__ uint64_t s_tmp[MQ_WAVES];
     const uint32_t ns = n == 0 ? 0u : *nseg_p;
     const uint32_t tile = blockIdx.x;
-    const uint32_t ntiles = (ns + COUNT_TILE - 1) / COUNT_TILE;
+    const uint32_t ntiles = ns ? (ns - 1) / COUNT_TILE + 1 : 0u;
     if (tile >= ntiles) return;
     // wave-striped: slot i of wave w holds segments base + (w * IPT + i) * 64 + lane
     const uint32_t w = threadIdx.x / MQ_WAVE;
@@ -884,7 +884,7 @@ __global__ __launch_bounds__(MQ_BLOCK) void mat_tile_kernel(MatArgs a, RunGrid g
     const int nc = 1 + nl + nr;
     const uint32_t w = threadIdx.x / MQ_WAVE;
     const uint32_t tile = blockIdx.x, base = tile * TILE, lim = min(TILE, a.n - base);
-    const bool past = base + TILE < a.n;
+    const bool past = a.n - base > TILE;
     const SegIn in{a.keys, a.vals, a.n, a.n_left};
     uint32_t ek = 0, ev = 0, lk = 0;
     if (w == MQ_WAVES - 1 && past) {

@@ -55,7 +55,7 @@ __global__ __launch_bounds__(NT) void radix_hist_kernel(SortSrc src, const uint3
     for (int i = threadIdx.x; i < R::MAXP * R::BUCKETS; i += NT) sh[i] = 0;
     __syncthreads();
     constexpr uint32_t TILE = NT * HIST_IPT;
-    const uint32_t ntiles = (n + TILE - 1) / TILE;
+    const uint32_t ntiles = (n - 1) / TILE + 1;
     for (uint32_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
         // a whole tile of one side on a 16-byte boundary: four keys a load,
         // neighbouring lanes on neighbouring addresses; else a thread's 16
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(NT) void radix_hist_kernel(SortSrc src, const uint3
         const bool right = GEN && base >= src.n0;
         const uint32_t* from = GEN ? reinterpret_cast<const uint32_t*>(right ? src.k1 + (base - src.n0) : src.k0 + base)
                                    : keys + base;
-        const bool vec = base + TILE <= (GEN && !right ? min(n, src.n0) : n) &&
+        const bool vec = (GEN && !right ? min(n, src.n0) : n) - base >= TILE &&
                          reinterpret_cast<uintptr_t>(from) % 16 == 0;
         uint32_t k[HIST_IPT];
         if (vec) {
@@ -188,7 +188,7 @@ __device__ __forceinline__ void radix_tile(SplitSmem<RB, KPT, NW>& sm, const Sor
     const uint32_t o0 = threadIdx.x / MQ_WAVE * KPT * MQ_WAVE + lane();
     // a first-pass tile on one side of the join loads from a uniform base
     const bool right = GEN && base >= src.n0;
-    const bool one = GEN && (right || base + TILE <= src.n0);
+    const bool one = GEN && (right || src.n0 - base >= TILE);
     uint32_t key[KPT];
     if (GEN) {
         int32_t raw[KPT];
@@ -323,7 +323,7 @@ hipError_t launch_radix_pass(int rb, int kpt, const SortSrc& src, const uint32_t
 uint32_t radix_tiles(uint32_t n, int kpt, int rb, bool gen) {
     const uint32_t per = sort_wide(rb, kpt) && !gen && n >= SORT_BIG ? 32u : (uint32_t)kpt;
     const uint32_t tile = (uint32_t)(sort_waves(rb, kpt) * MQ_WAVE) * per;
-    return (n + tile - 1) / tile;
+    return n ? (n - 1) / tile + 1 : 0u;
 }
 
 }  // namespace mq

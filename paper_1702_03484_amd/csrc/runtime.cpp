@@ -452,9 +452,19 @@ mapsq_status load_triples(Ctx* ctx, const int32_t* s, const int32_t* p, const in
     if (n > 0) {
         int res = 0;
         int ph = ctx->prof_begin(5);
-        if (2 * bitlen((uint32_t)so_max) + bitlen((uint32_t)(pmax - pmin)) <= 64) {
-            LCHK(build_orders(ctx, n, so_max, pmin, pmax, b));
-        } else {  // a triple does not fit one 64-bit word: sort a permutation
+        // triples that fit one 64-bit word are sorted whole; else, or where the
+        // arena lacks the room (the predicate table is held during the sorts,
+        // and they count more digits at once), a permutation is sorted
+        bool packed = 2 * bitlen((uint32_t)so_max) + bitlen((uint32_t)(pmax - pmin)) <= 64;
+        if (packed) {
+            st = build_orders(ctx, n, so_max, pmin, pmax, b);
+            packed = st != MAPSQ_ERR_CAPACITY;
+            if (packed)
+                LCHK(st);
+            else
+                ctx->err.clear();
+        }
+        if (!packed) {
             LCHK(build_order(ctx, n, S.s, S.o, so_max, pmin, pmax, b, S.pso_s, S.pso_o, true, &res));
             LCHK(build_order(ctx, n, S.o, S.s, so_max, pmin, pmax, b, S.pos_o, S.pos_s, false, &res));
         }

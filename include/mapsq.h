@@ -408,7 +408,9 @@ mapsq_status mapsq_set_tuning(mapsq_ctx* ctx, int32_t radix_bits, int32_t keys_p
  *   mapsq_query and of the server whose planned output (the System-R
  *   estimate of the pattern-size plan, or the exact planner's count) would
  *   take at most 1/8 of the arena's free space, and other joins whose
- *   output, estimated from the exact count over a 64th of the keys, would;
+ *   output, estimated from the exact count over a 64th of the keys, would
+ *   (estimated only where the arena's largest free block holds 40 bytes per
+ *   record, so that the sort and its count cannot run out of room);
  *   1 = never, 2 = every
  *   shuffle.  Without it the same outcome comes after the sort.
  * composite: 0 = a second variable both tables bind is part of the join key

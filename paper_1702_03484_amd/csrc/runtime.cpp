@@ -1250,12 +1250,14 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
     // which reads the key columns once and hardly writes: 16M + 16M records
     // 0.94 ms exactly, 0.07 ms sampled.  A sample that meets no pair, or
     // whose estimate is not small, is followed by the exact count; one that
-    // misses a hot key leaves the refusal to the count after the sort.)
+    // misses a hot key leaves the refusal to the count after the sort, so
+    // it is asked only where the sort is sure of its room.)
     const double room = (double)ctx->arena.free_bytes();
     bool est_small = est_rows >= 0.0 && est_rows * 4.0 * nc_mat * 8.0 < room;
     const bool auto_count =
         !composite && !ctx->count_only && ctx->precount == 0 && (uint64_t)N >= PRECOUNT_MIN_RECORDS;
-    if (auto_count && est_rows < 0.0 && !ctx->out_cols) {
+    const bool sort_room = ctx->arena.largest() >= SORT_ROOM * N + (ctx->semijoin == 2 ? SEMI_MAX_BITMAP : 0);
+    if (auto_count && est_rows < 0.0 && !ctx->out_cols && sort_room) {
         const uint64_t range = (uint64_t)((int64_t)kmax - (int64_t)kmin) + 1;
         Block cnt;
         if (range <= PRECOUNT_MAX_RANGE) cnt = alloc_block(ctx, key_sample_words(range) * 4);
@@ -1336,7 +1338,7 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
         else if (ctx->semijoin == 0)
             semi = nb >= SEMI_MIN_RECORDS && (uint64_t)nsm * SEMI_RATIO <= nb && words <= (uint64_t)nb;
         else if (ctx->semijoin == 2)
-            semi = words * 4 <= (uint64_t(1) << 30);
+            semi = words * 4 <= SEMI_MAX_BITMAP;
         Block bm;
         if (semi) bm = alloc_block(ctx, words * 4);
         if (bm.ok()) {

@@ -214,12 +214,20 @@ struct Ctx {
 // larger than the larger side's key column
 constexpr uint32_t SEMI_MIN_RECORDS = 1u << 16;
 constexpr uint64_t SEMI_RATIO = 4;
+// the largest bitmap of a reduction that is asked for (the automatic rule's is
+// no larger than the key column)
+constexpr uint64_t SEMI_MAX_BITMAP = uint64_t(1) << 30;
 // A LEFT side of at least this many rows with a bound of at most FEW_KEYS
 // distinct keys is grouped by counting instead of sorted, when the key range
 // takes the sort more than one pass (queries over LEFT sides of 2^18, 2^19,
 // 2^21 and 2^23 rows: 152, 157, 233 and 586 us counted, 153, 193, 373 and 1,328
 // sorted).
 constexpr uint32_t FEW_MIN_RECORDS = 1u << 19;
+// Bytes per record that a shuffle of PRECOUNT_MIN_RECORDS or more takes at most
+// before its output is sized: 24 of sort buffers and offsets, 8 of status words
+// (11-bit digits, tiles of 2,048), 4 of key bitmap (SEMI_MAX_BITMAP in all when
+// it is asked for), under 1 of histogram partials and segment scratch.
+constexpr uint64_t SORT_ROOM = 40;
 // exact output size before the shuffle of at least this many records, when
 // the key range needs at most PRECOUNT_MAX_RANGE counters
 constexpr uint64_t PRECOUNT_MIN_RECORDS = uint64_t(1) << 24;

@@ -30,7 +30,7 @@ bool ensure_stage(Ctx* ctx, size_t bytes) {
     ctx->stage = nullptr;
     ctx->stage_bytes = 0;
     size_t want = std::max(bytes, size_t(1) << 20);
-    if (hipHostMalloc(&ctx->stage, want, hipHostMallocDefault) != hipSuccess) return false;
+    if (hipHostMalloc(&ctx->stage, want, HOST_REPORT_FLAGS) != hipSuccess) return false;
     ctx->stage_bytes = want;
     return true;
 }

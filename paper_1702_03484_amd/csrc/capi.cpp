@@ -62,7 +62,7 @@ mapsq_status mapsq_create(int device, void* arena, size_t arena_bytes, void* hip
     ctx->arena.init(reinterpret_cast<char*>(arena), arena_bytes);
     ctx->small_off = ctx->arena.alloc(mq::SMALL_WORDS * 4);
     ctx->small = reinterpret_cast<uint32_t*>(ctx->arena.ptr(ctx->small_off));
-    if (hipHostMalloc(&ctx->pinned, mq::PINNED_BYTES, hipHostMallocCoherent | hipHostMallocMapped) != hipSuccess) {
+    if (hipHostMalloc(&ctx->pinned, mq::PINNED_BYTES, mq::HOST_REPORT_FLAGS) != hipSuccess) {
         delete c;
         return MAPSQ_ERR_HIP;
     }

@@ -49,6 +49,10 @@ class Arena {
     std::unordered_map<size_t, size_t> used_;  // offset -> size
 };
 
+// Host memory that kernels write and the host reads without waiting for the
+// kernel's end: coherent, which plain pinned memory is only by the runtime's
+// default.
+constexpr unsigned HOST_REPORT_FLAGS = hipHostMallocCoherent | hipHostMallocMapped;
 constexpr size_t PINNED_BYTES = 4096;
 constexpr size_t MAIL_OFFSET = 3072;  // the flag's cache line, then the data
 static_assert(MAIL_OFFSET + 64 + 4 * MAIL_WORDS <= PINNED_BYTES, "room for the mail");

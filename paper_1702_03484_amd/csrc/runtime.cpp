@@ -429,7 +429,7 @@ mapsq_status load_triples(Ctx* ctx, const int32_t* s, const int32_t* p, const in
         c.out[2] = no.as<int32_t>();
         c.count = scalar64(ctx, SC_COUNT);
         Block cs = alloc_block(ctx, compact_scratch_words((uint64_t)n) * 8);
-        if (!cs.ok()) {
+        if (!cs.ok() || !ctx->ensure_status(compact_status_words())) {
             free_store(ctx);
             return ctx->fail(MAPSQ_ERR_CAPACITY, "arena: no room for de-duplication");
         }
@@ -687,7 +687,7 @@ mapsq_status map_pattern(Ctx* ctx, const mapsq_pattern* pat, int32_t key_var, ma
     }
     CompactArgs a = map_scan_args(mp, ncols, t.col, scalar64(ctx, SC_COUNT));
     Block cs = alloc_block(ctx, compact_scratch_words((uint64_t)mp.rows) * 8);
-    if (!cs.ok()) {
+    if (!cs.ok() || !ctx->ensure_status(compact_status_words())) {
         free_table(ctx, &t);
         zero_table(out);
         return ctx->fail(MAPSQ_ERR_CAPACITY, "arena: no room for the map's row masks");
@@ -1063,7 +1063,7 @@ mapsq_status join_tables(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, i
         uint64_t kept = 0;
         e = hipSuccess;
         Block cs = alloc_block(ctx, compact_scratch_words((uint64_t)total) * 8);
-        if (!cs.ok()) {
+        if (!cs.ok() || !ctx->ensure_status(compact_status_words())) {
             free_table(ctx, &m);
             free_table(ctx, &f);
             return ctx->fail(MAPSQ_ERR_CAPACITY, "arena: no room for the equality filter's row masks");

@@ -781,8 +781,11 @@ static mapsq_status result_room(Ctx* ctx, uint64_t rows, int nc) {
 }
 
 // The join of a LEFT side with at most FEW_KEYS distinct keys (k_few.hip):
-// *done stays false when there is no room for the scratch or more keys than
-// that, and nothing has happened then.
+// *done stays false, and nothing has happened, when there is no room for the
+// scratch, when the result needs room that the scratch may be in the way of
+// (it is five blocks where the sort's is one, and splits the free space
+// differently), or when there are more keys after all (the caller's bound is a
+// hint; the planner's holds).
 template <class SetMeta, class Finish>
 static mapsq_status few_join(Ctx* ctx, const mapsq_table* L, const mapsq_table* R, int lk, int rk,
                              const std::vector<int>& lv, const std::vector<int>& rv, int32_t kmin, uint64_t range,
@@ -790,6 +793,8 @@ static mapsq_status few_join(Ctx* ctx, const mapsq_table* L, const mapsq_table* 
                              bool* done) {
     const uint32_t nL = (uint32_t)L->nrows, nR = (uint32_t)R->nrows;
     const int nl = (int)lv.size(), nr = (int)rv.size(), nc = 1 + nl + nr;
+    const mapsq_join_stats before = js;
+    const size_t free0 = ctx->arena.free_bytes();
     const uint64_t words = (range + 31) / 32;
     const size_t lb = align_up(size_t(nL) * 4, ARENA_ALIGN), rb4 = align_up(size_t(nR) * 4, ARENA_ALIGN);
     const size_t bmb = align_up(words * 4, ARENA_ALIGN), tabb = align_up(words * sizeof(FewEntry), ARENA_ALIGN);
@@ -893,11 +898,16 @@ static mapsq_status few_join(Ctx* ctx, const mapsq_table* L, const mapsq_table* 
         out->nrows = (int64_t)total;
         return MAPSQ_OK;
     }
-    part.reset();  // the result has at least the room the sort would leave it
+    part.reset();
     mapsq_table m{};
-    if ((st = result_room(ctx, total, nc))) return st;
-    if (alloc_table(ctx, (int64_t)total, nc, &m))
-        return ctx->fail(MAPSQ_ERR_TOO_LARGE, "join result exceeds the arena's free space");
+    const size_t need = align_up(size_t(total) * 4, ARENA_ALIGN) * nc;
+    if (need > free0) return result_room(ctx, total, nc);  // whatever groups the keys
+    if (alloc_table(ctx, (int64_t)total, nc, &m)) {
+        js = before;
+        ctx->last = js;
+        *done = false;
+        return MAPSQ_OK;
+    }
     // a launch that fails frees the result first
     auto step = [&](hipError_t e, const char* what) -> mapsq_status {
         if (e == hipSuccess) return MAPSQ_OK;

@@ -123,29 +123,21 @@ __global__ __launch_bounds__(1024) void few_segments_kernel(const uint32_t* __re
                                                             int32_t* __restrict__ lkey, Mail mail) {
     constexpr int W = 1024 / MQ_WAVE;
     __shared__ uint32_t s_l[W], s_r[W];
-    __shared__ uint64_t s_p[W], s_m[W];
+    __shared__ uint64_t s_p[W];
     const uint32_t d = threadIdx.x, w = d / MQ_WAVE;
     const uint32_t cl = d < nkeys ? lhist[d] : 0u, cr = d < nkeys ? rhist[d] : 0u;
     const uint64_t pairs = min((uint64_t)cl * cr, SAT40);  // 1,024 of them stay far below 2^64
     const uint32_t il = wave_incl_scan(cl), ir = wave_incl_scan(cr);
     const uint64_t ip = wave_incl_scan(pairs);
-    uint64_t mx = pairs;
-#pragma unroll
-    for (int o = MQ_WAVE / 2; o > 0; o >>= 1) {
-        const uint64_t y = __shfl_xor(mx, o);
-        mx = y > mx ? y : mx;
-    }
     if (lane() == MQ_WAVE - 1) {
         s_l[w] = il;
         s_r[w] = ir;
         s_p[w] = ip;
-        s_m[w] = mx;
     }
     __syncthreads();
     uint32_t el = il - cl, er = ir - cr;
     uint64_t ep = ip - pairs, total = 0;
     uint32_t rows_l = 0;
-    mx = 0;
     for (uint32_t i = 0; i < W; i++) {
         rows_l += s_l[i];
         if (i < w) {
@@ -154,7 +146,6 @@ __global__ __launch_bounds__(1024) void few_segments_kernel(const uint32_t* __re
             ep += s_p[i];
         }
         total += s_p[i];
-        mx = s_m[i] > mx ? s_m[i] : mx;
     }
     if (d < nkeys) {
         seg_ls[d] = el;
@@ -170,9 +161,7 @@ __global__ __launch_bounds__(1024) void few_segments_kernel(const uint32_t* __re
         mail.data[0] = nkeys;
         mail.data[2] = (uint32_t)total;
         mail.data[3] = (uint32_t)(total >> 32);
-        mail.data[4] = (uint32_t)mx;
-        mail.data[5] = (uint32_t)(mx >> 32);
-        mail.data[6] = rows_l;
+        mail.data[4] = rows_l;
         mail_post(mail);
     }
 }

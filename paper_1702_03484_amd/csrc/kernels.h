@@ -142,6 +142,10 @@ uint32_t few_table_tiles(uint64_t range);
 // One side of that shuffle: rows whose key - base is in the table, grouped by
 // the key's rank in it, in input order inside a group.  Row i's values are
 // in[c][ids[i]] (ids null: in[c][i]) and go to out[c].
+// The columns of a side are limited by the scratch, which stays below the 24
+// bytes per record that the sort asks for: per LEFT row 6 of bitmap and table
+// and 4 for the key and each column, per RIGHT row 8.1 of filtered records and 4
+// for each column.
 constexpr int FEW_COLS = 3;
 struct FewSide {
     const int32_t* keys;
@@ -161,8 +165,8 @@ hipError_t launch_few_hist(const FewSide& s, int rb, uint32_t* part, uint32_t* h
 uint32_t few_part_words(int rb);
 // Segments of nkeys keys from both sides' histograms; every key has rows on
 // both sides.  Runs, output offsets and *nseg as launch_merge_segments writes
-// them; lkey[first row of the LEFT run] = the key; mail as launch_seg_sum's,
-// then the LEFT rows that have a partner.
+// them; lkey[first row of the LEFT run] = the key; mail: nkeys, a pad word,
+// pairs (2 words, capped at 2^40 - 1), the LEFT rows that have a partner.
 hipError_t launch_few_segments(const uint32_t* lhist, const uint32_t* rhist, const int32_t* keys, uint32_t nkeys,
                                uint32_t* seg_ls, uint32_t* seg_lc, uint32_t* seg_rs, uint32_t* seg_rc,
                                uint64_t* seg_off, uint32_t* nseg, int32_t* lkey, Mail mail, hipStream_t stream);

@@ -885,7 +885,7 @@ static mapsq_status few_join(Ctx* ctx, const mapsq_table* L, const mapsq_table* 
     ctx->prof_end(ph, 4.0 * nL + 4.0 * kept);
     if ((st = wait_mail(ctx, mail))) return st;
     const uint64_t total = mail64(mail, 2);
-    const uint32_t rows_l = mail.data[6];
+    const uint32_t rows_l = mail.data[4];
     js.segments = (int64_t)nkeys;
     js.out_rows = (int64_t)total;
     js.radix_bits = rb;

@@ -137,7 +137,7 @@ __device__ __forceinline__ void sort_tile_split(SplitSmem<RB, KPT, NW>& sm, uint
                 run += c;
             }
             if (!FULL && d == pad_digit) run -= TILE - valid_n;
-            st_store(st + d, st_pack(epoch, tile == first ? ST_INC : ST_AGG, run));
+            if (BPT == 1) st_store(st + d, st_pack(epoch, tile == first ? ST_INC : ST_AGG, run));
         }
         tot[k] = run;
         sum_t += run;
@@ -166,10 +166,29 @@ __device__ __forceinline__ void sort_tile_split(SplitSmem<RB, KPT, NW>& sm, uint
             for (int i = 0; i < NW; i++) sm.wcnt[i][d] = (uint16_t)(sm.wcnt[i][d] + ex_t);
         }
         off[k] = ex_g - ex_t;
+        if (BPT > 1 && d < (uint32_t)R::BUCKETS) sm.goff[d] = off[k];
         ex_t += tot[k];
         ex_g += gh[k];
     }
     __syncthreads();
+    // Digits wider than the block: a thread's own are neighbours for the
+    // prefixes above, but its status words must not be (64 lanes would touch 64
+    // lines a word), so they are published and looked up striped, the tile's
+    // counts taken from the digits' places (25M records of 24 bits, 11-bit
+    // digits at 8 keys per thread: 9.9 ms, 2.3 striped; 10 bits: 4.0 and 1.5;
+    // 9 bits: 1.55 and 1.10).
+    auto striped = [&](int k) { return threadIdx.x + (uint32_t)k * NT; };
+    auto count_of = [&](uint32_t d) {
+        return (d + 1 < (uint32_t)R::BUCKETS ? (uint32_t)sm.wcnt[0][d + 1] : valid_n) - sm.wcnt[0][d];
+    };
+    if (BPT > 1) {
+#pragma unroll
+        for (int k = 0; k < BPT; k++) {
+            const uint32_t d = striped(k);
+            if (d < (uint32_t)R::BUCKETS)
+                st_store(st + d, st_pack(epoch, tile == first ? ST_INC : ST_AGG, count_of(d)));
+        }
+    }
     // keys into LDS in digit order; their places replace the ranks
     opaque(key);
     opaque(place);
@@ -184,14 +203,14 @@ __device__ __forceinline__ void sort_tile_split(SplitSmem<RB, KPT, NW>& sm, uint
     // the earlier tiles' records of each digit, while the other waves scatter
 #pragma unroll
     for (int k = 0; k < BPT; k++) {
-        const uint32_t d = threadIdx.x * BPT + k;
+        const uint32_t d = striped(k);
         if (d < (uint32_t)R::BUCKETS) {
             uint32_t ex = 0;
             if (tile > first) {
                 ex = (uint32_t)lookback(status + d, tile, first, R::BUCKETS, epoch);
-                st_store(st + d, st_pack(epoch, ST_INC, ex + tot[k]));
+                st_store(st + d, st_pack(epoch, ST_INC, ex + (BPT == 1 ? tot[k] : count_of(d))));
             }
-            sm.goff[d] = off[k] + ex;
+            sm.goff[d] = (BPT == 1 ? off[k] : sm.goff[d]) + ex;
         }
     }
     __syncthreads();

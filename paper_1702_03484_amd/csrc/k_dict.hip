@@ -356,14 +356,18 @@ static hipError_t scan_write(const Items& it, uint32_t n, void* part, const Out&
 // Terms back to back in out[0 .. total): term i takes out[pos[i] - base ..
 // pos[i + 1] - base) (the last one ends at total) from src.of(i).  HBM-bound
 // on the written bytes and short on parallel work per term, so the output is
-// what is split: a block owns COPY_BYTES consecutive bytes from a 16-byte
+// what is split: a block owns up to COPY_BYTES consecutive bytes from a 16-byte
 // boundary, finds its first term with a 64-ary search, stages offsets and
 // sources of COPY_TERMS terms at a time in LDS, and each thread writes whole
 // 16-byte pieces, looking its piece's term up in LDS and loading four bytes
 // at a time where a term holds them.  A term of any length, and any run of
 // empty terms, is spread the same way.  3M terms of 33 bytes: 0.44 ms with
-// one wave per term and one byte per lane, 0.11 ms so.
-constexpr uint32_t COPY_BYTES = 8192;
+// one wave per term and one byte per lane, 0.11 ms so.  A small output is
+// split over COPY_BLOCKS blocks first, down to pieces of COPY_LEAST bytes: its
+// terms are short, and a block takes 512 of them after another (decode of
+// 10,000 terms of 3 bytes: 81 us in pieces of 8,192 bytes, 45 so; 400,000
+// terms: 89 and 50).
+constexpr uint32_t COPY_BYTES = 8192, COPY_LEAST = 512, COPY_BLOCKS = 1024;
 constexpr uint32_t COPY_TERMS = 512;
 
 struct BatchSrc {
@@ -393,13 +397,14 @@ __device__ __forceinline__ uint32_t term_at(const int64_t* __restrict__ pos, uin
 
 template <class Src>
 __global__ __launch_bounds__(MQ_BLOCK) void copy_terms_kernel(Src src, const int64_t* __restrict__ pos, uint32_t n,
-                                                              int64_t base, int64_t total, uint8_t* __restrict__ out) {
+                                                              int64_t base, int64_t total, uint32_t per,
+                                                              uint8_t* __restrict__ out) {
     __shared__ int32_t s_off[COPY_TERMS + 1];  // offsets from c0, clamped to the block's range
     __shared__ const uint8_t* s_src[COPY_TERMS];
     // this block's bytes [c0, c1) of the output; c0 is 16-byte aligned in memory but for the first block
     const int64_t skew = (int64_t)(reinterpret_cast<uintptr_t>(out) & 15u);
-    const int64_t a0 = (int64_t)blockIdx.x * COPY_BYTES - skew;  // aligned start (may lie before the output)
-    const int64_t c0 = max(a0, (int64_t)0), c1 = min(a0 + (int64_t)COPY_BYTES, total);
+    const int64_t a0 = (int64_t)blockIdx.x * per - skew;  // aligned start (may lie before the output)
+    const int64_t c0 = max(a0, (int64_t)0), c1 = min(a0 + (int64_t)per, total);
     int64_t cur = c0;
     uint32_t i = 0;
     while (cur < c1) {
@@ -460,8 +465,10 @@ static hipError_t copy_terms(const Src& src, const int64_t* pos, uint32_t n, int
                              hipStream_t s) {
     if (n == 0 || total == 0) return hipSuccess;
     const uint64_t span = (uint64_t)total + (reinterpret_cast<uintptr_t>(out) & 15u);
-    copy_terms_kernel<Src><<<(uint32_t)((span + COPY_BYTES - 1) / COPY_BYTES), MQ_BLOCK, 0, s>>>(src, pos, n, base,
-                                                                                               total, out);
+    // a multiple of 16, so that every piece but the first starts on a 16-byte boundary
+    const uint32_t per = (uint32_t)std::min<uint64_t>(
+        COPY_BYTES, std::max<uint64_t>(COPY_LEAST, span / COPY_BLOCKS / 16 * 16));
+    copy_terms_kernel<Src><<<(uint32_t)((span + per - 1) / per), MQ_BLOCK, 0, s>>>(src, pos, n, base, total, per, out);
     return hipGetLastError();
 }
 

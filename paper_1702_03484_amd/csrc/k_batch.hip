@@ -33,8 +33,15 @@ uint32_t batch_chunk_rows() { return BMAT_WROWS; }
 // compaction 64 us, 141.
 constexpr int TILE_KPT = 8;
 constexpr int tile_waves(int kpt) { return kpt * (int)MQ_BLOCK / (int)MQ_WAVE / TILE_KPT; }
-// one resident round of blocks
-constexpr uint32_t tile_blocks(int kpt) { return 256u * 32u / (uint32_t)tile_waves(kpt); }
+// One resident round of blocks, but 1,024 at most: every block takes a tile
+// number at least once, and those queue on one word (a launch without work for
+// them: 11 ns a block).  Only 8 keys per thread (4 waves a block) have more
+// than that resident: one join of 1,800 records 164 us with 1,024 blocks, 237
+// with 2,048; one of 4M 567 and 625.
+constexpr uint32_t tile_blocks(int kpt) {
+    const uint32_t resident = 256u * 32u / (uint32_t)tile_waves(kpt);
+    return resident < 1024u ? resident : 1024u;
+}
 
 // Relative key of record idx (< nl + nr) of a join: the column is selected
 // per lane before one load, and callers clamp idx into range instead of

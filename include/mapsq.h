@@ -40,6 +40,8 @@
  *   that arena and never calls hipMalloc.  Host-side bookkeeping is the only
  *   host allocation.  All GPU work of a context is enqueued on its stream.
  *   A context is externally synchronised: one thread at a time per context.
+ *   A call that waits for a size polls host memory for up to 5 ms of its
+ *   thread's time before it blocks.
  *   Several contexts may share a device.
  */
 #ifndef MAPSQ_H

@@ -131,6 +131,8 @@ def install(sess, path) -> bool:
 
 
 DEFAULT_TABLE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuning.json")
+# Records up to 4,096 (classes 11 and 12) go through the radix passes only when
+# a composite key is sorted word by word; other joins that small take one block.
 DEFAULT_CLASSES = [(kb, 3 << (lg - 2)) for kb in (20, 24, 26, 31) for lg in range(11, 26)]
 DEFAULT_MAT_CLASSES = [1 << lg for lg in range(16, 29, 2)]
 

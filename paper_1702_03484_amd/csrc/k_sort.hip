@@ -166,10 +166,13 @@ uint32_t radix_hist_part_words(int rb, int passes) { return HIST_BLOCKS * (uint3
 // 16,384 records (32M records, carried pass: 148 us, against 181 us in 8-wave
 // blocks of half the tile, four to a CU: a pass pays for tiles in look-backs).
 // Carried passes of 2^24.6 records and more take 32 keys per thread, tiles of
-// 32,768 records in 137 KB: 133 us at 32M records, but 93 against 88 us at
-// 20M, where 610 tiles fill 256 CUs unevenly.  The first pass (its keys come
-// from two columns) stays at 16: 132 us, against 148.  Everything else, small
-// sorts and wide digits, runs in 4-wave blocks.
+// 32,768 records in 137 KB: 133 us at 32M records, but 93 against 88 us for one
+// at 20M, where 610 tiles fill 256 CUs unevenly.  (Whole sorts of 24-bit keys,
+// 32 against 16 keys: 12.6M records 0.197 and 0.206 ms, 16.8M 0.233 and 0.249,
+// 21M 0.297 and 0.300, 25M 0.330 and 0.348, 33.6M 0.431 and 0.456, so the line
+// could lie lower.)  The first pass (its keys come from two columns) stays at
+// 16: 132 us, against 148.  Everything else, small sorts and wide digits, runs
+// in 4-wave blocks.
 constexpr uint32_t SORT_BIG = 3u << 23;
 __host__ __device__ constexpr bool sort_wide(int rb, int kpt) { return rb <= 8 && kpt == 16; }
 __host__ __device__ constexpr int sort_waves(int rb, int kpt) { return sort_wide(rb, kpt) ? 16 : 4; }

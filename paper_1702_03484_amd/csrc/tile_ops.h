@@ -90,7 +90,7 @@ __device__ __forceinline__ void sort_tile_split(SplitSmem<RB, KPT, NW>& sm, uint
     // (two 16-bit ranks per register).  Peers of a lane, those with its digit:
     // per bit, the lanes whose ballot agrees with this lane's bit spread over
     // 64 bits; one extract, one compare and two three-input operations a bit.
-    // This is what bounds the pass: 41 vector instructions a key at 4 cycles
+    // This is what bounds the pass: 44 vector instructions a key at 4 cycles
     // each, half of a tile's time (75 of them, and 187 us for a pass over 32M
     // records, with shifts for extracts and population counts of masks).
     uint32_t place[KPT / 2];

@@ -26,10 +26,12 @@ static DictDev dev_of(const Dict& d) {
     return DictDev{d.table, d.slots - 1, d.off, d.bytes, (uint32_t)d.nterms};
 }
 
-// A synchronising read-back: every call goes on to a copy or a wait of the
-// stream, and those cost more when a polled report came before them than the
-// report saves (a lookup of one term in host buffers: 52 us, 73 polled; a decode
-// of one, sized and fetched: 64 and 81).
+// A synchronising read-back, for the calls whose wait or copy at the end costs
+// about 20 us more when polled reports came before it than the reports save:
+// those on host buffers, and those of more than some eight launches (a lookup of
+// one term in host buffers: 52 us, 73 polled; one new batch in device buffers: 58
+// and 77).  Short calls on device buffers are polled (a lookup: 50 us, 40 polled;
+// a decode: 38 and 34).
 static mapsq_status sync_read(Ctx* ctx, const void* dev, size_t bytes, void* host) {
     HIPCHK_D(hipMemcpyAsync(ctx->pinned, dev, bytes, hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK_D(hipStreamSynchronize(ctx->stream));
@@ -92,7 +94,7 @@ mapsq_status dict_encode(Ctx* ctx, const uint8_t* bytes, const int64_t* offsets,
     if (dev) {
         HIPCHK_D(launch_dict_check_offsets(offsets, nn, err, reinterpret_cast<int64_t*>(err + 6), ctx->stream));
         uint32_t e[8];
-        if (mapsq_status st = sync_read(ctx, err, sizeof(e), e)) return st;
+        if (mapsq_status st = (insert ? sync_read : readback)(ctx, err, sizeof(e), e)) return st;
         if (e[0]) return ctx->fail(MAPSQ_ERR_INVALID_ARG, "offsets must start at 0 and not decrease");
         std::memcpy(&total, &e[6], 8);
     } else {
@@ -132,7 +134,7 @@ mapsq_status dict_encode(Ctx* ctx, const uint8_t* bytes, const int64_t* offsets,
     const DictDev dd = dev_of(d);
     HIPCHK_D(launch_dict_encode_front(dd, t, insert ? 1 : 0, w, ctx->stream));
     uint32_t sv[6];  // err, pad, new terms, pad, new bytes (2 words)
-    if (mapsq_status st = sync_read(ctx, err, sizeof(sv), sv)) return st;
+    if (mapsq_status st = (dev && !insert ? readback : sync_read)(ctx, err, sizeof(sv), sv)) return st;
     if (sv[0] & 2) {
         if (insert) (void)launch_dict_fix(dd, w, (uint32_t)d.nterms, 0, ctx->stream);
         return ctx->fail(MAPSQ_ERR_HIP, "dictionary table full");
@@ -199,13 +201,15 @@ mapsq_status dict_decode(Ctx* ctx, const int32_t* ids, int64_t n, uint32_t flags
     const DictDev dd = dev_of(d);
     HIPCHK_D(launch_dict_decode_size(dd, ids_dev, nn, err + 1, total, part, err, ctx->stream));
     uint32_t sv[4];
-    if (mapsq_status st = sync_read(ctx, err, sizeof(sv), sv)) return st;
+    if (mapsq_status st = (dev ? readback : sync_read)(ctx, err, sizeof(sv), sv)) return st;
     if (sv[0]) return ctx->fail(MAPSQ_ERR_INVALID_ARG, "an identifier outside the dictionary");
     uint64_t need;
     std::memcpy(&need, &sv[2], 8);
     if (need_bytes) *need_bytes = (int64_t)need;
-    if ((int64_t)need > cap_bytes)
+    if ((int64_t)need > cap_bytes) {
+        if (dev) HIPCHK_D(hipStreamSynchronize(ctx->stream));  // the call that fetches them follows
         return ctx->fail(MAPSQ_ERR_TOO_LARGE, "decoded terms need " + std::to_string(need) + " bytes");
+    }
     if (need > 0 && !bytes) return ctx->fail(MAPSQ_ERR_INVALID_ARG, "null output bytes");
     Block ob;
     uint8_t* out = bytes;

@@ -274,15 +274,20 @@ hipError_t launch_unpack_pos(const uint32_t* w0, const uint32_t* w1, uint64_t n,
 // are [off[q], off[q + 1])), for the PSO subject column (blockIdx.y 0) and the
 // POS object column (1).  A wave owns DIST_IPT * 64 consecutive rows: each row
 // is read once (its neighbour comes from the next lane), the heads are kept as
-// bit words and counted per predicate under a mask, and the block's counts meet
-// in LDS before one add per predicate; where many predicates meet in a block,
-// every head finds its predicate by itself.  20M triples, 15 predicates: 50
-// us; 100 with the row before fetched again and every head tested against the
-// predicate's bounds, 627 as two launches per predicate.
+// bit words and counted per predicate under a mask (where many predicates meet
+// in a wave's rows, every head finds its predicate by itself), and the block's
+// counts meet in LDS before one add per predicate, unless its rows hold more
+// predicates than there is room for.  20M triples, 15 predicates: 50 us; 100
+// with the row before fetched again and every head tested against the
+// predicate's bounds, 627 as two launches per predicate.  Where a block of a
+// small store holds several predicates, adding its heads to memory one by one
+// queues them on a few words: a load of 176,000 triples under 11 predicates
+// takes 400 us, 870 with that, and 1M under 300 takes 3.5 ms, 4.3 with it.
 constexpr int DIST_IPT = 32;
 constexpr uint32_t DIST_THREADS = 1024;
 constexpr uint32_t DIST_ROWS = DIST_THREADS * DIST_IPT;
-constexpr uint32_t DIST_FEW = 4;
+constexpr uint32_t DIST_FEW = 16;    // predicates of a wave's rows that are counted under masks
+constexpr uint32_t DIST_LDS = 1024;  // predicates of a block's rows that are counted in LDS
 
 // last q with off[q] <= row
 __device__ __forceinline__ uint32_t pred_at(const int64_t* __restrict__ off, uint32_t np, int64_t row) {
@@ -299,14 +304,15 @@ __global__ __launch_bounds__(DIST_THREADS) void distinct_kernel(const int32_t* _
                                                                 const int32_t* __restrict__ b, int64_t n,
                                                                 const int64_t* __restrict__ off, uint32_t np,
                                                                 unsigned long long* __restrict__ cnt) {
-    static_assert(DIST_IPT <= MQ_WAVE && DIST_FEW <= DIST_THREADS, "a lane per head word");
-    __shared__ uint32_t sh[DIST_FEW];
+    static_assert(DIST_IPT <= MQ_WAVE && DIST_LDS <= DIST_THREADS, "a lane per head word, a thread per count");
+    __shared__ uint32_t sh[DIST_LDS];
     const int32_t* __restrict__ x = blockIdx.y ? b : a;
     unsigned long long* out = cnt + (blockIdx.y ? np : 0u);
     const int64_t r0 = (int64_t)blockIdx.x * DIST_ROWS;
     const int64_t r1 = min(r0 + (int64_t)DIST_ROWS, n);
     const uint32_t q0 = pred_at(off, np, r0), q1 = pred_at(off, np, r1 - 1);
-    if (threadIdx.x < DIST_FEW) sh[threadIdx.x] = 0;
+    const bool lds = q1 - q0 < DIST_LDS;
+    if (threadIdx.x < DIST_LDS) sh[threadIdx.x] = 0;
     __syncthreads();
     const int64_t w0 = r0 + (int64_t)(threadIdx.x / MQ_WAVE) * (DIST_IPT * MQ_WAVE);
     if (w0 < r1) {  // wave-uniform
@@ -327,10 +333,10 @@ __global__ __launch_bounds__(DIST_THREADS) void distinct_kernel(const int32_t* _
                 if (lane() == (uint32_t)(p + i)) word = m;
             }
         }
-        if (q1 - q0 < DIST_FEW) {
-            for (uint32_t q = q0; q <= q1; q++) {
+        const uint32_t qa = pred_at(off, np, w0), qb = pred_at(off, np, w0 + rows - 1);
+        if (qb - qa < DIST_FEW) {
+            for (uint32_t q = qa; q <= qb; q++) {
                 const int64_t lo = off[q] - w0, hi = off[q + 1] - w0;  // the predicate's rows, wave-relative
-                if (lo >= (int64_t)rows || hi <= 0) continue;
                 const int64_t f = (int64_t)lane() * MQ_WAVE;  // the lane's first row
                 uint64_t mask = ~0ull;
                 if (lo > f) mask = lo - f >= MQ_WAVE ? 0ull : ~0ull << (lo - f);
@@ -339,7 +345,10 @@ __global__ __launch_bounds__(DIST_THREADS) void distinct_kernel(const int32_t* _
                 // a predicate's first row starts a run whatever came before it
                 if (lo >= f && lo < f + MQ_WAVE) heads |= 1ull << (lo - f);
                 const uint32_t c = last_lane(wave_incl_u32((uint32_t)__popcll(heads & mask)));
-                if (lane() == 0 && c) atomicAdd(&sh[q - q0], c);
+                if (lane() == 0 && c) {
+                    if (lds) atomicAdd(&sh[q - q0], c);
+                    else atomicAdd(out + q, (unsigned long long)c);
+                }
             }
         } else {
             for (uint32_t k = 0; k < DIST_IPT; k++) {
@@ -347,12 +356,15 @@ __global__ __launch_bounds__(DIST_THREADS) void distinct_kernel(const int32_t* _
                 const uint32_t at = k * MQ_WAVE + lane();
                 if (at >= rows) continue;
                 const uint32_t q = pred_at(off, np, w0 + at);
-                if (((m >> lane()) & 1ull) || w0 + at == off[q]) atomicAdd(out + q, 1ull);
+                if (((m >> lane()) & 1ull) || w0 + at == off[q]) {
+                    if (lds) atomicAdd(&sh[q - q0], 1u);
+                    else atomicAdd(out + q, 1ull);
+                }
             }
         }
     }
     __syncthreads();
-    if (q1 - q0 < DIST_FEW && threadIdx.x <= q1 - q0 && sh[threadIdx.x])
+    if (lds && threadIdx.x <= q1 - q0 && sh[threadIdx.x])
         atomicAdd(out + q0 + threadIdx.x, (unsigned long long)sh[threadIdx.x]);
 }
 

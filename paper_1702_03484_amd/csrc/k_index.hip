@@ -277,21 +277,21 @@ hipError_t launch_unpack_pos(const uint32_t* w0, const uint32_t* w1, uint64_t n,
 // bit words and counted per predicate under a mask (where many predicates meet
 // in a wave's rows, every head finds its predicate by itself), and the block's
 // counts meet in LDS before one add per predicate, unless its rows hold more
-// predicates than there is room for.  20M triples, 15 predicates: 50 us; 100
+// predicates than there is room for.  20M triples, 15 predicates: 53 us; 100
 // with the row before fetched again and every head tested against the
 // predicate's bounds, 627 as two launches per predicate.  Where a block of a
 // small store holds several predicates, adding its heads to memory one by one
-// queues them on a few words: a load of 176,000 triples under 11 predicates
-// takes 400 us, 870 with that, and 1M under 300 takes 3.5 ms, 4.3 with it.
+// queues them on a few words: 158,000 triples under 15 predicates take 8 us, 585
+// with that, and 1M under 300 take 12, 840 with it.  A search of the whole table
+// in each wave, through vector registers, took 18 us more at 50M.
 constexpr int DIST_IPT = 32;
 constexpr uint32_t DIST_THREADS = 1024;
 constexpr uint32_t DIST_ROWS = DIST_THREADS * DIST_IPT;
 constexpr uint32_t DIST_FEW = 16;    // predicates of a wave's rows that are counted under masks
 constexpr uint32_t DIST_LDS = 1024;  // predicates of a block's rows that are counted in LDS
 
-// last q with off[q] <= row
-__device__ __forceinline__ uint32_t pred_at(const int64_t* __restrict__ off, uint32_t np, int64_t row) {
-    uint32_t lo = 0, hi = np - 1;
+// last q of [lo, hi] with off[q] <= row (off[lo] is)
+__device__ __forceinline__ uint32_t pred_at(const int64_t* __restrict__ off, uint32_t lo, uint32_t hi, int64_t row) {
     while (lo < hi) {
         const uint32_t m = (lo + hi + 1) / 2;
         if (off[m] <= row) lo = m;
@@ -310,11 +310,13 @@ __global__ __launch_bounds__(DIST_THREADS) void distinct_kernel(const int32_t* _
     unsigned long long* out = cnt + (blockIdx.y ? np : 0u);
     const int64_t r0 = (int64_t)blockIdx.x * DIST_ROWS;
     const int64_t r1 = min(r0 + (int64_t)DIST_ROWS, n);
-    const uint32_t q0 = pred_at(off, np, r0), q1 = pred_at(off, np, r1 - 1);
+    const uint32_t q0 = pred_at(off, 0, np - 1, r0), q1 = pred_at(off, 0, np - 1, r1 - 1);
     const bool lds = q1 - q0 < DIST_LDS;
     if (threadIdx.x < DIST_LDS) sh[threadIdx.x] = 0;
     __syncthreads();
-    const int64_t w0 = r0 + (int64_t)(threadIdx.x / MQ_WAVE) * (DIST_IPT * MQ_WAVE);
+    // in a scalar register, and so are the wave's predicates and their bounds
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / MQ_WAVE);
+    const int64_t w0 = r0 + (int64_t)wave * (DIST_IPT * MQ_WAVE);
     if (w0 < r1) {  // wave-uniform
         const uint32_t rows = (uint32_t)min((int64_t)(DIST_IPT * MQ_WAVE), r1 - w0);
         uint32_t before = w0 > 0 ? (uint32_t)x[w0 - 1] : ~(uint32_t)x[0];
@@ -333,7 +335,8 @@ __global__ __launch_bounds__(DIST_THREADS) void distinct_kernel(const int32_t* _
                 if (lane() == (uint32_t)(p + i)) word = m;
             }
         }
-        const uint32_t qa = pred_at(off, np, w0), qb = pred_at(off, np, w0 + rows - 1);
+        // a search among the block's predicates only: none where it holds one
+        const uint32_t qa = pred_at(off, q0, q1, w0), qb = pred_at(off, q0, q1, w0 + rows - 1);
         if (qb - qa < DIST_FEW) {
             for (uint32_t q = qa; q <= qb; q++) {
                 const int64_t lo = off[q] - w0, hi = off[q + 1] - w0;  // the predicate's rows, wave-relative
@@ -355,7 +358,7 @@ __global__ __launch_bounds__(DIST_THREADS) void distinct_kernel(const int32_t* _
                 const uint64_t m = __shfl(word, (int)k);
                 const uint32_t at = k * MQ_WAVE + lane();
                 if (at >= rows) continue;
-                const uint32_t q = pred_at(off, np, w0 + at);
+                const uint32_t q = pred_at(off, qa, qb, w0 + at);
                 if (((m >> lane()) & 1ull) || w0 + at == off[q]) {
                     if (lds) atomicAdd(&sh[q - q0], 1u);
                     else atomicAdd(out + q, 1ull);
